@@ -64,8 +64,7 @@
 // Kernels
 //   k_fprep     per group: clamped count, request offset, statistics; the
 //               request total; per instance: Theta, the variance scale, class
-//               and first model; k_fslo: the SLOs widened to double; k_ftail:
-//               the normal-tail table
+//               and first model; k_fslo: the SLOs widened to double
 //   k_fseg      one lane per plan, one wavefront per (64 plans, segment):
 //               each segment's trailing queue piece
 //   k_fstart    one lane per plan: the sums at each segment's first slot
@@ -207,7 +206,6 @@ struct FArgs {
     FInst *inst;              // [I]
     int32_t *first;           // [G + 1] request offsets in req_slo
     double *slo64;            // [n_req] the SLOs in double
-    float2 *tail;             // [kCells]
     double *nreq;             // [1] requests scored
     FRec *bucket;             // [tiles][nblk][kBlkCap] the transposition's buckets
     int32_t *bcnt;            // [tiles][nblk] records in each bucket
@@ -316,14 +314,6 @@ __global__ __launch_bounds__(kThreads) void k_fslo(FArgs a)
     for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < a.n_req;
          k += (int64_t)gridDim.x * kThreads)
         a.slo64[k] = (double)a.req_slo[k];
-}
-
-__global__ __launch_bounds__(kThreads) void k_ftail(FArgs a)
-{
-    __shared__ float2 tab[qlm_tail::kCells];
-    qlm_tail::build<kThreads>(tab);
-    __syncthreads();
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kThreads) a.tail[k] = tab[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -847,9 +837,9 @@ __global__ __launch_bounds__(kTransThreads) void k_fbscreen(FArgs a, int64_t pc)
     uint32_t *w1 = w0 + kBlkCap;
     uint32_t *w2 = w1 + kBlkCap;
     uint32_t *w3 = w2 + kBlkCap;
-    __shared__ float2 tab[qlm_tail::kCells];
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
     __shared__ int next;
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kTransThreads) tab[k] = a.tail[k];
+    qlm_tail::stage(tab, (int)threadIdx.x, kTransThreads);
     if (threadIdx.x == 0) next = 0;
     const int nblk = (a.G + kBlk - 1) / kBlk;
     const int64_t tiles = (pc + kWave - 1) / kWave;
@@ -1176,7 +1166,7 @@ int64_t chunk_of(int32_t G, int64_t P, int64_t want)
 }
 
 struct FLayout {
-    size_t grp, req, inst, first, slo64, tail, nreq, bucket, bcnt, piece, start, part, F, bmin, ncand,
+    size_t grp, req, inst, first, slo64, nreq, bucket, bcnt, piece, start, part, F, bmin, ncand,
         cand, Q, total;
     int64_t chunk;
 };
@@ -1198,7 +1188,6 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     put(L.inst, sizeof(FInst) * (size_t)I);
     put(L.first, 4 * ((size_t)G + 1));
     put(L.slo64, 8 * ((size_t)n_req + 1));
-    put(L.tail, 8 * (size_t)qlm_tail::kCells);
     put(L.nreq, 8);
     const size_t tiles = (size_t)(L.chunk / kWave);
     const size_t nblk = (size_t)((G + kBlk - 1) / kBlk);
@@ -1256,7 +1245,6 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.inst = (FInst *)(w + L.inst);
     a.first = (int32_t *)(w + L.first);
     a.slo64 = (double *)(w + L.slo64);
-    a.tail = (float2 *)(w + L.tail);
     a.nreq = (double *)(w + L.nreq);
     a.bucket = (FRec *)(w + L.bucket);
     a.bcnt = (int32_t *)(w + L.bcnt);
@@ -1281,7 +1269,7 @@ int launched(const char *what)
 // Common start of every call: argument checks, the workspace, the per-call
 // tables.
 int fbegin(const qlm_problem *problem, const qlm_plans *plans, const float *req_slo,
-           int64_t n_req, void *ws, size_t ws_bytes, FArgs *out, FLayout *lay, bool need_tail,
+           int64_t n_req, void *ws, size_t ws_bytes, FArgs *out, FLayout *lay, bool screen,
            bool prep, hipStream_t stream)
 {
     int rc = check_problem(problem);
@@ -1311,15 +1299,11 @@ int fbegin(const qlm_problem *problem, const qlm_plans *plans, const float *req_
     if (plans->n_plans == 0 || !prep) return QLM_OK;
     hipLaunchKernelGGL(k_fprep, dim3(1), dim3(kThreads), 0, stream, *out);
     if ((rc = launched("k_fprep launch"))) return rc;
-    if (n_req > 0 && need_tail) {
+    if (n_req > 0 && screen) {
         int64_t blocks = (n_req + kThreads - 1) / kThreads;
         if (blocks > 4096) blocks = 4096;
         hipLaunchKernelGGL(k_fslo, dim3((unsigned)blocks), dim3(kThreads), 0, stream, *out);
         if ((rc = launched("k_fslo launch"))) return rc;
-    }
-    if (need_tail) {
-        hipLaunchKernelGGL(k_ftail, dim3(1), dim3(kThreads), 0, stream, *out);
-        if ((rc = launched("k_ftail launch"))) return rc;
     }
     return QLM_OK;
 }

@@ -114,8 +114,9 @@ struct ScoreArgs {
     int64_t P, ld;
     const int32_t *perm, *qoff;
     const uint32_t *evict;
-    int32_t nparts;           // wavefronts per tile: 1, 2 or 4
-    int32_t bound[3];         // slots where parts 1, 2, 3 of every plan start (multiples of 32)
+    int32_t nparts;           // wavefronts per tile: 1, 2, 4, 8 or 16
+    int32_t part_first;       // slots of a plan's first part, and of each later one, before
+    int32_t part_step;        // rounding (part_begin)
     double *score, *penalty;
     int64_t d_begin, d_count;
     float *d_mean, *d_sd, *d_prob;
@@ -125,6 +126,12 @@ struct ScoreArgs {
 };
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// First slot of part k of a plan, k >= 1 (a multiple of 32).
+__host__ __device__ inline int part_begin(int first, int step, int k)
+{
+    return (first + (k - 1) * step) & ~31;
+}
 
 // LDS of the scoring kernel.  The normal-tail table is a static array (8 KiB at
 // the start of LDS).  Dynamic part, byte addresses from `base`:
@@ -330,17 +337,6 @@ __device__ void stage_general(const ScoreArgs &a, const Lds &l)
     }
 }
 
-// The normal-tail table: cell k covers t in [1024 + k, 1025 + k), i.e. z from
-// (512 - k) / kTailScale down to (511 - k) / kTailScale, and holds the line
-// that fits Q best there (the chord, moved by half its deviation at the middle
-// of the cell).
-__device__ void stage_tail(float2 *tab)
-{
-    // a fixed trip count (the kernel runs kScoreThreads threads): no loop whose
-    // exit depends on the thread, after which uniform values would turn divergent
-    qlm_tail::build<kScoreThreads>(tab);
-}
-
 __device__ inline double wave_min(double v)
 {
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
@@ -479,6 +475,15 @@ __device__ void walk_general(const ScoreArgs &a, const Lds &L, uint32_t tail0, i
 }
 #pragma clang fp contract(on)
 
+// The sums of a lane's plan over its np parts (the lane's own wavefront holds
+// the first), the last part's first.
+__device__ inline double add_parts(const double *psum, int np)
+{
+    double t = psum[(np - 1) * kWave];
+    for (int k = np - 2; k >= 0; --k) t = psum[k * kWave] + t;
+    return t;
+}
+
 // Screening score of every plan.  One lane = one plan; the slots of a plan are
 // walked in order, so every prefix sum is a running sum.  Per slot: the
 // group's record (one LDS gather), the tokens ahead and the swap/eviction
@@ -492,14 +497,17 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
     __shared__ __align__(16) float2 s_tail[kTailCells];
     extern __shared__ __align__(16) unsigned char lds[];
     const Lds L = lds_layout(a, lds);
-    stage_tail(s_tail);
+    qlm_tail::stage(s_tail, (int)threadIdx.x, (int)blockDim.x);
     // The form of the group records: compact when every group, model and cost
     // fits it, else general (and every plan takes the exact walk).  Every
     // workgroup stages the same tables, so all take the same decision.  (The
     // flag goes through LDS and readfirstlane, so that the compiler knows it is
     // uniform: the fast path's scalar row addressing depends on that.)
-    __shared__ int s_compact;
-    if (threadIdx.x == 0) s_compact = 1;
+    __shared__ int s_compact, s_parts;
+    if (threadIdx.x == 0) {
+        s_compact = 1;
+        s_parts = a.nparts;
+    }
     __syncthreads();
     // (both tables are staged whatever the first one's answer)
     const bool costs_fit = stage_costs(a, L);
@@ -530,12 +538,14 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
     const uint32_t inst0 = L.inst;
     const uint32_t tail0 = lds_addr(s_tail);
 
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     // the wavefront index is uniform within a wavefront; say so, so that the
     // tile, its row addresses and the buffer resources live in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wpb = blockDim.x / kWave;
-    const int64_t ntiles = (a.P + kWave - 1) / kWave;
+    // (plan indices fit 32 bits: P <= plan_stride <= 2^22)
+    const int P = (int)a.P;
+    const int ntiles = (P + kWave - 1) / kWave;
     const int G = a.G;
     // G held in a vector register (a scalar operand would cost the gather's
     // clamp its short issue form)
@@ -546,33 +556,32 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
     const int cs3 = a.col_shift + 3;          // log2(bytes per cost-table row)
     double lane_min = INFINITY;
 
-    // With a.nparts = 2 or 4 every tile (64 plans) is scored by that many
-    // wavefronts of the workgroup: part k takes slots [bound[k-1], bound[k])
-    // (bound[-1] = 0, bound[nparts-1] = G), each part after the first after a
-    // warm-up that rebuilds the running sums of the queue holding its first
-    // slot.  The partial sums pass through the outputs from the last part to
-    // the first, one barrier apart; the first part adds its own last.  Tiles
-    // are taken in rounds, the same number for every wavefront of the
-    // workgroup.
+    // With a.nparts > 1 every tile (64 plans) is scored by that many wavefronts
+    // of the workgroup: part k takes the slots from part_begin(k) to
+    // part_begin(k + 1) (the first from 0, the last to G), each part after the
+    // first after a warm-up that rebuilds the running sums of the queue holding
+    // its first slot.  The partial sums meet in LDS, in the place of the tail
+    // table (16 wavefronts of 64 sums fill it exactly), and the first part adds
+    // them, the last part's first.  Tiles are taken in rounds, the same number
+    // for every wavefront of the workgroup; a launch with parts has one round
+    // (score_grid), so the table is not needed again.
     const int np = a.nparts;
-    const bool halves = np > 1;
     const int per_round = wpb / np;
     const int in_round = wave / np;
     const int part = wave & (np - 1);
     const bool back = part > 0;
-    const int s_begin = back ? a.bound[part - 1] : 0;
-    const int s_end = part < np - 1 ? a.bound[part] : G;
+    const int s_begin = back ? part_begin(a.part_first, a.part_step, part) : 0;
+    const int s_end = part < np - 1 ? part_begin(a.part_first, a.part_step, part + 1) : G;
     if (!compact) {
       // General records: the front wavefront of each tile walks the whole plan
       // exactly (walk_general); the back one, if any, idles.
-      for (int64_t r0 = (int64_t)blockIdx.x * per_round; r0 < ntiles;
-           r0 += (int64_t)gridDim.x * per_round) {
-        const int64_t t = r0 + in_round;
+      for (int r0 = (int)blockIdx.x * per_round; r0 < ntiles; r0 += (int)gridDim.x * per_round) {
+        const int t = r0 + in_round;
         if (back || t >= ntiles) continue;
-        const int64_t tb = t * kWave;
-        const bool live = tb + lane < a.P;
-        const int lp = live ? lane : (int)(a.P - 1 - tb);
-        const int64_t p = tb + lp;
+        const int tb = t * kWave;
+        const bool live = tb + lane < P;
+        const int lp = live ? lane : P - 1 - tb;
+        const int p = tb + lp;
         const bool det = DETAIL && live && p >= a.d_begin && p < a.d_begin + a.d_count;
         double S = 0.0, PE = 0.0;
         walk_general<EVICT, PEN, DETAIL>(a, L, tail0, tb, lp, det, p - a.d_begin, S, PE);
@@ -583,16 +592,16 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
         }
       }
     } else
-    for (int64_t r0 = (int64_t)blockIdx.x * per_round; r0 < ntiles; r0 += (int64_t)gridDim.x * per_round) {
-      const int64_t t = r0 + in_round;
+    for (int r0 = (int)blockIdx.x * per_round; r0 < ntiles; r0 += (int)gridDim.x * per_round) {
+      const int t = r0 + in_round;
       double S_out = 0.0, PE_out = 0.0;
-      int64_t p_out = -1;                           // the lane's plan when live
+      int p_out = -1;                               // the lane's plan when live
       if (t < ntiles) {
-        const int64_t tb = t * kWave;               // first plan of the tile (uniform)
-        const bool live = tb + lane < a.P;
-        const int lp = live ? lane : (int)(a.P - 1 - tb);   // lane's plan, relative to tb
+        const int tb = t * kWave;                   // first plan of the tile (uniform)
+        const bool live = tb + lane < P;
+        const int lp = live ? lane : P - 1 - tb;    // lane's plan, relative to tb
         const uint32_t lpb = (uint32_t)lp * 4u;     // its byte offset within a row
-        const int64_t p = tb + lp;
+        const int p = tb + lp;
         const bool det = DETAIL && live && p >= a.d_begin && p < a.d_begin + a.d_count;
         const int64_t dq = p - a.d_begin;
         // Row r of a slot-major array, lane's column: a plain global load (queue
@@ -602,12 +611,12 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
         const int64_t ld4 = ld * 4;
         auto at = [&](const void *base, int row) __attribute__((always_inline)) {
             const unsigned char *rp =
-                reinterpret_cast<const unsigned char *>(base) + (int64_t)row * ld4 + tb * 4;
+                reinterpret_cast<const unsigned char *>(base) + (int64_t)row * ld4 + (int64_t)tb * 4;
             return *reinterpret_cast<const uint32_t *>(rp + lpb);
         };
         auto rsrc_at = [&](const void *base, int row) __attribute__((always_inline)) {
             const unsigned char *rp =
-                reinterpret_cast<const unsigned char *>(base) + (int64_t)row * ld4 + tb * 4;
+                reinterpret_cast<const unsigned char *>(base) + (int64_t)row * ld4 + (int64_t)tb * 4;
             return __builtin_amdgcn_make_buffer_rsrc((void *)rp, (short)0, 0x7FFFFFFF, 0x00020000);
         };
         // (non-temporal: every plan row is read once, and streaming it past the
@@ -655,7 +664,7 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
         // index), so that the compiler counts the outstanding loads exactly.
         // (the lane's queue-offset column: one 32 x 32 -> 64-bit multiply-add
         // per row; plan_stride <= 2^22 keeps the row pitch within 32 bits)
-        const unsigned char *qcol = reinterpret_cast<const unsigned char *>(a.qoff) + tb * 4 + lpb;
+        const unsigned char *qcol = reinterpret_cast<const unsigned char *>(a.qoff) + (int64_t)tb * 4 + lpb;
         const uint32_t ld4u = (uint32_t)ld4;
         auto load_qp = [&](int h) __attribute__((always_inline)) {
             h = min(h, I1);                   // g >= 0 wherever this is called
@@ -1077,22 +1086,22 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
             p_out = p;
         }
       }
-      if (halves) {
-          // the later parts' sums go through the outputs to the first part
-          for (int k = np - 1; k >= 1; --k) {
-              if (part == k && p_out >= 0) {
-                  if (k < np - 1) {
-                      S_out += a.score[p_out];
-                      if (PEN) PE_out += a.penalty[p_out];
-                  }
-                  a.score[p_out] = S_out;
-                  if (PEN) a.penalty[p_out] = PE_out;
-              }
+      // (read anew, not held in a register through the walk)
+      const int parts = __builtin_amdgcn_readfirstlane(s_parts);
+      if (parts > 1) {
+          static_assert(sizeof(s_tail) == sizeof(double) * kScoreThreads, "a partial sum per thread");
+          // (the lane found anew: nothing of the thread index lives through the walk)
+          const int me = wave * kWave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+          double *psum = reinterpret_cast<double *>(s_tail) + me;
+          __syncthreads();                          // every walk is done with the table
+          *psum = S_out;
+          __syncthreads();
+          if (!back) S_out = add_parts(psum, parts);
+          if (PEN) {
               __syncthreads();
-          }
-          if (!back && p_out >= 0) {
-              S_out += a.score[p_out];
-              if (PEN) PE_out += a.penalty[p_out];
+              *psum = PE_out;
+              __syncthreads();
+              if (!back) PE_out = add_parts(psum, parts);
           }
       }
       if (!back && p_out >= 0) {
@@ -1703,15 +1712,16 @@ int device_cus(int *cus)
 }
 
 struct OccKey {
-    int dev;
+    int dev, threads;
     ScoreKernel k;
     size_t lds;
 };
 std::mutex g_occ_mu;
 std::vector<std::pair<OccKey, std::pair<int, int>>> g_occ;   // -> (CUs, blocks per CU)
 
-// CU count and resident workgroups per CU for kernel k with lds bytes, cached.
-int occupancy(ScoreKernel k, size_t lds, int *cus, int *per_cu)
+// CU count and resident workgroups per CU for kernel k with that many threads
+// and lds bytes, cached.
+int occupancy(ScoreKernel k, int threads, size_t lds, int *cus, int *per_cu)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1719,7 +1729,8 @@ int occupancy(ScoreKernel k, size_t lds, int *cus, int *per_cu)
     {
         std::lock_guard<std::mutex> lk(g_occ_mu);
         for (auto &it : g_occ)
-            if (it.first.dev == dev && it.first.k == k && it.first.lds == lds) {
+            if (it.first.dev == dev && it.first.threads == threads && it.first.k == k &&
+                it.first.lds == lds) {
                 *cus = it.second.first;
                 *per_cu = it.second.second;
                 return QLM_OK;
@@ -1729,60 +1740,91 @@ int occupancy(ScoreKernel k, size_t lds, int *cus, int *per_cu)
     if (rc) return rc;
     e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void *)k, kScoreThreads, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void *)k, threads, lds);
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (*per_cu < 1) *per_cu = 1;
     std::lock_guard<std::mutex> lk(g_occ_mu);
-    g_occ.push_back({OccKey{dev, k, lds}, {*cus, *per_cu}});
+    g_occ.push_back({OccKey{dev, threads, k, lds}, {*cus, *per_cu}});
     return QLM_OK;
 }
 
-// Slots where parts 1 .. n-1 of every plan start when each plan is split
-// into n parts: multiples of 32, each part at least 64 slots.  A part after
-// the first also rebuilds about one queue's running sums (w slots), so it is
-// given that much less: the first part takes (G + (n - 1) w) / n slots.
-// Returns false when no such split exists.
-bool part_bounds(int G, int I, int n, int32_t *bound)
+// The split of every plan into n parts: multiples of 32 slots, each part at
+// least 32.  A part after the first also rebuilds about one queue's running
+// sums (w slots), so it is given that much less: the first part takes
+// (G + (n - 1) w) / n slots.  Returns false when no such split exists.
+bool part_split(int G, int I, int n, int32_t *first, int32_t *step)
 {
     const int w = G / I;
-    const int first = (G + (n - 1) * w) / n;
+    *first = (G + (n - 1) * w) / n;
+    *step = *first - w;
     int prev = 0;
     for (int k = 1; k < n; ++k) {
-        const int b = (first + (k - 1) * (first - w)) & ~31;
-        if (b - prev < 64) return false;
-        bound[k - 1] = b;
+        const int b = part_begin(*first, *step, k);
+        if (b - prev < 32) return false;
         prev = b;
     }
-    return G - prev >= 64;
+    return G - prev >= 32;
+}
+
+// Workgroups of the scoring kernel that can be resident with `waves`
+// wavefronts each.
+int score_resident(ScoreKernel k, int waves, size_t lds, int *cus, int64_t *blocks)
+{
+    int per_cu = 0;
+    const int rc = occupancy(k, waves * kWave, lds, cus, &per_cu);
+    *blocks = (int64_t)per_cu * *cus;
+    return rc;
 }
 
 // Grid of the scoring kernel: persistent, at most as many workgroups as fit.
-// When the tiles (64 plans each) fill at most a quarter (or half) of the
-// wavefronts the chip holds at once, every tile is split between four (or
-// two) wavefronts (part_bounds); four only where the queues are short against
-// a part (a part's warm-up rebuilds one queue's sums).
-int score_grid(ScoreKernel k, size_t lds, int64_t P, int G, int I, int *grid, int *nparts,
-               int32_t *bound)
+//
+// A wavefront walks its slots one after another, so while the chip has room a
+// tile (64 plans) is split between up to 16 wavefronts: as many as keep every
+// wavefront resident and the warm-ups (each part but the first rebuilds about
+// one queue's sums) at no more than half of the plan's own slots, or all of
+// them while there is at most one wavefront a SIMD.  Measured (k_score alone,
+// parts 4 / 8 / 16): 8192 groups and 2048 plans 247 / 163 / 137 us; 1024 groups
+// and 4096 plans 51 / 40 / 40 us, 16384 plans 52 / 43 / 45 us, 24000 plans with
+// detail 107 / 90 / 115 us.
+//
+// Workgroups hold 16 wavefronts, and fewer (down to one tile's) where that
+// leaves CUs without a workgroup: 16384 plans of 128 groups on 16 workgroups
+// took 50 us, on 256 32 us (unsplit), 23 us split in four.
+int score_grid(ScoreKernel k, size_t lds, int64_t P, int G, int I, int *grid, int *threads,
+               int32_t *nparts, int32_t *first, int32_t *step)
 {
-    int cus = 0, per_cu = 0;
-    int rc = occupancy(k, lds, &cus, &per_cu);
+    int cus = 0;
+    int64_t fit = 0;
+    int wpb = kScoreThreads / kWave;
+    int rc = score_resident(k, wpb, lds, &cus, &fit);
     if (rc) return rc;
-    const int wpb = kScoreThreads / kWave;
     const int64_t tiles = (P + kWave - 1) / kWave;
-    const int64_t resident = (int64_t)per_cu * cus * wpb;
-    int np = 1;
-    if (G >= 512 && 8 * (G / I) <= G && 4 * tiles <= resident && part_bounds(G, I, 4, bound))
-        np = 4;
-    else if (G >= 256 && 2 * tiles <= resident && part_bounds(G, I, 2, bound))
-        np = 2;
-    for (int k = np - 1; k < 3; ++k) bound[k] = G;
-    *nparts = np;
-    const int per_round = wpb / np;
-    const int64_t need = (tiles + per_round - 1) / per_round;
-    int64_t g = (int64_t)per_cu * cus;
-    if (g > need) g = need;
+    const int w = G / I;
+    int n = wpb;
+    for (; n > 1; n /= 2) {
+        const int64_t warm = (int64_t)(n - 1) * w;
+        if (n * tiles <= fit * wpb && (2 * warm <= G || (warm <= G && n * tiles <= 4 * cus)) &&
+            part_split(G, I, n, first, step))
+            break;
+    }
+    if (n == 1) *first = *step = G;
+    int64_t need = (tiles + wpb / n - 1) / (wpb / n);
+    while (wpb > n && 10 * need < 9 * (int64_t)cus) {
+        // (all of them resident still: a launch with parts has one round)
+        int64_t fit2 = 0;
+        rc = score_resident(k, wpb / 2, lds, &cus, &fit2);
+        if (rc) return rc;
+        const int64_t need2 = (tiles + wpb / 2 / n - 1) / (wpb / 2 / n);
+        if (need2 > fit2) break;
+        wpb /= 2;
+        need = need2;
+        fit = fit2;
+    }
+    int64_t g = fit < need ? fit : need;
     if (g > kMaxScoreBlocks) g = kMaxScoreBlocks;
     if (g < 1) g = 1;
+    *nparts = n;
+    *threads = wpb * kWave;
     *grid = (int)g;
     return QLM_OK;
 }
@@ -1814,9 +1856,9 @@ int launch_score(const qlm_problem *pr, const qlm_plans *pl, double *score, doub
     const bool use_det = det && det->plan_count > 0 &&
                          (det->wait_mean || det->wait_sd || det->prob);
     ScoreKernel k = pick_kernel(ev, penalty != nullptr, use_det);
-    int grid = 1;
+    int grid = 1, threads = kScoreThreads;
     int rc = score_grid(k, geo.lds_bytes, pl->n_plans, pr->n_groups, pr->n_instances, &grid,
-                        &a.nparts, a.bound);
+                        &threads, &a.nparts, &a.part_first, &a.part_step);
     if (rc) return rc;
     if (grid_out) *grid_out = grid;
 
@@ -1825,7 +1867,7 @@ int launch_score(const qlm_problem *pr, const qlm_plans *pl, double *score, doub
         rc = qlm_internal::timing_begin(stream, &tl);
         if (rc) return rc;
     }
-    hipLaunchKernelGGL(k, dim3(grid), dim3(kScoreThreads), geo.lds_bytes, stream, a);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), geo.lds_bytes, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_score launch");
     if (timed) qlm_internal::timing_end(stream, &tl);

@@ -63,8 +63,6 @@
 //   k_srank    once per call: the groups ranked by SLO (partial counts per
 //              tile of 1024 groups; k_srankout sums them, places each group
 //              at its rank and writes the group records)
-//   k_stail    once per call: the normal-tail table, which the screens copy
-//              into LDS
 //   k_sload    start plans, slot-major -> chain-major working copies
 //   k_sstate   one wavefront per queue: slot records, the exact running sums,
 //              the cached margins, the queue score (k_stotal: their sum)
@@ -185,7 +183,6 @@ struct SearchArgs {
     GRec *grec;                   // [G]
     int32_t *by_slo;              // [G] groups in SLO order
     int32_t *rank_part;           // [ceil(G / kRankTile)][G] partial ranks
-    float2 *tail;                 // [kCells] the normal-tail table (tail.h)
     // per chain, chain b at b * (per-chain size)
     int32_t *perm;                // [G]
     uint8_t *flag;                // [G]
@@ -610,15 +607,6 @@ __global__ __launch_bounds__(kThreads) void k_sgrec(SearchArgs a)
     a.grec[i] = group_record(a, i);
 }
 
-// The normal-tail table, once per call, for the screens to copy into LDS.
-__global__ __launch_bounds__(kThreads) void k_stail(SearchArgs a)
-{
-    __shared__ float2 tab[qlm_tail::kCells];
-    qlm_tail::build<kThreads>(tab);
-    __syncthreads();
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kThreads) a.tail[k] = tab[k];
-}
-
 // Start plans into the working copies; qoff is forced to a monotone split of
 // [0, G] and group ids to [0, G) so that every later access stays in bounds.
 __global__ __launch_bounds__(kThreads) void k_sload(SearchArgs a, qlm_plans pl)
@@ -1022,7 +1010,7 @@ __device__ inline double tail_walk(const TrAt &tr_at, const VAt &v_at, const flo
 // tasks G + s*W + d - 1 the moves SWAP(s, d).
 __global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
 {
-    __shared__ float2 tab[qlm_tail::kCells];
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
     __shared__ double lmin[kWaves];
     __shared__ int lint_lo[kWaves], lint_hi[kWaves];
     // one buffer: first the slot records the lanes visit, then their tails
@@ -1054,7 +1042,7 @@ __global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
     const bool rec_lds = vhi - vlo <= kSwapRecs;
     const int ncost = a.swap_cost ? a.C * a.M * a.M : 0;
     const bool cost_lds = ncost <= kSwapCostStage;
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kThreads) tab[k] = a.tail[k];
+    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
     if (rec_lds)
         for (int u = vlo + (int)threadIdx.x; u < vhi; u += kThreads) st_r[u - vlo] = sr[u];
     if (cost_lds)
@@ -1204,7 +1192,7 @@ __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, flo
     const bool pm_lds = eq - bq <= kPmaxSlots;
     const int ncost = a.swap_cost ? a.C * a.M * a.M : 0;
     const bool cost_lds = ncost <= kSwapCostStage;
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kThreads) tab[k] = a.tail[k];
+    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
     if (pm_lds)
         for (int u = bq + (int)threadIdx.x; u < eq; u += kThreads) pmax[u - bq] = sr[u].pmax;
     if (cost_lds)
@@ -1373,7 +1361,7 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
     TRec *st = stall + wave_id() * kRelStage;
     const int ncost = a.swap_cost ? a.C * a.M * a.M : 0;
     const bool cost_lds = ncost <= kSwapCostStage;
-    for (int k = threadIdx.x; k < qlm_tail::kCells; k += kThreads) tab[k] = a.tail[k];
+    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
     if (cost_lds)
         for (int k = threadIdx.x; k < ncost; k += kThreads) st_c[k] = a.swap_cost[k];
     __syncthreads();
@@ -1480,7 +1468,7 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_fmove(
     SearchArgs a)
 {
-    __shared__ float2 tab[qlm_tail::kCells];
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
     __shared__ double lmin[kWaves];
     __shared__ int lint[kWaves];
     // (the move screens stage kStage records and seven blank ones)
@@ -2251,7 +2239,7 @@ struct Layout {
     int nwg_a, nwg_b, nwg, nwg_f, nwg_r, nws;
     int64_t n_moves;
     size_t grec, by_slo, rank_part, perm, flag, qof, inv, srec, sst, trec, R, RD, Q, Nq, Es, T, cur, done, steps,
-        wmin_s, wmin_i, smin, F, D, cand, cex, ncand, U, scratch, dq, tail, total;
+        wmin_s, wmin_i, smin, F, D, cand, cex, ncand, U, scratch, dq, total;
 };
 
 Layout layout(int G, int I, int W, int64_t B)
@@ -2302,7 +2290,6 @@ Layout layout(int G, int I, int W, int64_t B)
     L.U = take(8 * b);
     L.scratch = take(8 * (size_t)G * b);
     L.dq = take(16 * b);
-    L.tail = take(sizeof(float2) * qlm_tail::kCells);
     L.total = o;
     return L;
 }
@@ -2378,7 +2365,6 @@ SearchArgs search_args(const qlm_problem *pr, int64_t B, int32_t W, unsigned cha
     a.U = (double *)(ws + L.U);
     a.scratch = (int32_t *)(ws + L.scratch);
     a.dq = (int32_t *)(ws + L.dq);
-    a.tail = (float2 *)(ws + L.tail);
     a.nwg_a = L.nwg_a;
     a.nwg_b = L.nwg_b;
     a.nwg = L.nwg;
@@ -2395,8 +2381,7 @@ int launched(const char *what)
     return e == hipSuccess ? QLM_OK : hip_fail(e, what);
 }
 
-// Checks, the group records, and (for the screens) the SLO ranks and the tail
-// table.
+// Checks, the group records, and (for the screens) the SLO ranks.
 int search_begin(const qlm_problem *pr, const qlm_plans *pl, int32_t W, void *ws, size_t ws_bytes,
                  SearchArgs *out, hipStream_t stream, bool screens = true)
 {
@@ -2424,11 +2409,8 @@ int search_begin(const qlm_problem *pr, const qlm_plans *pl, int32_t W, void *ws
         if (rc) return rc;
         hipLaunchKernelGGL(k_srankout, dim3((a.G + kThreads - 1) / kThreads), dim3(kThreads), 0,
                            stream, a, ntiles);
-        rc = launched("k_srankout launch");
+        return launched("k_srankout launch");
     }
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_stail, dim3(1), dim3(kThreads), 0, stream, a);
-    return launched("k_stail launch");
 }
 
 int launch_state(SearchArgs &a, int force, hipStream_t stream)

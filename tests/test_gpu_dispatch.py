@@ -1,0 +1,63 @@
+"""The dispatch rules' branches against the oracle, each at the sizes where it
+can go wrong: the smallest it takes, remainders, and either side of its line."""
+import numpy as np
+import pytest
+
+from gpu_util import SCORE_REL, assert_argmin, device_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def qlm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_00047_amd import qlm as q
+    q.library()
+    return q
+
+
+def make(G, I, P, seed, M=4, evict=True, loaded=True, sizes=(16, 128), ld=None):
+    """A random problem and plans of any size (fields as workload.make_problem)."""
+    from paper_2407_00047_amd import workload
+    rng = np.random.default_rng(seed)
+    C = min(3, I)
+    f = np.float32
+    swap = rng.uniform(5.0, 40.0, (C, M, M)).astype(f)
+    pr = {"seed": seed, "n_groups": G, "n_instances": I, "n_models": M, "n_classes": C,
+          "grp_count": rng.integers(sizes[0], sizes[1] + 1, G).astype(np.int32),
+          "grp_mu": rng.uniform(50, 600, G).astype(f), "grp_var": rng.uniform(1e3, 1e5, G).astype(f),
+          "grp_model": rng.integers(0, M, G).astype(np.int32),
+          "grp_slo": np.where(rng.random(G) < 0.3, 20.0, rng.uniform(100, 2000, G)).astype(f),
+          "inst_tput": rng.choice([800.0, 1500.0, 6000.0], I).astype(f),
+          "inst_class": rng.integers(0, C, I).astype(np.int32),
+          "inst_model0": rng.integers(-1, M, I).astype(np.int32) if loaded else None,
+          "swap_cost": swap.reshape(-1), "evict_cost": 2.0 if evict else 0.0,
+          "n_evict": max(1, G // 20) if evict else 0}
+    return pr, workload.make_plans(pr, 0, P, ld=ld)
+
+
+# Wavefronts per tile (1 to 16 parts of a plan) and per workgroup: from plans
+# too short to split to sixteen parts, one tile to more tiles than wavefronts fit
+@pytest.mark.parametrize("G,I,P,evict", [
+    (31, 3, 65, True), (64, 2, 200, False), (96, 3, 4100, True), (128, 4, 5000, False),
+    (160, 5, 700, True), (511, 8, 300, True), (545, 17, 2049, False), (1024, 16, 130, True),
+    (1000, 16, 9001, True), (2048, 16, 70, False), (2051, 5, 333, True), (4096, 64, 1030, True)])
+def test_score_parts(qlm, orc, G, I, P, evict):
+    import torch
+    pr, pl = make(G, I, P, 1000 + G, evict=evict)
+    dpr, dpl = device_inputs(pr, pl)
+    print("case parts", G, I, P, flush=True)
+    res = qlm.rwt_score(dpr, dpl, penalty=True)
+    bi, bs = qlm.best_plan(dpr, dpl)
+    torch.cuda.synchronize()
+    osc, ope = orc.score_plans(pr, pl)
+    err = np.abs(res["score"].cpu().numpy() - osc)
+    assert np.all(err <= SCORE_REL * dpr.total_requests), err.max()
+    # the bound of test_gpu_parity.test_scores_match_oracle
+    mag = (ope + pr["grp_slo"].astype(np.float64).sum()) + np.abs(pr["grp_slo"]).sum()
+    perr = np.abs(res["penalty"].cpu().numpy() - ope)
+    assert np.all(perr <= 2.0 * (2.0 ** -36 + (2 * G + 4) * 2.0 ** -53) * mag), perr.max()
+    _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
+    assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
