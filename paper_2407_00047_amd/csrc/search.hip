@@ -2091,42 +2091,214 @@ __device__ inline uint64_t seed_key(const SeedArgs &a, int pol, int i)
     return (hi << 32) | order_key(f);
 }
 
-// Each group's rank in its seed's order (grid: 64 groups x seeds).
-__global__ __launch_bounds__(kThreads) void k_seedrank(SeedArgs a)
+// Each group's rank in its seed's order (grid: 64 groups x seeds): the keys
+// pass through LDS in tiles, and each of the workgroup's 16 wavefronts counts,
+// for the same 64 groups, one slice of every tile.  (Four wavefronts left one
+// on each SIMD and took 70 us for two seeds of 8192 groups; sixteen take 32.)
+constexpr int kSeedRankThreads = 1024;
+constexpr int kSeedRankWaves = kSeedRankThreads / kWave;
+
+__global__ __launch_bounds__(kSeedRankThreads) void k_seedrank(SeedArgs a)
 {
-    __shared__ uint64_t keys[kRankTile];
-    __shared__ int part[kThreads];
+    __shared__ __align__(16) uint64_t keys[kRankTile];
+    __shared__ int part[kSeedRankThreads];
     const int seed = blockIdx.y;
     const int pol = a.policy[seed];
     const int G = a.G;
-    const int li = threadIdx.x & (kWave - 1), quarter = threadIdx.x / kWave;
+    const int li = threadIdx.x & (kWave - 1);
     const int i = blockIdx.x * kWave + li;
+    // keys below `mine` order before this group, and equal ones of a lower id:
+    // those below mine + 1 (a key's upper word is a model at most)
     const uint64_t mine = i < G ? seed_key(a, pol, i) : 0u;
+    constexpr int kSlice = kRankTile / kSeedRankWaves;
+    const int base = wave_id() * kSlice;
     int cnt = 0;
     for (int t0 = 0; t0 < G; t0 += kRankTile) {
         __syncthreads();
-        for (int k = threadIdx.x; k < kRankTile; k += kThreads)
+        for (int k = threadIdx.x; k < kRankTile; k += kSeedRankThreads)
             keys[k] = t0 + k < G ? seed_key(a, pol, t0 + k) : ~0ull;
         __syncthreads();
-        const int base = quarter * (kRankTile / kWaves);
-#pragma unroll 4
-        for (int k = 0; k < kRankTile / kWaves; ++k) {
-            const uint64_t o = keys[base + k];
-            const int id = t0 + base + k;       // ids past G hold the largest key
-            cnt += (o < mine || (o == mine && id < i)) ? 1 : 0;
-        }
+        const int lower = i - (t0 + base);      // ids of the slice below i
+#pragma unroll 8
+        for (int k = 0; k < kSlice; ++k)
+            cnt += keys[base + k] < mine + (k < lower ? 1u : 0u) ? 1 : 0;
     }
     part[threadIdx.x] = cnt;
     __syncthreads();
-    if (quarter == 0 && i < G)
-        a.order[(int64_t)seed * G + part[li] + part[li + kWave] + part[li + 2 * kWave] +
-                part[li + 3 * kWave]] = i;
+    if (threadIdx.x < kWave && i < G) {
+        for (int w = 1; w < kSeedRankWaves; ++w) cnt += part[w * kWave + li];
+        a.order[(int64_t)seed * G + cnt] = i;
+    }
 }
 
 #pragma clang fp contract(off)
 
-// Placement, one wavefront per seed: groups in order; each lane evaluates the
-// drain time of its queues (q = lane, lane + 64, ...), the lowest drain time
+// The lowest of 64 lanes' unsigned words, in every lane (a scalar).
+__device__ inline uint32_t wave_min_u32(uint32_t v)
+{
+    // within rows of 16 by shifts, then across the rows (lane 63 ends with all)
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));   // row_shr:1
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));   // row_shr:2
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));   // row_shr:4
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));   // row_shr:8
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));   // row_bcast:15
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The lane with the lowest d (the lowest lane on ties, as `<` decides; lane 0
+// when no d is below infinity).
+__device__ __attribute__((noinline)) int wave_argmin(double d)
+{
+    // the order of doubles as the order of unsigned words; -0 counts as +0, and
+    // infinity and NaN come after everything else
+    const uint64_t b = (uint64_t)__double_as_longlong(d + 0.0);
+    const uint64_t key = d < INFINITY ? ((b >> 63) ? ~b : (b | (1ull << 63))) : ~0ull;
+    const uint32_t hi = (uint32_t)(key >> 32);
+    const bool tied = hi == wave_min_u32(hi);
+    const uint32_t lo = tied ? (uint32_t)key : 0xFFFFFFFFu;
+    const uint32_t lowest = wave_min_u32(lo);
+    return (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(tied && lo == lowest));
+}
+
+// Placement with at most 64 queues, one wavefront per seed and one queue per
+// lane, the queues' states in registers.  Each choice depends on the one before:
+// a chain of G steps, whose single wavefront issues one instruction after
+// another, about 4.8 cycles each; so a step is cut to few instructions.
+//  - The lanes compare drain times formed with a product by 1 / Theta and, of
+//    those, the upper words alone: where all tokens and costs are >= 0 such a
+//    time is within 2^-50 of the definition's, which moves its upper word by one
+//    at most, so a lane whose word is lower than every other's by more than one
+//    holds the lowest.  Any other case (one step in some thousands on random
+//    groups, and every step with a negative token count or cost) forms the
+//    definition's drain times and compares them in full.
+//  - The groups' tokens and rows of the costs come from LDS, read two steps
+//    ahead, and the costs that the next group may need (in a queue as it stands
+//    or after the group in hand) one step ahead.
+//  - The positions within the queues follow from 64 choices at a time.
+// 8192 groups on 64 queues: 1225 us; 2520 with the division formed ahead for
+// both outcomes of a step (135 instructions), 8467 with the states in LDS.
+// kSwap: swap costs, staged in LDS with a row of zeros for "no model loaded"
+// before each class's rows and a zero diagonal, so that a read needs no test.
+constexpr int kSeedChunk = 512;                // groups staged at a time
+
+struct alignas(16) SeedGroup {
+    double tok;                                // n mu
+    uint32_t row, col;                         // byte offsets of its model's row and column
+};
+
+template <bool kSwap>
+__global__ __launch_bounds__(kWave) void k_seedassign_wave(SeedArgs a)
+{
+    extern __shared__ __align__(16) float sw[];
+    __shared__ SeedGroup ring[kSeedChunk + 2];
+    __shared__ int count[kWave];
+    const int seed = blockIdx.x;
+    const int G = a.G, I = a.I, M = a.M;
+    const int lane = threadIdx.x;
+    bool plain = true;                         // every token count and cost is >= 0
+    if (kSwap)
+        for (int k = lane; k < a.C * (M + 1) * M; k += kWave) {
+            const int m = k % M, l = (k / M) % (M + 1) - 1, c = k / (M * (M + 1));
+            const float v = l >= 0 && l != m ? a.swap_cost[((int64_t)c * M + l) * M + m] : 0.0f;
+            plain = plain && v >= 0.0f;
+            sw[k] = v;
+        }
+    count[lane] = 0;
+    const int32_t *order = a.order + (int64_t)seed * G;
+    int32_t *owner = a.owner + (int64_t)seed * G;
+    int32_t *pos = a.pos + (int64_t)seed * G;
+    const int q = min(lane, I - 1);
+    const double theta = (double)a.inst_tput[q];
+    const double inv = 1.0 / theta;
+    plain = plain && theta > 0.0 && theta < INFINITY;
+    const unsigned char *costs = reinterpret_cast<const unsigned char *>(sw);
+    // this lane's rows of the costs: from "none", then models 0 .. M-1
+    const uint32_t rows = (uint32_t)(clampi(a.inst_class[q], 0, a.C - 1) * (M + 1) * M * 4);
+    uint32_t row = rows;                       // the row of the model its queue ends with
+    if (a.inst_model0) row += (uint32_t)((clampi(a.inst_model0[q], -1, M - 1) + 1) * M * 4);
+    auto cost = [&](uint32_t r, uint32_t col) __attribute__((always_inline)) -> float {
+        return kSwap ? *reinterpret_cast<const float *>(costs + r + col) : 0.0f;
+    };
+    double A = 0.0;
+    double K = lane < I ? 0.0 : INFINITY;      // no queue: never the lowest
+    float sc = 0.0f;                           // the group in hand's swap cost
+    // how far above the lowest upper word another has to be to be passed over
+    uint32_t slack = __builtin_amdgcn_ballot_w64(!plain) == 0 ? 1u : 0xFFFFFFFFu;
+    for (int c0 = 0; c0 < G; c0 += kSeedChunk) {
+        const int nc = min(kSeedChunk, G - c0);
+        __syncthreads();
+        bool neg = false;
+        for (int k = lane; k < nc + 2; k += kWave) {
+            const int i = order[min(c0 + k, G - 1)];
+            const int m = clampi(a.grp_model[i], 0, M - 1);
+            SeedGroup e;
+            e.tok = (double)a.grp_count[i] * (double)a.grp_mu[i];
+            e.row = (uint32_t)((m + 1) * M * 4);
+            e.col = (uint32_t)(m * 4);
+            neg = neg || !(e.tok >= 0.0);
+            ring[k] = e;
+        }
+        __syncthreads();
+        if (__builtin_amdgcn_ballot_w64(neg)) slack = 0xFFFFFFFFu;
+        SeedGroup e0 = ring[0], e1 = ring[1];
+        if (c0 == 0) sc = cost(row, e0.col);
+        for (int b0 = 0; b0 < nc; b0 += kWave) {
+            const int n = min(kWave, nc - b0);
+            const SeedGroup *next = ring + b0 + 2;
+            int own = 0;                       // of the group this lane holds
+            auto step = [&](int j) __attribute__((always_inline)) {
+                const SeedGroup e2 = next[j];
+                const uint32_t taken = rows + e0.row;   // the row if this queue takes the group
+                const float x = cost(row, e1.col), y = cost(taken, e1.col);
+                const double A1 = A + e0.tok, K1 = K + (double)sc;
+                const uint32_t hi = (uint32_t)__double2hiint(fma(A1, inv, K1));
+                const uint32_t lowest = wave_min_u32(hi);
+                const uint64_t near = __builtin_amdgcn_ballot_w64(hi - lowest <= slack);
+                int best = (int)__builtin_ctzll(near);
+                if (__builtin_expect(__builtin_popcountll(near) != 1, 0))
+                    best = __builtin_amdgcn_readfirstlane(wave_argmin(A1 / theta + K1));
+                own = lane == j ? best : own;
+                const bool won = lane == best;
+                A = won ? A1 : A;
+                K = won ? K1 : K;
+                row = won ? taken : row;
+                sc = won ? y : x;
+                e0 = e1;
+                e1 = e2;
+            };
+            int j = 0;
+            for (; j + 4 <= n; j += 4) {       // (no copies from one step to the next)
+                step(j);
+                step(j + 1);
+                step(j + 2);
+                step(j + 3);
+            }
+            for (; j < n; ++j) step(j);
+            // the lanes of the same queue, and each one's rank among them
+            uint64_t same = __builtin_amdgcn_ballot_w64(lane < n);
+            for (int bit = 0; bit < 6; ++bit) {
+                const bool set = (own >> bit) & 1;
+                const uint64_t with = __builtin_amdgcn_ballot_w64(set);
+                same &= set ? with : ~with;
+            }
+            if (lane < n) {
+                const int rank = __builtin_popcountll(same & ((1ull << lane) - 1ull));
+                const int base = count[own];
+                owner[c0 + b0 + lane] = own;
+                pos[c0 + b0 + lane] = base + rank;
+                // (in step: every lane has read its base before the last of
+                // each queue's lanes writes the new one)
+                if ((same >> lane) == 1ull) count[own] = base + rank + 1;
+            }
+        }
+    }
+    __syncthreads();
+    if (lane < I) a.qcount[(int64_t)seed * I + lane] = count[lane];
+}
+
+// Placement with more than 64 queues, one wavefront per seed: groups in order;
+// each lane evaluates the drain time of its queues (q = lane, lane + 64, ...), the lowest drain time
 // (then the lowest queue) wins, and the winning queue takes the group.
 __global__ __launch_bounds__(kWave) void k_seedassign(SeedArgs a)
 {
@@ -2210,13 +2382,20 @@ __global__ __launch_bounds__(kThreads) void k_seedwrite(SeedArgs a)
     const int seed = blockIdx.x;
     const int G = a.G, I = a.I;
     const int64_t st = a.out.plan_stride;
-    if (threadIdx.x == 0) {
-        int t = 0;
-        qo[0] = 0;
-        for (int q = 0; q < I; ++q) {
-            t += a.qcount[(int64_t)seed * I + q];
-            qo[q + 1] = t;
+    if (threadIdx.x < kWave) {
+        // the queues' first slots: a scan of their counts, 64 at a time
+        int before = 0;
+        for (int q0 = 0; q0 < I; q0 += kWave) {
+            const int q = q0 + (int)threadIdx.x;
+            int t = q < I ? a.qcount[(int64_t)seed * I + q] : 0;
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int y = __shfl_up(t, o, kWave);
+                if ((int)threadIdx.x >= o) t += y;
+            }
+            if (q < I) qo[q + 1] = before + t;
+            before += __shfl(t, kWave - 1, kWave);
         }
+        if (threadIdx.x == 0) qo[0] = 0;
     }
     __syncthreads();
     for (int q = threadIdx.x; q <= I; q += kThreads) a.out.qoff[(int64_t)q * st + seed] = qo[q];
@@ -2600,13 +2779,20 @@ int qlm_seed_plans(const qlm_problem *problem, int32_t n, const int32_t *policy,
     a.out = *out;
     const size_t swap_bytes = problem->swap_cost ? sizeof(float) * (size_t)a.C * a.M * a.M : 0;
     a.swap_in_lds = swap_bytes > 0 && swap_bytes <= kSeedSwapLds;
-    const size_t lds = 24 * (size_t)I + (a.swap_in_lds ? swap_bytes : 0);
-    hipError_t e = hipFuncSetAttribute((const void *)k_seedassign,
+    // a queue per lane while the queues fit a wavefront and the costs (with
+    // their rows of zeros) fit LDS
+    const size_t wave_lds = swap_bytes + (swap_bytes ? sizeof(float) * (size_t)a.C * a.M : 0);
+    const bool one = I <= kWave && wave_lds <= kSeedSwapLds;
+    const size_t lds = one ? wave_lds : 24 * (size_t)I + (a.swap_in_lds ? swap_bytes : 0);
+    void (*assign)(SeedArgs) = !one ? &k_seedassign
+                               : swap_bytes ? &k_seedassign_wave<true> : &k_seedassign_wave<false>;
+    hipError_t e = hipFuncSetAttribute((const void *)assign,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-    hipLaunchKernelGGL(k_seedrank, dim3((G + kWave - 1) / kWave, n), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_seedrank, dim3((G + kWave - 1) / kWave, n), dim3(kSeedRankThreads), 0,
+                       stream, a);
     if ((rc = launched("k_seedrank launch"))) return rc;
-    hipLaunchKernelGGL(k_seedassign, dim3(n), dim3(kWave), lds, stream, a);
+    hipLaunchKernelGGL(assign, dim3(n), dim3(kWave), lds, stream, a);
     if ((rc = launched("k_seedassign launch"))) return rc;
     hipLaunchKernelGGL(k_seedwrite, dim3(n), dim3(kThreads), 0, stream, a);
     return launched("k_seedwrite launch");

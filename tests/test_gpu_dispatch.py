@@ -61,3 +61,36 @@ def test_score_parts(qlm, orc, G, I, P, evict):
     assert np.all(perr <= 2.0 * (2.0 ** -36 + (2 * G + 4) * 2.0 ** -53) * mag), perr.max()
     _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
     assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
+
+
+# Seeds: a queue per lane up to 64 queues and the LDS form past them; chunks of
+# 512 groups and batches of 64; equal drain times (identical instances and
+# groups, groups without tokens) and negative tokens, which the approximate
+# comparison leaves to the full one
+@pytest.mark.parametrize("G,I,kind", [
+    (1, 1, "plain"), (63, 3, "plain"), (65, 64, "plain"), (130, 65, "plain"), (511, 7, "plain"),
+    (513, 63, "ties"), (1027, 64, "plain"), (700, 16, "negative"), (600, 5, "no swap"),
+    (300, 130, "ties")])
+def test_seed_lanes(qlm, orc, G, I, kind):
+    import torch
+    pr, _ = make(G, I, 1, 77 + G, evict=False)
+    rng = np.random.default_rng(G)
+    if kind == "ties":
+        pr["inst_tput"][:] = 1500.0
+        pr["inst_class"][:] = 0
+        pr["grp_count"] = rng.choice([0, 8], G).astype(np.int32)
+        pr["grp_mu"][:] = 100.0
+        pr["swap_cost"][:] = 7.0
+    if kind == "negative":
+        pr["grp_mu"] = rng.uniform(-300.0, 600.0, G).astype(np.float32)
+    if kind == "no swap":
+        pr["swap_cost"] = None
+    dpr, _ = device_inputs(pr, {"perm": np.zeros((G, 1), np.int32),
+                                "qoff": np.zeros((I + 1, 1), np.int32)})
+    print("case seeds", G, I, kind, flush=True)
+    sp = qlm.seed_plans(dpr, (0, 1))
+    torch.cuda.synchronize()
+    for k in (0, 1):
+        perm, qoff = orc.seed_plan(pr, k)
+        assert np.array_equal(sp.perm[:, k].cpu().numpy(), perm)
+        assert np.array_equal(sp.qoff[:, k].cpu().numpy(), qoff)
