@@ -391,11 +391,11 @@ int qlm_seed_plans(const qlm_problem *problem, int32_t n, const int32_t *policy,
  * With one request per group and req_slo = grp_slo this is the group score.
  *
  * Every call takes a device workspace, 256-byte aligned, used as scratch.
- * The plans are screened in chunks: a chunk of c plans needs 16 bytes per
- * group and plan for the groups' starts, and every call 8 bytes per request
- * and 8 (I + 2) bytes per plan.  qlm_fcfs_workspace_bytes(problem, n_plans,
+ * The plans are screened in chunks: a chunk of c plans needs about 19 bytes per
+ * group and plan for the lists of groups, and every call a quarter of a byte per
+ * request and 8 (I + 2) bytes per plan.  qlm_fcfs_workspace_bytes(problem, n_plans,
  * n_requests, chunk_plans) is the size for chunks of chunk_plans plans
- * (rounded up to a multiple of 64; 0 = as many as 1 GiB of starts holds, the
+ * (rounded up to a multiple of 64; 0 = as many as 1 GiB of lists holds, the
  * size to use), 0 for an invalid problem.  A call uses the largest chunk the
  * workspace it is given holds, so any workspace of at least the size for
  * chunk_plans = 64 works; smaller chunks only take more launches.  Calls that
@@ -412,7 +412,8 @@ size_t qlm_fcfs_workspace_bytes(const qlm_problem *problem, int64_t n_plans, int
  * r = 0 and throughout groups without variance.  Method: per group and plan,
  * the start E[W] in double (one walk of each queue); per request, the margin
  * in double, the variance in single precision and the normal tail from the
- * 1024-cell table; single-precision sums of at most 32 terms.
+ * 1024-cell table, except where that is surely exactly 0 or 1;
+ * single-precision sums of at most 32 terms.
  */
 int qlm_fcfs_score(const qlm_problem *problem, const qlm_plans *plans, const float *req_slo,
                    int64_t n_requests, void *ws, size_t ws_bytes, double *score,
@@ -514,7 +515,7 @@ const char *qlm_last_error(void);
  * kernel of every qlm_rwt_score / qlm_best_plan call, the kernel that scores
  * the reassignment moves in every qlm_search_moves / qlm_search_screen call
  * and every step of qlm_local_search, the candidate kernel of every
- * qlm_place_group call, and the per-request screening kernel of every plan
+ * qlm_place_group call, and the per-request kernel of every plan
  * chunk of qlm_fcfs_score / qlm_fcfs_best_plan.  qlm_timing_read waits for the recorded events and
  * returns the number of timed launches and their summed duration in
  * milliseconds since the last reset, then resets.

@@ -20,27 +20,29 @@
 // that, not for memory traffic.
 //
 // Screen.  The running sums are per position (one walk of each plan), the
-// tails are per request.  The walk produces, for every group and plan, the
-// group's start E[W] = A/Theta + K (double), its variance ahead (single,
-// scaled for the tail table) and its queue, gathered group by group; the
-// screen then takes one lane per plan and one wavefront per (64 plans, one
-// group): all 64 lanes work on the same group at a time, so the request SLOs
-// are the same across the wavefront and come through the scalar cache, the
-// request's position in its group is a constant of the unrolled loop, and
-// each request costs a margin in double, a variance in single and one read of
-// the normal-tail table (11 vector instructions).
+// tails are per request.  Most requests need no tail: a spread is tens of
+// seconds, waits and SLOs are hundreds or thousands apart, and where a margin is
+// beyond six spreads the tail table holds exactly 0 or 1.  The walk forms, at
+// every position, the group's start E[W] = A/Theta + K (double) and its variance
+// ahead (single, scaled for the tail table), and compares them with the group's
+// earliest and latest SLO: a group whose requests all lie on one side adds 0 or
+// its request count.  The others are listed; another kernel takes 64 of them at a
+// time, one per lane, and looks at their blocks of 32 requests in the same way; the
+// blocks that remain are listed again, and 64 of those are evaluated at
+// a time, a block per lane: per request a margin in double, a variance in single
+// and one read of the normal-tail table.  (8192 groups of 128 requests, random
+// plans: 14% of the groups and 41% of their blocks remain.)
 //
 // The walk reads the plans slot-major with every lane (plan) of a wavefront at
 // the same slot, so its reads are coalesced.  It is cut into segments of 128
-// slots: k_fseg sums each segment's trailing queue piece, k_fstart chains the
-// pieces into each segment's starting sums, and k_frec walks each segment
-// again from them and forms the records.  The records belong in the rows of
-// the groups, a different row in every lane: this transposition from the
-// plans' slot order to group order is the price of the screen's shared SLOs.
-// It runs in two passes: k_frec sorts every 8 slots' records by block of 128
-// groups in LDS and appends each block's run to the block's bucket of the
-// tile; k_fbscreen places each bucket's records in LDS by (group, plan) and
-// screens them there.
+// slots (32 or 64 for few plans): k_fseg sums each segment's trailing queue piece, k_fstart chains the
+// pieces into each segment's starting sums, and k_fwalk walks each segment again
+// from them.
+//
+// Sums.  A block's terms are added in single precision (32 terms at most) and
+// join the plan's sum over the segment as a 64-bit fixed-point number (2^-32: the
+// segment's requests stay below 2^29), so that the order in which blocks are
+// evaluated changes no bit; the segments' sums are added in order, in double.
 //
 // Screening bound, per request: table error below 2.2e-6; single-precision
 // rounding of the cell coordinate, of the line's evaluation, of the margin and
@@ -50,10 +52,10 @@
 // below 2^-50 E[W_r]: negligible while E[W_r] <= 2^30 SD[W_r] (true of any
 // plan whose variances are not zero or vanishingly small).  A request with
 // SD = 0 at r = 0 (a queue's first group, or one behind groups without
-// variance) takes the exact comparison with the oracle's E[W] (formed in the
-// oracle's order: where a segment starts with nothing varying ahead, its sums
-// are formed again from the queue's first slot); a group without variance is
-// walked with exact comparisons throughout.
+// variance) is decided by the sign of its margin, the exact comparison with the
+// oracle's E[W] (formed in the oracle's order: where a segment starts with
+// nothing varying ahead, its sums are formed again from the queue's first slot);
+// a group without variance there is compared exactly throughout.
 //
 // Exact argmin.  Plans whose screened score is within twice the bound of the
 // lowest are re-scored exactly (k_fexact: one workgroup per queue, the running
@@ -64,17 +66,15 @@
 // Kernels
 //   k_fprep     per group: clamped count, request offset, statistics; the
 //               request total; per instance: Theta, the variance scale, class
-//               and first model; k_fslo: the SLOs widened to double
+//               and first model; k_fblocks: each group's and block's first and
+//               last SLO
 //   k_fseg      one lane per plan, one wavefront per (64 plans, segment):
 //               each segment's trailing queue piece
 //   k_fstart    one lane per plan: the sums at each segment's first slot
-//   k_frec      as k_fseg: the records of the segment's groups, into the
-//               buckets of their group blocks (k_fbzero clears the counts);
-//               a tile's workgroups on one XCD
-//   k_fbscreen  one workgroup per (64 plans, 128 groups): the bucket into LDS
-//               by (group, plan), then the partial screened scores, one
-//               wavefront per group at a time (lane = plan)
-//   k_fsum      partial scores -> screened plan scores, and the per-block
+//   k_fwalk     as k_fseg: the walk, and the list of the groups that are not sure
+//   k_ftails    one workgroup per (64 plans, segment): the listed groups' blocks
+//               and tails
+//   k_fsum      the segments' sums -> screened plan scores, and the per-block
 //               minimum
 //   k_fselect   the plans within the bound of the lowest -> candidates
 //   k_fexact    one workgroup per (candidate, queue): exact queue scores
@@ -103,74 +103,67 @@ using qlm_ripple::wave_id;
 constexpr int kWave = 64;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kSeg = 128;                   // slots per segment of the queue walks
-constexpr int kSegThreads = 1024;           // k_fseg: 16 wavefronts, one workgroup per CU
+constexpr int kSeg = 128;                   // most slots per segment of the queue walks
+constexpr int kMinSeg = 32;                 // and fewest (segment_of)
+constexpr int kSegThreads = 1024;           // k_fseg, k_fwalk: at most 16 wavefronts a workgroup
 constexpr int kSegWaves = kSegThreads / kWave;
+constexpr int kSegBlocks = 230;             // workgroups that (nearly) every CU has one of
 constexpr size_t kSegLdsLimit = 160 * 1024; // LDS of one workgroup
-constexpr int kBlk = 128;                   // groups per bucket of the transposition
-constexpr int kBlkCap = kBlk * 64;          // records per bucket (a tile's plans)
-constexpr int kSub = 8;                     // slots a walk sorts into buckets at a time
-constexpr int kRecWaves = 4;                // wavefronts of a k_frec workgroup
-constexpr int kXcds = 8;                    // XCDs of the device (workgroups dealt in turn)
-constexpr size_t kFrecTabLimit = 16 * 1024; // k_frec: most bytes of tables copied into LDS
-constexpr size_t kCuLds = 160 * 1024;       // LDS of one CU
+constexpr int kPrepThreads = 256;
+constexpr int kReqBlk = 32;                 // requests of a block of a group
+constexpr int kHalf = 16;                   // of which so many are evaluated at a time
+constexpr int kSub = 8;                     // slots of a k_fwalk batch
+constexpr int kTailWaves = 4;               // wavefronts of a k_ftails workgroup
+constexpr int kBlockList = 2 * kWave;       // blocks a wavefront's list holds
 constexpr int kMaxFcfsGroups = 1 << 16;
 constexpr int kMaxFcfsInstances = 4096;
-constexpr int kMaxBlocks = kMaxFcfsGroups / kBlk;
 constexpr int kSumBlocks = 1024;            // k_fsum blocks (per-block minima)
 constexpr int kExactBlocks = 256;
 constexpr int kPickThreads = 256;
 constexpr uint32_t kCountMask = (1u << 21) - 1u;
-constexpr uint32_t kNoVar = 1u << 31;       // record flag: no variance ahead
 constexpr double kEpsP = 8e-6;              // screening bound per request
 constexpr int64_t kMaxRequests = (int64_t)1 << 31;
-constexpr size_t kRecBudget = (size_t)1 << 30;    // bytes of group records per chunk
+constexpr size_t kChunkBudget = (size_t)1 << 30;  // bytes of lists and segment sums per chunk
+// Tail cells beyond which a tail is surely in an end cell (exactly 0 or 1): the
+// table's half width, 512, and room for the rounding of margin and spread.
+constexpr float kSureCells = 516.0f;
 
 // Per group, built once per call: for the walks (the count clamped to 21 bits,
-// the model clamped to [0, M)) ...
+// the model clamped to [0, M), the bounds of the group's SLOs) in 16 bytes, so
+// that a table of 8192 groups fits LDS.  The bounds are the upper halves of
+// floats, rounded outwards (a sure side may be missed for it, never mistaken) ...
 struct FGrp {
     float mu, var;
-    uint32_t cnt;
-    uint32_t model;
+    uint32_t cm;                // count | model << 21
+    uint32_t bounds;            // upper half of the lowest SLO | of the highest << 16
 };
+__device__ inline uint32_t grp_count(const FGrp &g) { return g.cm & kCountMask; }
+__device__ inline int grp_model(const FGrp &g) { return (int)(g.cm >> 21); }
+__device__ inline float grp_smin(const FGrp &g) { return __uint_as_float(g.bounds << 16); }
+__device__ inline float grp_smax(const FGrp &g) { return __uint_as_float(g.bounds & 0xFFFF0000u); }
 
-// ... and for the requests: how many are scored (clamped to n_requests).
+// ... and for the requests: how many are scored (clamped to n_requests), and
+// where their SLOs start.
 struct FReq {
-    float mu, var;
-    uint32_t n;
-    uint32_t pad;
+    uint32_t first, n;
 };
 
-// Per instance, for the walks: Theta, the table scale over Theta^2, the class
+// Per instance, for the walks: Theta, its reciprocal (for what need not be exact),
+// the table scale over Theta^2, the class
 // clamped to [0, C), the model loaded at the start (-1: none).
 struct FInst {
-    double theta, vscale;
+    double theta, inv, vscale;
     int32_t cls, m0;
-    int32_t pad[2];
 };
 
-// A slot's group start in one plan: E[W] of its first request, its variance
-// ahead V / Theta^2 times the table's scale, and its queue (| kNoVar when
-// V = 0).
-struct FRec {
+// A listed group of a plan: the start E[W] of its first request, its variance
+// ahead V / Theta^2 times the table's scale, group | lane of the plan << 16.
+// Its queue is in a list beside.
+struct FEntry {
     double c0;
     float v0;
-    uint32_t q;
+    uint32_t id;
 };
-
-// The transposition's streaming reads (each bucket record read once):
-// non-temporal.  (For k_frec's bucket appends, runs of a few records merged
-// into lines in L2, non-temporal stores were slower.)
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline FRec ld_rec_nt(const FRec *p)
-{
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    FRec r;
-    r.c0 = __hiloint2double((int)v.y, (int)v.x);
-    r.v0 = __uint_as_float(v.z);
-    r.q = v.w;
-    return r;
-}
 
 // Sums over the slots of one segment of a plan that belong to the queue open
 // at the segment's end (tokens, variance, fixed costs), whether that queue
@@ -205,38 +198,37 @@ struct FArgs {
     FReq *req;                // [G]
     FInst *inst;              // [I]
     int32_t *first;           // [G + 1] request offsets in req_slo
-    double *slo64;            // [n_req] the SLOs in double
+    float2 *blk;              // lowest and highest SLO of each block (block_of)
     double *nreq;             // [1] requests scored
-    FRec *bucket;             // [tiles][nblk][kBlkCap] the transposition's buckets
-    int32_t *bcnt;            // [tiles][nblk] records in each bucket
+    FEntry *list;             // [tiles][nseg][kSeg * 64] the listed groups
+    uint16_t *listq;          // and their queues
+    int32_t *listn;           // [tiles][nseg] how many
     Piece *piece;             // [nseg][chunk]
     Start *start;             // [nseg][chunk]
-    double *part;             // [ceil(G / kBlk)][chunk] partial screened scores
+    double *part;             // [nseg][chunk] the segments' screened scores
     double *F;                // [P] screened scores
     double *bmin;             // [kSumBlocks]
     int32_t *ncand;           // [1]
     int64_t *cand;            // [P]
     double *Q;                // [P][I] exact queue scores
+    double *parts;            // [2 kExactBlocks] their sums of sixteen slices, when tasks are shared
     int64_t chunk;
+    int32_t seg, nseg;        // slots per segment, segments of a plan
 };
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-template <class T>
-__device__ inline const __attribute__((address_space(4))) T *as_const(const T *p)
+// Block b of a group whose requests start at `first`, group i, in FArgs::blk: a
+// group of n requests from `first` on has at most floor(n / 32) + 1 blocks, so
+// the groups' ranges do not overlap.
+__device__ inline int64_t block_of(uint32_t first, int i, int b)
 {
-    return (const __attribute__((address_space(4))) T *)p;
+    return (int64_t)(first / kReqBlk) + i + b;
 }
 
 __device__ inline double wave_min(double v)
 {
     for (int o = kWave / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-__device__ inline int wave_max_int(int v)
-{
-    for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
     return v;
 }
 
@@ -252,68 +244,98 @@ __device__ inline bool better(double s, int64_t i, double s2, int64_t i2)
 // ---------------------------------------------------------------------------
 // Per-call tables
 
-// One workgroup: clamped counts, request offsets (an exclusive scan), group
-// statistics, the request total.
-__global__ __launch_bounds__(kThreads) void k_fprep(FArgs a)
+// Clamped counts, request offsets, group statistics, the request total, the
+// instance table.  A workgroup takes 256 groups and adds up every count before
+// them itself, coalesced and all in flight: 8192 groups take 6.7 us on 32
+// workgroups, and took 48 in one workgroup that scanned them.
+__global__ __launch_bounds__(kPrepThreads) void k_fprep(FArgs a)
 {
-    __shared__ int64_t part[kThreads];
-    const int t = threadIdx.x;
-    const int per = (a.G + kThreads - 1) / kThreads;
-    const int b = t * per, e = min(a.G, b + per);
-    int64_t s = 0;
-    for (int i = b; i < e; ++i) s += (int64_t)((uint32_t)a.grp_count[i] & kCountMask);
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int k = 0; k < kThreads; ++k) {
-            const int64_t v = part[k];
-            part[k] = run;
-            run += v;
-        }
+    __shared__ int64_t part[kPrepThreads / kWave], mine[kPrepThreads / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = wave_id();
+    const int b0 = (int)blockIdx.x * kPrepThreads;
+    int64_t before = 0;
+#pragma unroll 8
+    for (int k = t; k < b0; k += kPrepThreads)
+        before += (int64_t)((uint32_t)a.grp_count[k] & kCountMask);
+    const int i = b0 + t;
+    const int64_t want = i < a.G ? (int64_t)((uint32_t)a.grp_count[i] & kCountMask) : 0;
+    int64_t off = want;                        // inclusive scan over the wavefront
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t y = __shfl_up(off, o, kWave);
+        if (lane >= o) off += y;
     }
+    for (int o = kWave / 2; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
+    if (lane == kWave - 1) mine[w] = off;
+    if (lane == 0) part[w] = before;
     __syncthreads();
-    int64_t off = part[t];
-    for (int i = b; i < e; ++i) {
-        const int64_t want = (int64_t)((uint32_t)a.grp_count[i] & kCountMask);
+    off -= want;
+    for (int k = 0; k < kPrepThreads / kWave; ++k) off += part[k] + (k < w ? mine[k] : 0);
+    if (i < a.G) {
         const int64_t lo = off < a.n_req ? off : a.n_req;
         const int64_t hi = off + want < a.n_req ? off + want : a.n_req;
-        a.first[i] = (int32_t)lo;
         FGrp g;
         g.mu = a.grp_mu[i];
         g.var = a.grp_var[i];
-        g.cnt = (uint32_t)want;
-        g.model = (uint32_t)clampi(a.grp_model[i], 0, a.M - 1);
+        g.cm = (uint32_t)want | ((uint32_t)clampi(a.grp_model[i], 0, a.M - 1) << 21);
+        g.bounds = 0x7F80FF80u;                // none sure, before k_fblocks (-inf, inf)
         a.grp[i] = g;
         FReq r;
-        r.mu = g.mu;
-        r.var = g.var;
+        r.first = (uint32_t)lo;
         r.n = (uint32_t)(hi - lo);
-        r.pad = 0u;
         a.req[i] = r;
-        off += want;
+        if (i == a.G - 1) {
+            a.nreq[0] = (double)hi;
+            a.ncand[0] = 0;
+        }
     }
-    for (int q = t; q < a.I; q += kThreads) {
+    for (int q = i; q < a.I; q += (int)gridDim.x * kPrepThreads) {
         FInst v;
         v.theta = (double)a.inst_tput[q];
+        v.inv = 1.0 / v.theta;
         v.vscale = qlm_tail::kVarScale / (v.theta * v.theta);
         v.cls = clampi(a.inst_class[q], 0, a.C - 1);
         v.m0 = a.inst_model0 ? clampi(a.inst_model0[q], -1, a.M - 1) : -1;
-        v.pad[0] = v.pad[1] = 0;
         a.inst[q] = v;
-    }
-    // the last thread's range ends at G: its offset is then the total
-    if (t == kThreads - 1) {
-        a.first[a.G] = (int32_t)(off < a.n_req ? off : a.n_req);
-        a.nreq[0] = (double)(off < a.n_req ? off : a.n_req);
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_fslo(FArgs a)
+// The lowest and highest SLO of every block of 32 requests of a group, and of the
+// group: one wavefront per group, two blocks at a time.
+__global__ __launch_bounds__(kThreads) void k_fblocks(FArgs a)
 {
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < a.n_req;
-         k += (int64_t)gridDim.x * kThreads)
-        a.slo64[k] = (double)a.req_slo[k];
+    const int i = (int)blockIdx.x * kWaves + wave_id();
+    if (i >= a.G) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const FReq q = a.req[i];
+    float gmin = INFINITY, gmax = -INFINITY;
+    for (int r0 = 0; r0 < (int)q.n; r0 += kWave) {
+        const int r = r0 + lane;
+        float lo = INFINITY, hi = -INFINITY;
+        if (r < (int)q.n) {
+            const float v = a.req_slo[q.first + r];
+            lo = v == v ? v : -INFINITY;
+            hi = v == v ? v : INFINITY;
+        }
+        for (int o = kReqBlk / 2; o > 0; o >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o, kWave));
+            hi = fmaxf(hi, __shfl_xor(hi, o, kWave));
+        }
+        if ((lane & (kReqBlk - 1)) == 0 && r < (int)q.n)
+            a.blk[block_of(q.first, i, r / kReqBlk)] = make_float2(lo, hi);
+        gmin = fminf(gmin, fminf(lo, __shfl_xor(lo, kReqBlk, kWave)));
+        gmax = fmaxf(gmax, fmaxf(hi, __shfl_xor(hi, kReqBlk, kWave)));
+    }
+    if (lane == 0) {
+        if (!(a.grp[i].mu >= 0.0f)) {
+            gmin = -INFINITY;
+            gmax = INFINITY;
+        }
+        // outwards: the upper half as it is rounds towards zero
+        uint32_t lo = __float_as_uint(gmin), hi = __float_as_uint(gmax);
+        if ((lo & 0x80000000u) && (lo & 0xFFFFu)) lo += 0x10000u;
+        if (!(hi & 0x80000000u) && (hi & 0xFFFFu)) hi += 0x10000u;
+        a.grp[i].bounds = (lo >> 16) | (hi & 0xFFFF0000u);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -327,10 +349,21 @@ __global__ __launch_bounds__(kThreads) void k_fslo(FArgs a)
 constexpr int kAhead = 3;      // queue boundaries a walk holds beyond the open queue's
 static_assert(kAhead == 3, "open_queue settles nh and three boundaries");
 
+// x / y, y's reciprocal r correctly rounded: a product and two corrections by its
+// exact remainder give the correctly rounded quotient (Markstein's theorem; x and
+// y are products and copies of single-precision numbers, far from overflow and
+// underflow).  Half of a division's instructions.
+__device__ inline double quotient(double x, double y, double r)
+{
+    double q = x * r;
+    q = fma(fma(-q, y, x), r, q);
+    return fma(fma(-q, y, x), r, q);
+}
+
 struct Walk {
     int q, nh;                 // open queue, first slot of the next queue
     int nx[kAhead];            // qoff[q + 2 + j] (j < kAhead), -1 where not read
-    double theta, vscale;
+    double theta, inv, vscale;
     int cls, prev;
     double A, V, K;
 };
@@ -340,6 +373,7 @@ __device__ inline void set_queue(const FInst *inst, int q, Walk &w)
     const FInst v = inst[q];
     w.q = q;
     w.theta = v.theta;
+    w.inv = v.inv;
     w.vscale = v.vscale;
     w.cls = v.cls;
     w.prev = v.m0;
@@ -359,6 +393,24 @@ __device__ inline void open_queue(const FArgs &a, const FInst *inst, int64_t p, 
         w.nx[j] = q + 2 + j <= a.I ? a.qoff[(int64_t)(q + 2 + j) * a.ld + p] : -1;
     asm volatile("" ::"v"(w.nh), "v"(w.nx[0]), "v"(w.nx[1]), "v"(w.nx[2]));
     set_queue(inst, q, w);
+}
+
+// Slot s lies past the open queue: open the queue that holds it.
+__device__ inline void next_queue(const FArgs &a, const FInst *inst, int64_t p, int s, Walk &w)
+{
+    if (w.q + 1 < a.I && w.nx[0] >= 0 && (w.q + 2 >= a.I || w.nx[0] > s)) {
+        // the next queue (qoff[q+1] <= s < qoff[q+2]), from the boundaries held
+        // (a negative one is taken as not held)
+        w.nh = w.nx[0];
+#pragma unroll
+        for (int j = 0; j + 1 < kAhead; ++j) w.nx[j] = w.nx[j + 1];
+        w.nx[kAhead - 1] = -1;
+        set_queue(inst, w.q + 1, w);
+    } else {
+        int q = w.q;
+        while (q + 1 < a.I && a.qoff[(int64_t)(q + 1) * a.ld + p] <= s) ++q;
+        open_queue(a, inst, p, q, w);
+    }
 }
 
 // The queue holding slot s: the largest q with qoff[q] <= s.
@@ -381,8 +433,7 @@ __device__ inline int queue_at(const FArgs &a, int64_t p, int s)
 // multiples of B (so one eviction word covers a batch); slots before s0 are
 // passed over.  At a queue's first slot (the next queue's first slot reached,
 // empty queues skipped) the sums restart; then the slot's model-change and
-// eviction costs; visit(s, i, w) sees the sums on entry to the slot (fixed
-// costs included); then the group's tokens and variance join the sums.  Ids
+// eviction costs; then the group's tokens and variance join the sums.  Ids
 // out of range (a malformed plan) are skipped.  The group records and swap
 // costs are read from grp and swc: the problem's own arrays, or copies in LDS.
 template <int B>
@@ -410,14 +461,9 @@ __device__ inline void batch_groups(const FArgs &a, const FGrp *grp, const Batch
     for (int u = 0; u < B; ++u) gr[u] = grp[clampi(b.ids[u], 0, a.G - 1)];
 }
 
-struct NoPost {
-    __device__ void operator()(int) const {}
-};
-
-template <int B, bool kPipe, class Visit, class Post = NoPost>
+template <int B, bool kPipe>
 __device__ inline void walk(const FArgs &a, const FGrp *grp, const float *swc, const FInst *inst,
-                            int64_t p, int s0, int s1, Walk &w, bool *fresh, const Visit &visit,
-                            const Post &post = Post{})
+                            int64_t p, int s0, int s1, Walk &w, bool *fresh)
 {
     static_assert(B <= 32 && (B & (B - 1)) == 0, "a batch lies in one eviction word");
     if (s0 >= s1) return;
@@ -436,35 +482,20 @@ __device__ inline void walk(const FArgs &a, const FGrp *grp, const float *swc, c
             if (s < s0) continue;
             if (s >= s1) break;
             if (s >= w.nh) {
-                if (w.q + 1 < a.I && w.nx[0] >= 0 && (w.q + 2 >= a.I || w.nx[0] > s)) {
-                    // the next queue (qoff[q+1] <= s < qoff[q+2]), from the
-                    // boundaries held (a negative one is taken as not held)
-                    w.nh = w.nx[0];
-#pragma unroll
-                    for (int j = 0; j + 1 < kAhead; ++j) w.nx[j] = w.nx[j + 1];
-                    w.nx[kAhead - 1] = -1;
-                    set_queue(inst, w.q + 1, w);
-                } else {
-                    int q = w.q;
-                    while (q + 1 < a.I && a.qoff[(int64_t)(q + 1) * a.ld + p] <= s) ++q;
-                    open_queue(a, inst, p, q, w);
-                }
+                next_queue(a, inst, p, s, w);
                 *fresh = true;
             }
             const int i = cur.ids[u];
             if (i < 0 || i >= a.G) continue;
-            const int m = (int)gr[u].model;
+            const int m = grp_model(gr[u]);
             if (w.prev >= 0 && w.prev != m && a.swap_cost)
                 w.K += (double)swc[((int64_t)w.cls * a.M + w.prev) * a.M + m];
             if ((cur.ev >> (s & 31)) & 1u) w.K += (double)a.evict_cost;
-            visit(s, i, w);
-            const double n = (double)gr[u].cnt;
+            const double n = (double)grp_count(gr[u]);
             w.A += n * (double)gr[u].mu;
             w.V += n * (double)gr[u].var;
             w.prev = m;
         }
-        // the next batch's gathers go out before post: waiting for them then
-        // waits for none of post's stores
         if (more) {
             if (kPipe)
                 cur = nxt;
@@ -472,7 +503,6 @@ __device__ inline void walk(const FArgs &a, const FGrp *grp, const float *swc, c
                 batch_ids<B>(a, p, sb + B, s1, cur);
             batch_groups<B>(a, grp, cur, gr);
         }
-        post(sb);                       // every lane, after each batch
     }
 }
 
@@ -496,11 +526,20 @@ __device__ inline void stage_tables(const FArgs &a, unsigned char *t, int nthrea
     *inst = si;
 }
 
-struct NoVisit {
-    __device__ void operator()(int, int, const Walk &) const {}
-};
+// The group records, the swap costs and the instance table in LDS at t; every
+// thread of a workgroup takes part.
+__device__ inline void stage_groups(const FArgs &a, unsigned char *t, const FGrp **grp,
+                                    const float **swc, const FInst **inst)
+{
+    FGrp *sg = reinterpret_cast<FGrp *>(t);
+    const int nthreads = (int)blockDim.x;
+    for (int i = threadIdx.x; i < a.G; i += nthreads) sg[i] = a.grp[i];
+    stage_tables(a, t + sizeof(FGrp) * (size_t)a.G, nthreads, swc, inst);
+    __syncthreads();
+    *grp = sg;
+}
 
-// Grid: ceil(chunk/64) tiles x ceil(nseg/16); wavefront = (tile, segment).
+// Grid: ceil(chunk/64) tiles x ceil(nseg/wavefronts); wavefront = (tile, segment).
 // Pass 1: each segment's trailing piece (the sums of its last queue over the
 // segment's slots).  With kLds the group records, the swap costs and the
 // instance table are first copied into LDS (dynamic: 16 G bytes, the costs,
@@ -513,32 +552,27 @@ __global__ __launch_bounds__(kSegThreads) void k_fseg(FArgs a, int64_t p0, int64
     const FGrp *grp = a.grp;
     const float *swc = a.swap_cost;
     const FInst *inst = a.inst;
-    if (kLds) {
-        FGrp *sg = reinterpret_cast<FGrp *>(fseg_lds);
-        for (int i = threadIdx.x; i < a.G; i += kSegThreads) sg[i] = a.grp[i];
-        stage_tables(a, fseg_lds + sizeof(FGrp) * (size_t)a.G, kSegThreads, &swc, &inst);
-        __syncthreads();
-        grp = sg;
-    }
-    const int nseg = (a.G + kSeg - 1) / kSeg;
-    const int sq = (nseg + kSegWaves - 1) / kSegWaves;
+    if (kLds) stage_groups(a, fseg_lds, &grp, &swc, &inst);
+    const int nseg = a.nseg;
+    const int waves = (int)(blockDim.x / kWave);
+    const int sq = (nseg + waves - 1) / waves;
     const int64_t tile = blockIdx.x / sq;
-    const int k = (int)(blockIdx.x % sq) * kSegWaves + wave_id();
+    const int k = (int)(blockIdx.x % sq) * waves + wave_id();
     if (k >= nseg) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t col = tile * kWave + lane;
     const bool on = col < pc;
     const int64_t p = p0 + (on ? col : pc - 1);
-    const int s0 = k * kSeg, s1 = min(a.G, s0 + kSeg);
+    const int s0 = k * a.seg, s1 = min(a.G, s0 + a.seg);
     Walk w;
     const int q0 = queue_at(a, p, s0);
     open_queue(a, inst, p, q0, w);
     bool fresh = s0 == 0 || a.qoff[(int64_t)q0 * a.ld + p] >= s0;
     if (!fresh) {
         const int i = a.perm[(int64_t)(s0 - 1) * a.ld + p];
-        if (i >= 0 && i < a.G) w.prev = (int)grp[i].model;
+        if (i >= 0 && i < a.G) w.prev = grp_model(grp[i]);
     }
-    walk<8, true>(a, grp, swc, inst, p, s0, s1, w, &fresh, NoVisit{});
+    walk<8, true>(a, grp, swc, inst, p, s0, s1, w, &fresh);
     if (on) {
         Piece t;
         t.A = w.A;
@@ -551,60 +585,33 @@ __global__ __launch_bounds__(kSegThreads) void k_fseg(FArgs a, int64_t p0, int64
 }
 
 // Pass 2: one lane per plan, the segments in order: the sums at each
-// segment's first slot.
-__global__ __launch_bounds__(kThreads) void k_fstart(FArgs a, int64_t pc)
+// segment's first slot.  (Eight segments' pieces are read together; one at a
+// time, 64 segments took 26 us.)
+__global__ __launch_bounds__(kWave) void k_fstart(FArgs a, int64_t pc)
 {
-    const int64_t col = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t col = (int64_t)blockIdx.x * kWave + threadIdx.x;
     if (col >= pc) return;
-    const int nseg = (a.G + kSeg - 1) / kSeg;
+    const int nseg = a.nseg;
     double A = 0.0, V = 0.0, K = 0.0;
-    for (int k = 0; k < nseg; ++k) {
-        Start st;
-        st.A = A;
-        st.V = V;
-        st.K = K;
-        st.pad[0] = st.pad[1] = 0;
-        a.start[(int64_t)k * a.chunk + col] = st;
-        const Piece t = a.piece[(int64_t)k * a.chunk + col];
-        if (t.head) {
-            A = t.A;
-            V = t.V;
-            K = t.K;
-        } else {
-            A = A + t.A;
-            V = V + t.V;
-            K = K + t.K;
+    for (int k0 = 0; k0 < nseg; k0 += 8) {
+        Piece t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = a.piece[(int64_t)min(k0 + u, nseg - 1) * a.chunk + col];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (k0 + u >= nseg) break;
+            Start st;
+            st.A = A;
+            st.V = V;
+            st.K = K;
+            st.pad[0] = st.pad[1] = 0;
+            a.start[(int64_t)(k0 + u) * a.chunk + col] = st;
+            A = t[u].head ? t[u].A : A + t[u].A;
+            V = t[u].head ? t[u].V : V + t[u].V;
+            K = t[u].head ? t[u].K : K + t[u].K;
         }
     }
 }
-
-// Pass 3: each slot's record (its group's start E[W] = A/Theta + K, its
-// variance ahead, its queue), on its way to the group's row.  A queue open at
-// the segment's start continues from the sums of pass 2; where nothing varies
-// ahead (V = 0) those sums are formed again slot by slot from the queue's
-// first slot, so that E[W] is the oracle's bit for bit wherever an exact
-// comparison uses it.
-//
-// The records go to group rows, a different row in every lane, so they are
-// not stored directly (every store would be a partial line).  Every kSub
-// slots the wavefront sorts its records by group block (kBlk groups) in LDS
-// and appends each block's run to that block's bucket of the tile, in
-// consecutive addresses; k_fbscreen then places each bucket by group.  A
-// record carries its group within the block and its lane in the word of its
-// queue (the queue < 4096 in bits 0-11, the group in bits 12-18, the lane in
-// bits 19-24, kNoVar in bit 31).
-template <int kNB>
-struct WaveBuf {
-    // the records as four arrays of 32-bit words (c0's low and high words, v0,
-    // q): a gather of records in sorted order then spreads its lanes over the
-    // banks by entry, where 16-byte records would give it 16 bank groups
-    uint32_t rw[4][kSub * kWave];
-    uint32_t sidx[kSub * kWave];    // sorted position -> entry | group block << 16
-    uint16_t sgb[kSub * kWave];     // entry -> group block
-    uint8_t val[kSub * kWave];      // entry holds a record
-    int cnt[kNB];                   // per group block (nblk <= kNB)
-    uint16_t boff[kNB], gbase[kNB];
-};
 
 __device__ inline void wave_sync()
 {
@@ -613,101 +620,55 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The wavefront's buffered records into the buckets of tile `tile`.
-template <int kNB>
-__device__ inline void flush(const FArgs &a, WaveBuf<kNB> &wb, int64_t tile, int nblk)
+// This lane's place among the lanes of a ballot.
+__device__ inline int lane_rank(uint64_t mask)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    for (int k = lane; k < nblk; k += kWave) wb.cnt[k] = 0;
-    wave_sync();
-    int rank[kSub];
-#pragma unroll
-    for (int j = 0; j < kSub; ++j) {
-        const int e = j * kWave + lane;
-        rank[j] = wb.val[e] ? atomicAdd(&wb.cnt[wb.sgb[e]], 1) : 0;
-    }
-    wave_sync();
-    // offsets of the blocks' runs (a scan over the blocks), and their room in
-    // the buckets
-    int run = 0;
-    for (int k0 = 0; k0 < nblk; k0 += kWave) {
-        const int k = k0 + lane;
-        const int c = k < nblk ? wb.cnt[k] : 0;
-        int x = c;
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int y = __shfl_up(x, o, kWave);
-            if (lane >= o) x += y;
-        }
-        if (k < nblk) {
-            wb.boff[k] = (uint16_t)(run + x - c);
-            const int at = c > 0 ? atomicAdd(&a.bcnt[tile * nblk + k], c) : 0;
-            wb.gbase[k] = (uint16_t)min(at, kBlkCap);
-        }
-        run += __shfl(x, kWave - 1, kWave);
-    }
-    wave_sync();
-#pragma unroll
-    for (int j = 0; j < kSub; ++j) {
-        const int e = j * kWave + lane;
-        if (wb.val[e]) {
-            const uint32_t k = wb.sgb[e];
-            wb.sidx[wb.boff[k] + rank[j]] = (uint32_t)e | (k << 16);
-        }
-    }
-    wave_sync();
-    for (int pos = lane; pos < run; pos += kWave) {
-        const uint32_t se = wb.sidx[pos];
-        const int e = (int)(se & 0xFFFFu);
-        const int k = (int)(se >> 16);
-        const int dst = wb.gbase[k] + (pos - wb.boff[k]);
-        if (dst < kBlkCap) {
-            FRec r;
-            r.c0 = __hiloint2double((int)wb.rw[1][e], (int)wb.rw[0][e]);
-            r.v0 = __uint_as_float(wb.rw[2][e]);
-            r.q = wb.rw[3][e];
-            a.bucket[(tile * nblk + k) * (int64_t)kBlkCap + dst] = r;
-        }
-    }
-    wave_sync();
-#pragma unroll
-    for (int j = 0; j < kSub; ++j) wb.val[j * kWave + lane] = 0;
-    wave_sync();
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// kNB: group blocks the wavefront buffers hold (64 or kMaxBlocks); kTab: the
-// swap costs and the instance table copied into (dynamic) LDS.
-template <int kNB, bool kTab>
-__global__ __launch_bounds__(kRecWaves * kWave) void k_frec(FArgs a, int64_t p0, int64_t pc)
+// Requests whose SLOs lie in [smin, smax], whose mean waits lie in [lo, hi] and
+// whose scaled variances are at most vmax: whether every tail is exactly 0 or
+// every one exactly 1 (a NaN is never sure), and which.
+struct Side {
+    bool sure, one;
+};
+__device__ inline Side side_of(float smin, float smax, double lo, double hi, float vmax)
 {
-    __shared__ WaveBuf<kNB> bufs[kRecWaves];
-    extern __shared__ __align__(16) unsigned char frec_lds[];
+    const double early = (double)smin - hi, late = lo - (double)smax;   // (one at most is > 0)
+    Side r;
+    r.one = late > early;
+    r.sure = (float)(r.one ? late : early) * __builtin_amdgcn_rsqf(vmax) >= kSureCells;
+    return r;
+}
+
+// Pass 3: the walk of one segment of 64 plans, one wavefront.  A queue open at
+// the segment's start continues from the sums of pass 2; where nothing varies
+// ahead (V = 0) those sums are formed again slot by slot from the queue's
+// first slot, so that E[W] is the oracle's bit for bit wherever an exact
+// comparison uses it.  Groups whose side is sure add their requests to the
+// plan's count here; the others go to the (tile, segment)'s list, one after
+// another.  kLds as for k_fseg.
+template <bool kLds>
+__global__ __launch_bounds__(kSegThreads) void k_fwalk(FArgs a, int64_t p0, int64_t pc)
+{
+    extern __shared__ __align__(16) unsigned char fseg_lds[];
+    const FGrp *grp = a.grp;
     const float *swc = a.swap_cost;
     const FInst *inst = a.inst;
-    if (kTab) {
-        stage_tables(a, frec_lds, kRecWaves * kWave, &swc, &inst);
-        __syncthreads();
-    }
-    const int nseg = (a.G + kSeg - 1) / kSeg;
-    const int nblk = (a.G + kBlk - 1) / kBlk;
-    const int sq = (nseg + kRecWaves - 1) / kRecWaves;
-    // Workgroups are dealt to the XCDs in turn; all workgroups of a tile get
-    // the same XCD (xcd = blockIdx mod kXcds), so that the bucket lines their
-    // appends share fill up in that XCD's L2 before they are written back
-    // (from several L2s they went out in pieces).  The grid holds the tiles
-    // rounded up to a multiple of kXcds.
-    const int64_t local = blockIdx.x / kXcds;
-    const int64_t tile = (local / sq) * kXcds + blockIdx.x % kXcds;
-    const int k = (int)(local % sq) * kRecWaves + wave_id();
-    if (tile * kWave >= pc || k >= nseg) return;
-    WaveBuf<kNB> &wb = bufs[wave_id()];
+    if (kLds) stage_groups(a, fseg_lds, &grp, &swc, &inst);
+    const int nseg = a.nseg;
+    const int waves = (int)(blockDim.x / kWave);
+    const int sq = (nseg + waves - 1) / waves;
+    const int64_t tile = blockIdx.x / sq;
+    const int k = (int)(blockIdx.x % sq) * waves + wave_id();
+    if (k >= nseg) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t col = tile * kWave + lane;
     const bool on = col < pc;
     const int64_t c = on ? col : pc - 1;
     const int64_t p = p0 + c;
-    const int s0 = k * kSeg, s1 = min(a.G, s0 + kSeg);
-#pragma unroll
-    for (int j = 0; j < kSub; ++j) wb.val[j * kWave + lane] = 0;
+    const int s0 = k * a.seg, s1 = min(a.G, s0 + a.seg);
     Walk w;
     const int q0 = a.piece[(int64_t)k * a.chunk + c].q0;
     open_queue(a, inst, p, q0, w);
@@ -717,211 +678,278 @@ __global__ __launch_bounds__(kRecWaves * kWave) void k_frec(FArgs a, int64_t p0,
         if (st.V == 0.0) {
             // nothing varies ahead: form the sums again in the oracle's order
             bool f = false;
-            walk<8, true>(a, a.grp, swc, inst, p, max(b, 0), s0, w, &f, NoVisit{});
+            walk<8, true>(a, grp, swc, inst, p, max(b, 0), s0, w, &f);
         } else {
             w.A = st.A;
             w.V = st.V;
             w.K = st.K;
             const int i = a.perm[(int64_t)(s0 - 1) * a.ld + p];
-            if (i >= 0 && i < a.G) w.prev = (int)a.grp[i].model;
+            if (i >= 0 && i < a.G) w.prev = grp_model(grp[i]);
         }
     }
-    wave_sync();
-    bool f = false;
-    // batches of kSub slots (s0 is a multiple of kSub); the next batch's reads
-    // are in flight while a batch's records are sorted into the buckets
-    walk<kSub, true>(a, a.grp, swc, inst, p, s0, s1, w, &f, [&](int s, int i, const Walk &x) {
-        if (on) {
-            const int e = (s & (kSub - 1)) * kWave + lane;
-            FRec r;
-            r.c0 = x.A / x.theta + x.K;
-            r.v0 = (float)(x.V * x.vscale);
-            r.q = (uint32_t)x.q | ((uint32_t)(i & (kBlk - 1)) << 12) |
-                  ((uint32_t)lane << 19) | (x.V == 0.0 ? kNoVar : 0u);
-            wb.rw[0][e] = (uint32_t)__double2loint(r.c0);
-            wb.rw[1][e] = (uint32_t)__double2hiint(r.c0);
-            wb.rw[2][e] = __float_as_uint(r.v0);
-            wb.rw[3][e] = r.q;
-            wb.sgb[e] = (uint16_t)(i / kBlk);
-            wb.val[e] = 1;
-        }
-    }, [&](int) {
-        wave_sync();
-        flush(a, wb, tile, nblk);
-    });
-}
-
-__global__ __launch_bounds__(kThreads) void k_fbzero(FArgs a, int64_t n)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * kThreads)
-        a.bcnt[k] = 0;
-}
-
-// Q of the margin m (seconds) at scaled variance vz, from the table in LDS.
-__device__ inline float tail_q(const float2 *tab, float m, float vz)
-{
-    return qlm_tail::q_of(tab, m, vz);
-}
-
-// The screened sum of P over the requests of group i in one plan (lane = plan;
-// every lane of a wavefront at the same request of the same group, whose SLO
-// is read through the scalar cache), from the group's start record rc.
-__device__ inline double group_screen(const FArgs &a, const float2 *tab, int i, const FRec &rc)
-{
-    const auto req = as_const(a.req);
-    const auto first = as_const(a.first);
-    const int n = (int)req[i].n;
-    if (n == 0) return 0.0;
-    const float mu = req[i].mu, var = req[i].var;
-    const auto slo = as_const(a.slo64 + first[i]);
-    const int g = min((int)(rc.q & ~kNoVar), a.I - 1);
-    const bool novar = (rc.q & kNoVar) != 0u;
-    const double theta = (double)a.inst_tput[g];
-    const double c1 = (double)mu / theta;
-    const float v1 = (float)((double)var * (qlm_tail::kVarScale / (theta * theta)));
-    const double c0 = rc.c0;
-    const float v0 = rc.v0;
-    const double s0 = slo[0];
-    double Sg = novar ? (c0 > s0 ? 1.0 : 0.0) : (double)tail_q(tab, (float)(s0 - c0), v0);
-    if (var == 0.0f) {
-        for (int r = 1; r < n; ++r) {
-            const double Er = c0 + (double)r * c1;
-            const double sr = slo[r];
-            Sg += novar ? (Er > sr ? 1.0 : 0.0) : (double)tail_q(tab, (float)(sr - Er), v0);
-        }
-    } else {
-        int r = 1;
-        for (; r + 32 <= n; r += 32) {
-            const double eb = c0 + (double)r * c1;
-            const float vb = fmaf((float)r, v1, v0);
-            float S = 0.0f;
+    int sure = 0;                              // requests whose tail is exactly 1 (below 2^29)
+    int ng = 0;                                // entries of the list
+    FEntry *list = a.list + (tile * nseg + k) * (int64_t)(a.seg * kWave);
+    uint16_t *listq = a.listq + (tile * nseg + k) * (int64_t)(a.seg * kWave);
+    Batch<kSub> cur, nxt;
+    FGrp gr[kSub];
+    batch_ids<kSub>(a, p, s0, s1, cur);
+    batch_groups<kSub>(a, grp, cur, gr);
+    // batches of kSub slots (s0 is a multiple of kSub), the next batch's group
+    // ids in flight while one is walked
+    for (int sb = s0; sb < s1; sb += kSub) {
+        const bool more = sb + kSub < s1;
+        if (more) batch_ids<kSub>(a, p, sb + kSub, s1, nxt);
 #pragma unroll
-            for (int k = 0; k < 32; ++k) {
-                const float m = (float)fma(-(double)k, c1, slo[r + k] - eb);
-                const float v = fmaf((float)k, v1, vb);
-                S += tail_q(tab, m, v);
+        for (int u = 0; u < kSub; ++u) {
+            const int s = sb + u;
+            if (s >= s1) break;
+            if (s >= w.nh) next_queue(a, inst, p, s, w);
+            const int i = cur.ids[u];
+            bool put = false;
+            FEntry e{0.0, 0.0f, 0u};
+            if (i >= 0 && i < a.G) {
+                const int m = grp_model(gr[u]);
+                if (w.prev >= 0 && w.prev != m && a.swap_cost)
+                    w.K += (double)swc[((int64_t)w.cls * a.M + w.prev) * a.M + m];
+                if ((cur.ev >> (s & 31)) & 1u) w.K += (double)a.evict_cost;
+                const double n = (double)grp_count(gr[u]);
+                const double mu = (double)gr[u].mu, var = (double)gr[u].var;
+                e.c0 = quotient(w.A, w.theta, w.inv) + w.K;
+                e.v0 = (float)(w.V * w.vscale);
+                e.id = (uint32_t)i | ((uint32_t)lane << 16);
+                // (up to where the group after it starts, to within rounding, and
+                // the variance ahead there; a group with mu < 0 has no sure side)
+                const double tok = n * mu, tvar = n * var;
+                w.A += tok;
+                w.V += tvar;
+                const Side d = side_of(grp_smin(gr[u]), grp_smax(gr[u]), e.c0,
+                                       fma(tok, w.inv, e.c0), (float)(w.V * w.vscale));
+                put = on && !d.sure && n > 0.0;
+                sure += d.sure && d.one ? (int)grp_count(gr[u]) : 0;
+                w.prev = m;
             }
-            Sg += (double)S;
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(put);
+            if (put) {
+                const int at = ng + lane_rank(mask);
+                list[at] = e;
+                listq[at] = (uint16_t)w.q;
+            }
+            ng += __builtin_popcountll(mask);
         }
-        float S = 0.0f;
-        for (; r < n; ++r) {
-            const double e = c0 + (double)r * c1;
-            const float m = (float)(slo[r] - e);
-            const float v = fmaf((float)r, v1, v0);
-            S += tail_q(tab, m, v);
+        if (more) {
+            cur = nxt;
+            batch_groups<kSub>(a, grp, cur, gr);
         }
-        Sg += (double)S;
     }
-    return Sg;
+    if (lane == 0) a.listn[tile * nseg + k] = ng;
+    if (on) a.part[(int64_t)k * a.chunk + col] = (double)sure;
 }
 
-// The second pass of the transposition and the screen in one: one workgroup
-// per bucket (tile, block of kBlk groups), group block major (the workgroups
-// running at one time share their groups' SLOs in the caches).  The bucket's
-// records go into LDS at their (group, plan) place; the 16 wavefronts then
-// take the block's groups one at a time from a counter in LDS and screen each
-// from LDS, leaving the group's sum for every plan in the place of its record;
-// these are added in a fixed order (blocks of consecutive groups, then the
-// blocks), the block's partial score of each plan.  The records sit in LDS as four arrays of 32-bit words (the low and
-// high words of c0, v0, q), so that a scattered store's lanes land in banks by
-// their plan's lane alone: a 16-byte record per place would give the 64 lanes
-// of a store only 16 bank groups.  (Writing the records out as group rows for
-// a separate screen moved 2 GiB more per chunk at large.)
-constexpr int kTransThreads = 1024;
+// A wavefront's list of blocks to be evaluated, eight words an entry: the start
+// E[W] of the group's first request and the step from one request to the next
+// (double each), the variance ahead of the block and its step (single), where its
+// SLOs start,
+// and requests | lane of the plan << 6 | nothing varies << 12 | the block's
+// number << 13.  Each word has an array of its own: 64 lanes storing consecutive
+// entries then meet every bank, and reading them too.
+struct BlockList {
+    uint32_t w[8][kBlockList];
+};
 
-__global__ __launch_bounds__(kTransThreads) void k_fbscreen(FArgs a, int64_t pc)
+// The sum of P over a block's requests: the group's start c0 and step c1, the
+// block's first request r0 of the group, the variance ahead v0 and its step v1,
+// the block's SLOs at src.  kAll: 32 requests in every lane, none of them flat;
+// else cnt requests (0 adds nothing), and where nothing varies (flat) comparisons
+// with E[W_r] as the oracle forms it.  kLast: reads no SLO past the block's last.
+template <bool kAll, bool kLast>
+__device__ __attribute__((always_inline)) inline float block_sum(const float2 *tab, const float *src, double c0, double c1, int r0,
+                                  float v0, float v1, int cnt, bool flat)
 {
-    extern __shared__ __align__(16) unsigned char dyn[];
-    uint32_t *w0 = reinterpret_cast<uint32_t *>(dyn);      // [kBlkCap] each
-    uint32_t *w1 = w0 + kBlkCap;
-    uint32_t *w2 = w1 + kBlkCap;
-    uint32_t *w3 = w2 + kBlkCap;
-    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
-    __shared__ int next;
-    qlm_tail::stage(tab, (int)threadIdx.x, kTransThreads);
-    if (threadIdx.x == 0) next = 0;
-    const int nblk = (a.G + kBlk - 1) / kBlk;
-    const int64_t tiles = (pc + kWave - 1) / kWave;
-    const int gb = (int)(blockIdx.x / tiles);
-    const int64_t tile = blockIdx.x % tiles;
-    const int i0 = gb * kBlk;
-    const int ng = min(kBlk, a.G - i0);
-    const int n = min(a.bcnt[tile * nblk + gb], kBlkCap);
-    const FRec *src = a.bucket + (tile * nblk + gb) * (int64_t)kBlkCap;
-    constexpr int kU = kBlkCap / kTransThreads;       // 8 records a thread, read together
-    FRec x[kU];
+    const double eb = c0 + (double)r0 * c1;
+    float S = 0.0f;
+    // (half a block at a time: the SLOs of a whole one, with what the unrolled
+    // tails keep in flight, spill registers at four wavefronts a SIMD)
+#pragma unroll 1
+    for (int h = 0; h < kReqBlk; h += kHalf) {
+        float slo[kHalf];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const int r = u * kTransThreads + (int)threadIdx.x;
-        if (r < n) x[u] = ld_rec_nt(src + r);
-    }
+        for (int k = 0; k < kHalf; ++k) slo[k] = src[kLast ? min(h + k, max(cnt - 1, 0)) : h + k];
+        const double c0h = (double)h;
+        const float v0h = (float)h;
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const int r = u * kTransThreads + (int)threadIdx.x;
-        if (r < n) {
-            const int gi = (int)((x[u].q >> 12) & (kBlk - 1));
-            const int ln = (int)((x[u].q >> 19) & (kWave - 1));
-            const int at = gi * kWave + ln;
-            w0[at] = (uint32_t)__double2loint(x[u].c0);
-            w1[at] = (uint32_t)__double2hiint(x[u].c0);
-            w2[at] = __float_as_uint(x[u].v0);
-            w3[at] = x[u].q & (0xFFFu | kNoVar);
+        for (int k = 0; k < kHalf; ++k) {
+            const float m = (float)fma(-(c0h + (double)k), c1, (double)slo[k] - eb);
+            const float q = qlm_tail::q_of(tab, m, fmaf(v0h + (float)k, v1, v0));
+            if (kAll) {
+                S += q;
+            } else {
+                const float late = c0 + (double)(r0 + h + k) * c1 > (double)slo[k] ? 1.0f : 0.0f;
+                S += h + k < cnt ? (flat ? late : q) : 0.0f;
+            }
         }
     }
-    __syncthreads();
+    return S;
+}
+
+// The list's entries [from, from + n), n <= 64, one per lane, evaluated and added
+// to their plans' sums.
+__device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a, const float2 *tab, const BlockList &bl,
+                                   unsigned long long *sum, int from, int n)
+{
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t col0 = tile * kWave + lane;
-    const bool on = col0 < pc;
-    // a lane past the chunk takes the record of the tile's last plan
-    const int ln = on ? lane : (int)(pc - 1 - tile * kWave);
+    const bool on = lane < n;
+    const int e = from + (on ? lane : 0);
+    const double c0 = __hiloint2double((int)bl.w[1][e], (int)bl.w[0][e]);
+    const double c1 = __hiloint2double((int)bl.w[3][e], (int)bl.w[2][e]);
+    const float v0 = __uint_as_float(bl.w[4][e]), v1 = __uint_as_float(bl.w[5][e]);
+    const uint32_t at = bl.w[6][e], what = bl.w[7][e];
+    const float *src = a.req_slo + at;
+    const int cnt = on ? (int)(what & 63u) : 0;
+    const int r0 = (int)(what >> 13) * kReqBlk;
+    const bool flat = (what >> 12) & 1u;
+    float S;
+    // (a whole block's reads stay inside req_slo except near its end)
+    if (__builtin_amdgcn_ballot_w64((int64_t)at + kReqBlk > a.n_req) != 0)
+        S = block_sum<false, true>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
+    else if (__builtin_amdgcn_ballot_w64(cnt < kReqBlk || flat) != 0)
+        S = block_sum<false, false>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
+    else
+        S = block_sum<true, false>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
+    if (on)
+        atomicAdd(&sum[(what >> 6) & 63u], (unsigned long long)(long long)((double)S * 0x1p32));
+}
+
+// Pass 4: the listed groups of one (tile, segment), one workgroup: its wavefronts
+// take 64 of them at a time, one per lane, look at their blocks of 32 requests
+// and evaluate the blocks that are not sure, 64 at a time.
+//
+// What the walk, the lists and this replaced: the records of every (group, plan)
+// sorted by group in two passes through LDS and memory, so that a wavefront
+// could take one group of 64 plans and evaluate all of its requests with the SLOs
+// in scalar registers (0.31 + 1.45 ms for 4096 plans of 8192 groups of 128
+// requests).  Here an evaluated request costs more (its SLO comes from L2, a
+// block per lane: with every request evaluated, where spreads are as wide as the
+// waits, the whole call takes 3.4 ms and took 2.0) and few are evaluated: 0.11 +
+// 0.28 ms on random plans.  With the lists in LDS and both passes in one kernel
+// its registers left two wavefronts a SIMD: 1.40 ms.
+__global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_ftails(
+    FArgs a, int64_t pc)
+{
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
+    __shared__ BlockList lists[kTailWaves];
+    __shared__ unsigned long long sum[kWave];  // per plan, times 2^32
+    const int nseg = a.nseg;
+    const int64_t tile = blockIdx.x / nseg;
+    const int k = (int)(blockIdx.x % nseg);
+    const int total = min(a.listn[blockIdx.x], a.seg * kWave);
+    if (total == 0) return;                    // (the same in the whole workgroup)
+    qlm_tail::stage(tab, (int)threadIdx.x, kTailWaves * kWave);
+    if (threadIdx.x < kWave) sum[threadIdx.x] = 0ull;
+    __syncthreads();
+    BlockList &bl = lists[wave_id()];
+    const int lane = threadIdx.x & (kWave - 1);
+    const FEntry *list = a.list + (int64_t)blockIdx.x * (a.seg * kWave);
+    const uint16_t *listq = a.listq + (int64_t)blockIdx.x * (a.seg * kWave);
+    int nb = 0;                                // entries of the list of blocks
+    int g0 = (wave_id() - kTailWaves) * kWave; // the groups in hand
+    bool have = false;                         // they have blocks left
+    int n = 0, bb = 0;                         // this lane's requests; the block in hand
+    FEntry e{0.0, 0.0f, 0u};
+    uint32_t q = 0u, first = 0u;
+    const float2 *blk = a.blk;
+    double c1 = 0.0;
+    float v1 = 0.0f;
+    bool flat = false;
+    unsigned long long ones = 0ull;
     for (;;) {
-        int gi = 0;
-        if (lane == 0) gi = atomicAdd(&next, 1);
-        gi = __builtin_amdgcn_readfirstlane(__shfl(gi, 0, kWave));
-        if (gi >= ng) break;
-        const int at = gi * kWave + ln;
-        FRec rc;
-        rc.c0 = __hiloint2double((int)w1[at], (int)w0[at]);
-        rc.v0 = __uint_as_float(w2[at]);
-        rc.q = w3[at];
-        const double Sg = group_screen(a, tab, i0 + gi, rc);
-        // (every lane has read its record: the wavefront moves in step)
-        const int me = gi * kWave + lane;
-        w0[me] = (uint32_t)__double2loint(Sg);
-        w1[me] = (uint32_t)__double2hiint(Sg);
+        while (nb < kWave) {
+            if (!have) {
+                g0 += kTailWaves * kWave;
+                if (g0 >= total) break;
+                const bool mine = g0 + lane < total;
+                e = list[mine ? g0 + lane : g0];
+                q = listq[mine ? g0 + lane : g0];
+                const int i = (int)(e.id & 0xFFFFu);
+                const FReq r = a.req[i];
+                const FInst in = a.inst[q];
+                const float mu = a.grp[i].mu, var = a.grp[i].var;
+                first = r.first;
+                c1 = (double)mu / in.theta;
+                v1 = (float)((double)var * in.vscale);
+                flat = var == 0.0f && e.v0 == 0.0f;
+                n = mine ? (int)r.n : 0;
+                blk = a.blk + block_of(first, i, 0);
+                ones = 0ull;
+                bb = 0;
+                have = true;
+            }
+            const int rb = bb * kReqBlk;
+            const float vb = fmaf((float)rb, v1, e.v0);
+            bool put = false;
+            if (rb < n) {
+                const int cb = min(kReqBlk, n - rb);
+                const float2 mm = blk[bb];
+                const double ea = e.c0 + (double)rb * c1, ez = e.c0 + (double)(rb + cb - 1) * c1;
+                const Side d = side_of(mm.x, mm.y, fmin(ea, ez), fmax(ea, ez),
+                                       fmaf((float)cb, v1, vb));
+                put = !d.sure;
+                ones += d.sure && d.one ? (unsigned long long)cb : 0ull;
+            }
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(put);
+            if (put) {
+                const int to = nb + lane_rank(mask);
+                bl.w[0][to] = (uint32_t)__double2loint(e.c0);
+                bl.w[1][to] = (uint32_t)__double2hiint(e.c0);
+                bl.w[2][to] = (uint32_t)__double2loint(c1);
+                bl.w[3][to] = (uint32_t)__double2hiint(c1);
+                bl.w[4][to] = __float_as_uint(vb);
+                bl.w[5][to] = __float_as_uint(v1);
+                bl.w[6][to] = first + (uint32_t)rb;
+                bl.w[7][to] = (uint32_t)min(kReqBlk, n - rb) | ((e.id >> 16) << 6) |
+                              (flat ? 1u << 12 : 0u) | ((uint32_t)bb << 13);
+            }
+            nb += __builtin_popcountll(mask);
+            ++bb;
+            if (__builtin_amdgcn_ballot_w64(bb * kReqBlk < n) == 0) {
+                if (ones) atomicAdd(&sum[e.id >> 16], ones << 32);
+                have = false;
+            }
+        }
+        if (nb == 0) break;
+        const int m = min(nb, kWave);
+        nb -= m;
+        wave_sync();
+        eval_blocks(a, tab, bl, sum, nb, m);
+        wave_sync();
     }
     __syncthreads();
-    // the sums in a fixed order: each wavefront adds kBlk / 16 consecutive
-    // groups, then one wavefront adds the 16 partials (in the record words
-    // v0, q, free now)
-    constexpr int kPer = kBlk / (kTransThreads / kWave);
-    const int wv = wave_id();
-    double part = 0.0;
-    for (int gi = wv * kPer; gi < min(ng, wv * kPer + kPer); ++gi)
-        part += __hiloint2double((int)w1[gi * kWave + lane], (int)w0[gi * kWave + lane]);
-    w2[wv * kWave + lane] = (uint32_t)__double2loint(part);
-    w3[wv * kWave + lane] = (uint32_t)__double2hiint(part);
-    __syncthreads();
-    if (threadIdx.x < kWave) {
-        double tot = 0.0;
-        for (int k = 0; k < kTransThreads / kWave; ++k)
-            tot += __hiloint2double((int)w3[k * kWave + lane], (int)w2[k * kWave + lane]);
-        if (on) a.part[(int64_t)gb * a.chunk + col0] = tot;
+    const int64_t col = tile * kWave + threadIdx.x;
+    if (threadIdx.x < kWave && col < pc) {
+        double *part = a.part + (int64_t)k * a.chunk + col;
+        *part += (double)(long long)sum[threadIdx.x] * 0x1p-32;
     }
 }
 
-// Screened plan scores of the chunk (partials in group-block order) and the
+// Screened plan scores of the chunk (the segments' sums in order) and the
 // running minimum per block (grid-stride over plans, fixed grid).
 __global__ __launch_bounds__(kThreads) void k_fsum(FArgs a, int64_t p0, int64_t pc, int first_chunk)
 {
     __shared__ double lmin[kWaves];
-    const int nb = (a.G + kBlk - 1) / kBlk;
+    const int nb = a.nseg;
     double mn = first_chunk ? INFINITY : a.bmin[blockIdx.x];
     for (int64_t c = (int64_t)blockIdx.x * kThreads + threadIdx.x; c < pc;
          c += (int64_t)gridDim.x * kThreads) {
         double s = 0.0;
-        for (int b = 0; b < nb; ++b) s += a.part[(int64_t)b * a.chunk + c];
+        // (eight reads in flight: one after another they took 21 us for 64 segments)
+        for (int b0 = 0; b0 < nb; b0 += 8) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = b0 + u < nb ? a.part[(int64_t)(b0 + u) * a.chunk + c] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
         a.F[p0 + c] = s;
         mn = fmin(mn, s);
     }
@@ -936,7 +964,7 @@ __global__ __launch_bounds__(kThreads) void k_fsum(FArgs a, int64_t p0, int64_t 
 
 // Candidates: plans whose screened score lies within twice the bound of the
 // lowest (their exact score can be the lowest), and plans with a NaN score.
-// Block 0 clears the counter first in a kernel of its own (k_fzero).
+// (k_fprep clears the counter; k_fzero does when there is no plan.)
 __global__ void k_fzero(FArgs a) { if (threadIdx.x == 0) a.ncand[0] = 0; }
 
 __global__ __launch_bounds__(kThreads) void k_fselect(FArgs a, int nbmin)
@@ -972,7 +1000,7 @@ __device__ inline double slot_exact(const FArgs &a, int i, double A, double V, d
     const int n = (int)a.req[i].n;
     const double mu = (double)a.grp[i].mu;
     const double var = (double)a.grp[i].var;
-    const float *slo = a.req_slo + a.first[i];
+    const float *slo = a.req_slo + a.req[i].first;
     const double EW = A / theta + K;
     double slot = 0.0;
     const int r0 = (int)((int64_t)n * j / nsl), r1 = (int)((int64_t)n * (j + 1) / nsl);
@@ -990,29 +1018,54 @@ __device__ inline double slot_exact(const FArgs &a, int i, double A, double V, d
     return slot;
 }
 
-// One workgroup per (candidate k, queue g), over a fixed grid; each of its 16
-// wavefronts takes one slice of every group's requests (consecutive
-// arrivals).  A wavefront walks the queue's positions 64 at a time, one per
+// Workgroups over a fixed grid take (candidate k, queue g) tasks; every group's
+// requests are cut into 64 slices (consecutive arrivals), four for each of a
+// workgroup's 16 wavefronts (slices w, w + 16, ...).  A wavefront walks the queue's positions 64 at a time, one per
 // lane; the running sums ripple from lane to lane in position order, then each
-// lane forms its slice of its group's requests' terms, and those sums ripple
-// into the slice's queue sum the same way.  The queue score is the slices'
-// sums added in slice order (the oracle's sum reassociated: equal to within
-// the rounding of a sum of that many terms).  Sixteen wavefronts per queue
-// instead of one keep the requests' erfc chains short and the chip busy when
-// only a few plans are re-scored.
+// lane forms its slices of its group's requests' terms, and those sums ripple
+// into the slices' queue sums the same way.  The queue score is the slices'
+// sums added in slice order, sixteen at a time, then the four sums (the oracle's
+// sum reassociated: equal to within the rounding of a sum of that many terms).
+// When few tasks are there (one candidate of 64 queues is the usual case) two or
+// four workgroups share a task, each with half or a quarter of every wavefront's
+// slices, and the sums of sixteen go to `parts` (task_score adds them); the
+// additions are the same.  One candidate of 64 queues and 1,048,576 requests: 58
+// us on 64 workgroups, 36 on 256.
 constexpr int kExactThreads = 1024;
-constexpr int kExactSlices = kExactThreads / kWave;
+constexpr int kExactWaves = kExactThreads / kWave;
+constexpr int kExactSubs = 4;                      // slices per wavefront
+constexpr int kExactSlices = kExactWaves * kExactSubs;
+
+// Workgroups that share a task.
+__device__ inline int task_split(int64_t tasks)
+{
+    return tasks * 4 <= kExactBlocks ? 4 : (tasks * 2 <= kExactBlocks ? 2 : 1);
+}
+
+// The exact score of queue g of candidate k of n, after k_fexact.
+__device__ inline double task_score(const FArgs &a, int64_t n, int64_t k, int g)
+{
+    const int64_t t = k * a.I + g;
+    if (task_split(n * a.I) == 1) return a.Q[t];
+    double q = 0.0;
+    for (int s = 0; s < kExactSubs; ++s) q += a.parts[t * kExactSubs + s];
+    return q;
+}
 
 __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t *plan_index,
                                                            const int32_t *count_dev, int64_t count)
 {
-    __shared__ double part[kExactSlices];
+    __shared__ double part[kExactSubs][kExactWaves];
     const int lane = threadIdx.x & (kWave - 1);
     const int js = wave_id();
     const int64_t n = count_dev ? (int64_t)__builtin_amdgcn_readfirstlane(count_dev[0]) : count;
     const int64_t tasks = n * a.I;
+    const int split = task_split(tasks);
+    const int subs = kExactSubs / split;            // of this workgroup, from sub0 on
     const double ecost = (double)a.evict_cost;
-    for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {
+    for (int64_t ts = blockIdx.x; ts < tasks * split; ts += gridDim.x) {
+        const int64_t t = ts / split;
+        const int sub0 = (int)(ts % split) * subs;
         const int64_t k = t / a.I;
         const int g = (int)(t % a.I);
         int64_t p = plan_index[k];
@@ -1023,7 +1076,7 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
         const double theta = (double)a.inst_tput[g];
         const int cls = clampi(a.inst_class[g], 0, a.C - 1);
         int prev = a.inst_model0 ? clampi(a.inst_model0[g], -1, a.M - 1) : -1;
-        double rA = 0.0, rV = 0.0, rK = 0.0, rC = 0.0;
+        double rA = 0.0, rV = 0.0, rK = 0.0, rC[kExactSubs] = {0.0, 0.0, 0.0, 0.0};
         for (int v0 = bq; v0 < eq; v0 += kWave) {
             const int cnt = min(kWave, eq - v0);
             const bool on = lane < cnt;
@@ -1032,14 +1085,14 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
                 i = a.perm[(int64_t)(v0 + lane) * a.ld + p];
                 if (i < 0 || i >= G) i = -1;
             }
-            const int m = i >= 0 ? (int)a.grp[i].model : -1;
+            const int m = i >= 0 ? grp_model(a.grp[i]) : -1;
             // an invalid id (malformed plan) keeps the model before it
             int pm = __shfl_up(m, 1, kWave);
             if (lane == 0) pm = prev;
             const int mm = m >= 0 ? m : pm;
             double xa = 0.0, xb = 0.0, c1 = 0.0, c2 = 0.0;
             if (i >= 0) {
-                const double nn = (double)a.grp[i].cnt;
+                const double nn = (double)grp_count(a.grp[i]);
                 xa = nn * (double)a.grp[i].mu;
                 xb = nn * (double)a.grp[i].var;
                 if (pm >= 0 && pm != m && a.swap_cost)
@@ -1065,28 +1118,40 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
             }
             double K = K0 + c1;
             K = K + c2;
-            const double term = i >= 0 ? slot_exact(a, i, A, V, K, theta, js, kExactSlices) : 0.0;
-            const double lt = from_left0(term);
-            double C = rC;
-            for (int j = 0; j < steps; j += 8) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) C = from_left(C) + lt;
-            }
             const int last = cnt - 1;
+#pragma unroll
+            for (int s = 0; s < kExactSubs; ++s) {
+                if (s >= subs) break;
+                const double term = i >= 0 ? slot_exact(a, i, A, V, K, theta,
+                                                        (sub0 + s) * kExactWaves + js, kExactSlices)
+                                           : 0.0;
+                const double lt = from_left0(term);
+                double C = rC[s];
+                for (int j = 0; j < steps; j += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) C = from_left(C) + lt;
+                }
+                rC[s] = lane_value(C, last) + lane_value(term, last);
+            }
             rA = lane_value(A, last) + lane_value(xa, last);
             rV = lane_value(V, last) + lane_value(xb, last);
             rK = lane_value(K, last);
-            rC = lane_value(C, last) + lane_value(term, last);
             // the model the next round starts from: the last valid one
             int carry = __builtin_amdgcn_readlane(mm, last);
             prev = carry;
         }
-        if (lane == 0) part[js] = rC;
+        if (lane == 0)
+            for (int s = 0; s < kExactSubs; ++s) part[s][js] = rC[s];
         __syncthreads();
         if (threadIdx.x == 0) {
             double q = 0.0;
-            for (int j = 0; j < kExactSlices; ++j) q += part[j];
-            a.Q[k * a.I + g] = q;
+            for (int s = 0; s < subs; ++s) {
+                double x = 0.0;
+                for (int j = 0; j < kExactWaves; ++j) x += part[s][j];
+                if (split > 1) a.parts[t * kExactSubs + sub0 + s] = x;
+                q += x;
+            }
+            if (split == 1) a.Q[t] = q;
         }
         __syncthreads();
     }
@@ -1098,7 +1163,7 @@ __global__ __launch_bounds__(kThreads) void k_fplan(FArgs a, int64_t n, double *
     for (int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * kThreads) {
         double s = 0.0;
-        for (int g = 0; g < a.I; ++g) s += a.Q[k * a.I + g];
+        for (int g = 0; g < a.I; ++g) s += task_score(a, n, k, g);
         score[k] = s;
     }
 }
@@ -1112,11 +1177,18 @@ __global__ __launch_bounds__(kPickThreads) void k_fpick(FArgs a, int64_t *best_i
     const int n = a.ncand[0];
     double bs = INFINITY;
     int64_t bi = -1;
-    for (int k = threadIdx.x; k < n; k += kPickThreads) {
+    // one wavefront per candidate: the lanes load its queue scores, which are
+    // added in queue order
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int k = wave_id(); k < n; k += kPickThreads / kWave) {
         double s = 0.0;
-        for (int g = 0; g < a.I; ++g) s += a.Q[(int64_t)k * a.I + g];
+        for (int g0 = 0; g0 < a.I; g0 += kWave) {
+            const double q = g0 + lane < a.I ? task_score(a, n, k, g0 + lane) : 0.0;
+            const int c = min(kWave, a.I - g0);
+            for (int j = 0; j < c; ++j) s += lane_value(q, j);
+        }
         const int64_t p = a.cand[k];
-        if (s == s && (bi < 0 || better(s, p, bs, bi))) {   // a NaN score never wins
+        if (lane == 0 && s == s && (bi < 0 || better(s, p, bs, bi))) {   // a NaN score never wins
             bs = s;
             bi = p;
         }
@@ -1153,11 +1225,26 @@ __global__ __launch_bounds__(kPickThreads) void k_fpick(FArgs a, int64_t *best_i
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
-// Plans per chunk: as many as `want` asks for (0 = up to kRecBudget bytes of
-// group records), a multiple of 64, no more than the plans rounded up.
+// Slots per segment: 128, or 64 or 32 while that leaves fewer than 2048 wavefronts
+// (a wavefront walks a segment one slot after another).  6000 plans of 1000
+// groups, k_fseg and k_fwalk: 49 and 65 us with 128 slots in workgroups of 16
+// wavefronts (94 of them), 23 and 31 us with 32 in workgroups of 8.  All the
+// plans of a call count, not those of a chunk: chunks change no bit.
+int segment_of(int32_t G, int64_t P)
+{
+    const int64_t tiles = (P + kWave - 1) / kWave;
+    int seg = kSeg;
+    while (seg > kMinSeg && tiles * ((G + seg - 1) / seg) < 2048) seg /= 2;
+    return seg;
+}
+
+// Plans per chunk: as many as `want` asks for (0 = up to kChunkBudget bytes of
+// lists, which hold every group at most, and segment sums), a multiple of 64, no more than the plans rounded up.
 int64_t chunk_of(int32_t G, int64_t P, int64_t want)
 {
-    int64_t c = (int64_t)(kRecBudget / (sizeof(FRec) * (size_t)(G > 0 ? G : 1)));
+    const size_t nseg = (size_t)((G > 0 ? G : 1) + kSeg - 1) / kSeg;
+    int64_t c = (int64_t)(kChunkBudget / ((sizeof(Piece) + sizeof(Start) + 8 +
+                                         kSeg * (sizeof(FEntry) + sizeof(uint16_t))) * nseg));
     if (want > 0) c = want;
     c = (c + kWave - 1) / kWave * kWave;
     const int64_t all = (P + kWave - 1) / kWave * kWave;
@@ -1166,9 +1253,9 @@ int64_t chunk_of(int32_t G, int64_t P, int64_t want)
 }
 
 struct FLayout {
-    size_t grp, req, inst, first, slo64, nreq, bucket, bcnt, piece, start, part, F, bmin, ncand,
-        cand, Q, total;
+    size_t grp, req, inst, blk, nreq, list, listq, listn, piece, start, part, F, bmin, ncand, cand, Q, parts, total;
     int64_t chunk;
+    int seg;
 };
 
 FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
@@ -1177,7 +1264,6 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     const int32_t G = pr->n_groups, I = pr->n_instances;
     L.chunk = chunk_of(G, P, chunk);
     const int64_t Pn = P > 0 ? P : 1;
-    const int nb = (G + kBlk - 1) / kBlk;
     size_t o = 0;
     auto put = [&](size_t &field, size_t bytes) {
         field = o;
@@ -1186,22 +1272,23 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     put(L.grp, sizeof(FGrp) * (size_t)G);
     put(L.req, sizeof(FReq) * (size_t)G);
     put(L.inst, sizeof(FInst) * (size_t)I);
-    put(L.first, 4 * ((size_t)G + 1));
-    put(L.slo64, 8 * ((size_t)n_req + 1));
+    put(L.blk, sizeof(float2) * ((size_t)n_req / kReqBlk + (size_t)G + 1));
     put(L.nreq, 8);
+    L.seg = segment_of(G, P);
+    const size_t nseg = (size_t)((G + L.seg - 1) / L.seg);
     const size_t tiles = (size_t)(L.chunk / kWave);
-    const size_t nblk = (size_t)((G + kBlk - 1) / kBlk);
-    put(L.bucket, sizeof(FRec) * tiles * nblk * (size_t)kBlkCap);
-    put(L.bcnt, 4 * tiles * nblk);
-    const size_t nseg = (size_t)((G + kSeg - 1) / kSeg);
+    put(L.list, sizeof(FEntry) * tiles * nseg * (size_t)(L.seg * kWave));
+    put(L.listq, sizeof(uint16_t) * tiles * nseg * (size_t)(L.seg * kWave));
+    put(L.listn, 4 * tiles * nseg);
     put(L.piece, sizeof(Piece) * nseg * (size_t)L.chunk);
     put(L.start, sizeof(Start) * nseg * (size_t)L.chunk);
-    put(L.part, 8 * (size_t)nb * (size_t)L.chunk);
+    put(L.part, 8 * nseg * (size_t)L.chunk);
     put(L.F, 8 * (size_t)Pn);
     put(L.bmin, 8 * (size_t)kSumBlocks);
     put(L.ncand, 256);
     put(L.cand, 8 * (size_t)Pn);
     put(L.Q, 8 * (size_t)Pn * (size_t)I);
+    put(L.parts, 8 * 2 * (size_t)kExactBlocks);
     L.total = o;
     return L;
 }
@@ -1243,11 +1330,11 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.grp = (FGrp *)(w + L.grp);
     a.req = (FReq *)(w + L.req);
     a.inst = (FInst *)(w + L.inst);
-    a.first = (int32_t *)(w + L.first);
-    a.slo64 = (double *)(w + L.slo64);
+    a.blk = (float2 *)(w + L.blk);
     a.nreq = (double *)(w + L.nreq);
-    a.bucket = (FRec *)(w + L.bucket);
-    a.bcnt = (int32_t *)(w + L.bcnt);
+    a.list = (FEntry *)(w + L.list);
+    a.listq = (uint16_t *)(w + L.listq);
+    a.listn = (int32_t *)(w + L.listn);
     a.piece = (Piece *)(w + L.piece);
     a.start = (Start *)(w + L.start);
     a.part = (double *)(w + L.part);
@@ -1256,7 +1343,10 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.ncand = (int32_t *)(w + L.ncand);
     a.cand = (int64_t *)(w + L.cand);
     a.Q = (double *)(w + L.Q);
+    a.parts = (double *)(w + L.parts);
     a.chunk = L.chunk;
+    a.seg = L.seg;
+    a.nseg = (a.G + L.seg - 1) / L.seg;
     return a;
 }
 
@@ -1297,42 +1387,15 @@ int fbegin(const qlm_problem *problem, const qlm_plans *plans, const float *req_
     *out = fargs(problem, plans, req_slo, n_req, ws, L);
     *lay = L;
     if (plans->n_plans == 0 || !prep) return QLM_OK;
-    hipLaunchKernelGGL(k_fprep, dim3(1), dim3(kThreads), 0, stream, *out);
+    hipLaunchKernelGGL(k_fprep, dim3((unsigned)((out->G + kPrepThreads - 1) / kPrepThreads)),
+                       dim3(kPrepThreads), 0, stream, *out);
     if ((rc = launched("k_fprep launch"))) return rc;
-    if (n_req > 0 && screen) {
-        int64_t blocks = (n_req + kThreads - 1) / kThreads;
-        if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(k_fslo, dim3((unsigned)blocks), dim3(kThreads), 0, stream, *out);
-        if ((rc = launched("k_fslo launch"))) return rc;
+    if (screen) {
+        hipLaunchKernelGGL(k_fblocks, dim3((unsigned)((out->G + kWaves - 1) / kWaves)),
+                           dim3(kThreads), 0, stream, *out);
+        if ((rc = launched("k_fblocks launch"))) return rc;
     }
     return QLM_OK;
-}
-
-// k_frec in the form the problem allows: wavefront buffers for 64 group
-// blocks where they suffice, and the tables in LDS where they leave as many
-// workgroups on a CU as there are without them.
-template <int kNB>
-int launch_frec_nb(const FArgs &a, size_t tab_bytes, dim3 grid, hipStream_t stream, int64_t p0,
-                   int64_t pc)
-{
-    const size_t fixed = sizeof(WaveBuf<kNB>) * kRecWaves;
-    if (tab_bytes <= kFrecTabLimit &&
-        kCuLds / (fixed + tab_bytes) == kCuLds / fixed) {
-        hipLaunchKernelGGL((k_frec<kNB, true>), grid, dim3(kRecWaves * kWave), tab_bytes, stream, a,
-                           p0, pc);
-    } else {
-        hipLaunchKernelGGL((k_frec<kNB, false>), grid, dim3(kRecWaves * kWave), 0, stream, a, p0,
-                           pc);
-    }
-    return launched("k_frec launch");
-}
-
-int launch_frec(const FArgs &a, size_t tab_bytes, dim3 grid, hipStream_t stream, int64_t p0,
-                int64_t pc)
-{
-    const int nblk = (a.G + kBlk - 1) / kBlk;
-    if (nblk <= 64) return launch_frec_nb<64>(a, tab_bytes, grid, stream, p0, pc);
-    return launch_frec_nb<kMaxBlocks>(a, tab_bytes, grid, stream, p0, pc);
 }
 
 // The screen over every plan, chunk by chunk: F and the per-block minima.
@@ -1342,7 +1405,12 @@ int screen_all(const FArgs &a, hipStream_t stream)
     for (int64_t p0 = 0; p0 < a.P; p0 += a.chunk) {
         const int64_t pc = a.P - p0 < a.chunk ? a.P - p0 : a.chunk;
         const int64_t tiles = (pc + kWave - 1) / kWave;
-        const int64_t sq = ((a.G + kSeg - 1) / kSeg + kSegWaves - 1) / kSegWaves;
+        // workgroups of 16 wavefronts, or of 8 or 4 where that leaves CUs without
+        // one (the tables in LDS are then copied by more workgroups)
+        int waves = kSegWaves;
+        while (waves > 4 && tiles * ((a.nseg + waves - 1) / waves) < kSegBlocks) waves /= 2;
+        const dim3 wgrid((unsigned)(tiles * ((a.nseg + waves - 1) / waves)));
+        const dim3 wblock((unsigned)(waves * kWave));
         const size_t tab_bytes = swap_bytes(a) + sizeof(FInst) * (size_t)a.I;
         const size_t seg_lds = sizeof(FGrp) * (size_t)a.G + tab_bytes;
         if (seg_lds <= kSegLdsLimit) {
@@ -1350,47 +1418,34 @@ int screen_all(const FArgs &a, hipStream_t stream)
                                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                                      (int)seg_lds);
             if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-            hipLaunchKernelGGL(k_fseg<true>, dim3((unsigned)(tiles * sq)), dim3(kSegThreads),
-                               seg_lds, stream, a, p0, pc);
+            hipLaunchKernelGGL(k_fseg<true>, wgrid, wblock, seg_lds, stream, a, p0, pc);
         } else {
-            hipLaunchKernelGGL(k_fseg<false>, dim3((unsigned)(tiles * sq)), dim3(kSegThreads), 0,
-                               stream, a, p0, pc);
+            hipLaunchKernelGGL(k_fseg<false>, wgrid, wblock, 0, stream, a, p0, pc);
         }
         if ((rc = launched("k_fseg launch"))) return rc;
-        hipLaunchKernelGGL(k_fstart, dim3((unsigned)((pc + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, stream, a, pc);
+        hipLaunchKernelGGL(k_fstart, dim3((unsigned)tiles), dim3(kWave), 0, stream, a, pc);
         if ((rc = launched("k_fstart launch"))) return rc;
-        const int64_t nblk = (a.G + kBlk - 1) / kBlk;
-        int64_t zb = (tiles * nblk + kThreads - 1) / kThreads;
-        if (zb > 1024) zb = 1024;
-        hipLaunchKernelGGL(k_fbzero, dim3((unsigned)zb), dim3(kThreads), 0, stream, a, tiles * nblk);
-        if ((rc = launched("k_fbzero launch"))) return rc;
-        const int64_t sq2 = ((a.G + kSeg - 1) / kSeg + kRecWaves - 1) / kRecWaves;
-        const int64_t tiles8 = (tiles + kXcds - 1) / kXcds * kXcds;
-        if ((rc = launch_frec(a, tab_bytes, dim3((unsigned)(tiles8 * sq2)), stream, p0, pc)))
-            return rc;
-        const hipError_t ea = hipFuncSetAttribute((const void *)k_fbscreen,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  (int)(sizeof(FRec) * kBlkCap));
-        if (ea != hipSuccess) return hip_fail(ea, "hipFuncSetAttribute");
+        if (seg_lds <= kSegLdsLimit) {
+            const hipError_t e = hipFuncSetAttribute((const void *)k_fwalk<true>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (int)seg_lds);
+            if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
+            hipLaunchKernelGGL(k_fwalk<true>, wgrid, wblock, seg_lds, stream, a, p0, pc);
+        } else {
+            hipLaunchKernelGGL(k_fwalk<false>, wgrid, wblock, 0, stream, a, p0, pc);
+        }
+        if ((rc = launched("k_fwalk launch"))) return rc;
         qlm_internal::TimedLaunch tl;
         if ((rc = qlm_internal::timing_begin(stream, &tl))) return rc;
-        hipLaunchKernelGGL(k_fbscreen, dim3((unsigned)(tiles * nblk)), dim3(kTransThreads),
-                           sizeof(FRec) * kBlkCap, stream, a, pc);
-        if ((rc = launched("k_fbscreen launch"))) return rc;
+        hipLaunchKernelGGL(k_ftails, dim3((unsigned)(tiles * a.nseg)), dim3(kTailWaves * kWave), 0,
+                           stream, a, pc);
+        if ((rc = launched("k_ftails launch"))) return rc;
         qlm_internal::timing_end(stream, &tl);
         hipLaunchKernelGGL(k_fsum, dim3(kSumBlocks), dim3(kThreads), 0, stream, a, p0, pc,
                            p0 == 0 ? 1 : 0);
         if ((rc = launched("k_fsum launch"))) return rc;
     }
     return QLM_OK;
-}
-
-int exact_grid(int64_t tasks)
-{
-    int64_t b = tasks;                         // a workgroup per task
-    if (b > kExactBlocks) b = kExactBlocks;
-    return (int)(b < 1 ? 1 : b);
 }
 
 }  // namespace
@@ -1439,7 +1494,7 @@ int qlm_fcfs_score_exact(const qlm_problem *problem, const qlm_plans *plans, con
                     stream);
     if (rc) return rc;
     if (n == 0) return QLM_OK;
-    hipLaunchKernelGGL(k_fexact, dim3((unsigned)exact_grid(n * a.I)), dim3(kExactThreads), 0, stream, a,
+    hipLaunchKernelGGL(k_fexact, dim3(kExactBlocks), dim3(kExactThreads), 0, stream, a,
                        plan_index, (const int32_t *)nullptr, n);
     if ((rc = launched("k_fexact launch"))) return rc;
     int64_t blocks = (n + kThreads - 1) / kThreads;
@@ -1459,9 +1514,10 @@ int qlm_fcfs_best_plan(const qlm_problem *problem, const qlm_plans *plans, const
     FLayout L;
     int rc = fbegin(problem, plans, req_slo, n_requests, ws, ws_bytes, &a, &L, true, true, stream);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_fzero, dim3(1), dim3(kWave), 0, stream, a);
-    if ((rc = launched("k_fzero launch"))) return rc;
-    if (plans->n_plans > 0) {
+    if (plans->n_plans == 0) {
+        hipLaunchKernelGGL(k_fzero, dim3(1), dim3(kWave), 0, stream, a);
+        if ((rc = launched("k_fzero launch"))) return rc;
+    } else {
         if ((rc = screen_all(a, stream))) return rc;
         hipLaunchKernelGGL(k_fselect, dim3(kSumBlocks), dim3(kThreads), 0, stream, a, kSumBlocks);
         if ((rc = launched("k_fselect launch"))) return rc;

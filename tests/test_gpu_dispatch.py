@@ -94,3 +94,57 @@ def test_seed_lanes(qlm, orc, G, I, kind):
         perm, qoff = orc.seed_plan(pr, k)
         assert np.array_equal(sp.perm[:, k].cpu().numpy(), perm)
         assert np.array_equal(sp.qoff[:, k].cpu().numpy(), qoff)
+
+
+# Per-request screen: segments of 32, 64 and 128 slots; groups of 0 to 3 blocks
+# of 32 requests and a remainder; spreads from none to wider than the waits (every
+# group sure, some, none); SLOs met exactly, infinite or far apart within a
+# group; negative tokens (no sure side)
+@pytest.mark.parametrize("G,I,P,kind", [
+    (1, 1, 3, "plain"), (40, 3, 130, "plain"), (130, 4, 65, "ragged"), (257, 16, 200, "ragged"),
+    (300, 5, 64, "wide"), (200, 6, 70, "none"), (150, 4, 100, "half"), (90, 3, 64, "infinite"),
+    (120, 4, 64, "negative"), (600, 9, 9000, "plain"), (513, 64, 26000, "plain")])
+def test_fcfs_lists(qlm, orc, G, I, P, kind):
+    import torch
+    pr, pl = make(G, I, P, 300 + G, sizes=(0, 100) if kind == "ragged" else (32, 64))
+    rng = np.random.default_rng(G)
+    if kind == "wide":
+        pr["grp_var"] = (pr["grp_var"] * 1e4).astype(np.float32)
+    if kind == "none":
+        pr["grp_var"][:] = 0.0
+        pr["grp_mu"] = rng.integers(1, 9, G).astype(np.float32) * 100.0
+        pr["inst_tput"][:] = 800.0
+    if kind == "half":
+        pr["grp_var"][rng.random(G) < 0.5] = 0.0
+    if kind == "negative":
+        pr["grp_mu"] = rng.uniform(-200.0, 600.0, G).astype(np.float32)
+    N = int(pr["grp_count"].sum())
+    req = rng.uniform(0.0, 3000.0, N).astype(np.float32)
+    if kind == "none":
+        req = rng.integers(0, 3000, N).astype(np.float32)       # waits met exactly among them
+    if kind == "infinite":
+        req[rng.random(N) < 0.2] = np.inf
+    dpr, dpl = device_inputs(pr, pl)
+    dreq = qlm.device_requests(req)
+    print("case fcfs lists", G, I, P, kind, flush=True)
+    F = qlm.fcfs_score(dpr, dpl, dreq).cpu().numpy()
+    n = min(P, 400)
+    S = orc.score_plans_fcfs(pr, pl, req, 0, n) if n < P else orc.score_plans_fcfs(pr, pl, req)
+    err = np.abs(F[:n] - S[:n])
+    assert np.all(err <= SCORE_REL * N + 1e-9), err.max()
+    # chunks of 64 plans change no bit
+    m = min(P, 700)
+    sub = qlm.DevicePlans(dpl.perm, dpl.qoff, dpl.evict_bits, m)
+    whole = qlm.fcfs_score(dpr, sub, dreq)
+    small = qlm.fcfs_score(dpr, sub, dreq,
+                           ws=qlm.fcfs_workspace(dpr, m, N, chunk_plans=64))
+    bi, bs = qlm.fcfs_best_plan(dpr, dpl, dreq)
+    some = qlm.fcfs_score_exact(dpr, dpl, dreq, np.arange(n))
+    torch.cuda.synchronize()
+    assert torch.equal(whole, small)
+    X = some.cpu().numpy()
+    assert np.all(np.abs(X - S[:n]) <= 1e-12 * (np.abs(S[:n]) + 1.0))
+    # one task, several and many: the same bits
+    one = qlm.fcfs_score_exact(dpr, dpl, dreq, [int(bi.item())])
+    assert float(one[0]) == float(bs[0])
+    assert float(one[0]) <= X.min()
