@@ -1446,7 +1446,70 @@ __global__ void k_zero_i64(int64_t *p)
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
 
-// One workgroup per plan: a bitmap of seen group ids in LDS.
+// One workgroup per 2^ls plans, its threads that many to a row: the rows of perm
+// and qoff are read coalesced, kValRows of them in flight per thread, and every
+// plan has a bitmap of seen group ids in LDS (word w of plan j at w 2^ls + j: with
+// 64 plans a wavefront's 64 bits lie in 64 banks).  A permutation sets G bits.
+// Bytes bound it: 16,384 plans of 1024 groups (70 MB) take 14.8 us; a workgroup
+// per plan, whose reads were 4 bytes out of every row, took 84.
+constexpr int kValThreads = 1024;
+constexpr int kValRows = 8;
+constexpr int kMaxValShift = 6, kMinValShift = 3;
+
+__global__ __launch_bounds__(kValThreads) void k_validate_tile(ExactArgs a, int ls,
+                                                               int64_t *n_invalid, int32_t *status)
+{
+    extern __shared__ unsigned int seen[];
+    __shared__ int s_bad[1 << kMaxValShift], s_bits[1 << kMaxValShift];
+    const int L = 1 << ls, per = kValThreads >> ls;     // plans, rows a pass
+    const int W = (a.G + 31) / 32;
+    const int j = (int)threadIdx.x & (L - 1), r = (int)threadIdx.x >> ls;
+    const int64_t p0 = (int64_t)blockIdx.x << ls;
+    const bool on = p0 + j < a.P;
+    const int64_t p = on ? p0 + j : a.P - 1;
+    for (int w = threadIdx.x; w < W << ls; w += kValThreads) seen[w] = 0u;
+    if ((int)threadIdx.x < L) s_bad[threadIdx.x] = s_bits[threadIdx.x] = 0;
+    __syncthreads();
+    int bad = 0;
+    for (int g = r; g <= a.I; g += per) {
+        const int32_t q = a.qoff[(int64_t)g * a.ld + p];
+        if (g == 0 && q != 0) bad |= 1;
+        if (g == a.I && q != a.G) bad |= 1;
+        if (g < a.I && q > a.qoff[(int64_t)(g + 1) * a.ld + p]) bad |= 1;
+        if (q < 0 || q > a.G) bad |= 1;
+    }
+    for (int s0 = r; s0 < a.G; s0 += per * kValRows) {
+        int32_t id[kValRows];
+#pragma unroll
+        for (int u = 0; u < kValRows; ++u)
+            id[u] = a.perm[(int64_t)min(s0 + u * per, a.G - 1) * a.ld + p];
+#pragma unroll
+        for (int u = 0; u < kValRows; ++u) {
+            if (s0 + u * per >= a.G) break;
+            if ((uint32_t)id[u] >= (uint32_t)a.G)
+                bad |= 2;
+            else
+                atomicOr(&seen[((id[u] >> 5) << ls) + j], 1u << (id[u] & 31));
+        }
+    }
+    if (a.evict && (a.G & 31) && r == 0)
+        if (a.evict[(int64_t)(W - 1) * a.ld + p] >> (a.G & 31)) bad |= 4;
+    if (bad) atomicOr(&s_bad[j], bad);
+    __syncthreads();
+    int bits = 0;
+    for (int w = r; w < W; w += per) bits += __popc(seen[(w << ls) + j]);
+    if (bits) atomicAdd(&s_bits[j], bits);
+    __syncthreads();
+    if (r == 0) {
+        const int b = s_bad[j] | (s_bits[j] != a.G ? 2 : 0);
+        if (on && status) status[p] = b;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(on && b != 0);
+        if (m && j == 0) atomicAdd((unsigned long long *)n_invalid, (unsigned long long)__popcll(m));
+    }
+}
+
+// More groups than eight plans' bitmaps of k_validate_tile leave room for: one
+// workgroup per plan.
 __global__ __launch_bounds__(256) void k_validate_plans(ExactArgs a, int64_t *n_invalid,
                                                        int32_t *status)
 {
@@ -1597,6 +1660,7 @@ using qlm_internal::fail;
 using qlm_internal::hip_fail;
 
 constexpr size_t kLdsLimit = 160 * 1024;   // gfx950 LDS per workgroup
+constexpr int64_t kValBlocks = 512;        // workgroups of k_validate_tile that fill the chip
 
 // Dynamic LDS of the scoring kernel: everything but its static tail table.
 constexpr size_t kScoreLdsLimit = kLdsLimit - sizeof(float) * 2 * kTailCells;
@@ -2091,12 +2155,26 @@ int qlm_validate_plans(const qlm_problem *problem, const qlm_plans *plans, int64
     ExactArgs a = exact_args(problem, plans);
     const size_t lds = 4 * (size_t)((problem->n_groups + 31) / 32);
     if (lds > kLdsLimit) return fail(QLM_ERR_CAPACITY, "too many groups to validate");
-    e = hipFuncSetAttribute((const void *)k_validate_plans,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const int64_t P = plans->n_plans;
+    // plans a workgroup: 64, fewer (down to 8, whose rows are 32 bytes) where that
+    // leaves less than two workgroups a CU or where the bitmaps do not fit
+    int ls = kMaxValShift;
+    while (ls > kMinValShift && (P >> ls) < kValBlocks) --ls;
+    while (ls >= kMinValShift && (lds << ls) + 1024 > kLdsLimit) --ls;
+    const bool tile = ls >= kMinValShift;
+    const size_t bytes = tile ? lds << ls : lds;
+    const void *kernel = tile ? (const void *)k_validate_tile : (const void *)k_validate_plans;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
-    const int grid = (int)(plans->n_plans < 8192 ? plans->n_plans : 8192);
-    hipLaunchKernelGGL(k_validate_plans, dim3(grid), dim3(256), lds, stream, a, n_invalid,
-                       plan_status);
+    if (tile) {
+        const unsigned grid = (unsigned)((P + (1 << ls) - 1) >> ls);
+        hipLaunchKernelGGL(k_validate_tile, dim3(grid), dim3(kValThreads), bytes, stream, a, ls,
+                           n_invalid, plan_status);
+    } else {
+        const int grid = (int)(P < 8192 ? P : 8192);
+        hipLaunchKernelGGL(k_validate_plans, dim3(grid), dim3(256), bytes, stream, a, n_invalid,
+                           plan_status);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_validate_plans launch");
     return QLM_OK;

@@ -148,3 +148,36 @@ def test_fcfs_lists(qlm, orc, G, I, P, kind):
     one = qlm.fcfs_score_exact(dpr, dpl, dreq, [int(bi.item())])
     assert float(one[0]) == float(bs[0])
     assert float(one[0]) <= X.min()
+
+
+# Validation: 8 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
+# a workgroup per plan past them; each kind of malformed plan at the tile's edges
+@pytest.mark.parametrize("G,I,P,ld", [
+    (1, 1, 5, 5), (33, 4, 4097, 4100), (64, 1, 9000, 9000), (500, 9, 16500, 16501),
+    (300, 9, 33000, 33000), (5000, 16, 70, 70), (25000, 3, 33, 40), (170000, 2, 3, 3)])
+def test_validate_tiles(qlm, G, I, P, ld):
+    import torch
+    pr, pl = make(G, I, P, 900 + G, ld=ld)
+    rng = np.random.default_rng(G)
+    want = np.zeros(P, np.int32)
+    for p in {0, P - 1, P // 2, min(63, P - 1), min(64, P - 1)}:
+        if G > 1:
+            kind = int(rng.integers(0, 4))
+            if kind == 0:
+                pl["perm"][G - 1, p] = pl["perm"][0, p]
+            elif kind == 1:
+                pl["perm"][int(rng.integers(0, G)), p] = [-1, G][int(rng.integers(0, 2))]
+            if kind <= 1:
+                want[p] |= 2
+            if kind == 2:
+                pl["qoff"][I, p] = G - 1
+                want[p] |= 1
+        if G % 32 and (G == 1 or kind == 3):
+            pl["evict_bits"][-1, p] |= np.uint32(1) << np.uint32(G % 32)
+            want[p] |= 4
+    dpr, dpl = device_inputs(pr, pl)
+    print("case validate", G, I, P, flush=True)
+    n, status = qlm.validate_plans(dpr, dpl)
+    torch.cuda.synchronize()
+    assert np.array_equal(status.cpu().numpy(), want)
+    assert int(n.item()) == int((want != 0).sum())
