@@ -59,6 +59,11 @@
 // formed from the exact score's sums, so the move is re-scored exactly.
 // Exact scores (of the candidates) walk both queues exactly.
 //
+// What a screen finds is the change a move makes to the score of a queue, and it
+// depends on the group and on that queue alone; it is kept by group and queue
+// (X, below).  A step changes two queues, so after the first step only the moves
+// of those two are screened again: 1 in 32 of them with 64 queues.
+//
 // Kernels
 //   k_srank    once per call: the groups ranked by SLO (partial counts per
 //              tile of 1024 groups; k_srankout sums them, places each group
@@ -76,8 +81,9 @@
 //              wavefront (one record read per position for all 128 moves); in
 //              the same launch, one lane per slot: screened RELOCATE within
 //              the slot's queue
-//   k_sbound / k_sselect / k_sexact   the bound min(F + D), the candidates,
-//              their exact scores
+//   k_finc     after a step: the screens of the two queues it changed
+//   k_smin / k_sselect / k_sexact   the bound min(F + D), the candidates, their
+//              exact scores
 //   k_spick    lowest (exact score, k) of the candidates; applied when it
 //              improves on the plan, else the chain has converged
 //   k_sout     final plans back to the caller's slot-major layout
@@ -191,8 +197,9 @@ struct SearchArgs {
     SRec *srec;                   // [G]
     SSt *sst;                     // [G]
     TRec *trec;                   // [G]
-    double *R;                    // [G] score of the queue of s without s (exact in
-                                  // the exact kernels, screened in the screens)
+    double *R;                    // [G] exact kernels: score of the queue of slot s
+                                  // without s; screens: what group i's leaving its
+                                  // queue changes of the queue's score (screened)
     double *RD;                   // [G] bound of the screened one
     double *Q;                    // [I] queue scores
     double *Nq;                   // [I] requests per queue
@@ -203,18 +210,22 @@ struct SearchArgs {
     double *wmin_s;               // [nwg] exact kernels: workgroup minima
     int64_t *wmin_i;              // [nwg] and their move numbers
     double *smin;                 // [nws] screens: workgroup minima of F + D
-    double *F, *D;                // [n_moves] screened scores and their bounds
+    double *X;                    // [n_moves] screened changes of scores, by group (entry)
+    double *F, *D;                // [B][n_moves] screened scores and their bounds (or null)
     int32_t *cand;                // [n_moves] candidate moves
     double *cex;                  // [n_moves] their exact scores
     int32_t *ncand;               // [1]
     double *U;                    // [1] min(F + D)
     int32_t *scratch;             // [2 G] shifts of k_spick
     int32_t *dq;                  // [4] placement: the group's slot and queue, and
-                                  // whether it is running (stays)
+                                  // whether it is running (stays); search: the two
+                                  // queues the last step changed, and the group
+                                  // whose flag it set (-1: none)
     int32_t nwg_a, nwg_b, nwg;    // per chain: k_sswap, k_smove and k_sreloc (per
                                   // queue), total
     int32_t nwg_f, nwg_r, nws;    // per chain: k_fswap (d = 0..W), k_fmove's own-queue
-                                  // relocations, all screen workgroups
+                                  // relocations, k_smin
+    int32_t inc_f, inc_r;         // the same for each of two changed queues; 0: screen all
     int64_t n_moves;
     double *move_score;           // [B][n_moves] or null (exact kernels)
     int64_t *trace;               // [B][max_steps] or null
@@ -1005,59 +1016,97 @@ __device__ inline double tail_walk(const TrAt &tr_at, const VAt &v_at, const flo
     return acc;
 }
 
-// Screened removals and SWAPs, one lane per task: tasks [0, G) are the
-// queues of each slot s without s (which the MOVE screens of s take up),
-// tasks G + s*W + d - 1 the moves SWAP(s, d).
-__global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
+// What the screens leave, by group: entry k of a chain's X is the change of the
+// plan's score (of the queue's, before the removal of a reassigned group) that a
+// move makes, +inf where it names no move; its lowest bit is set where the screen
+// cannot bound it (the bound the change enters, 1e-12 of the scores, covers the
+// bit).  A group's entries depend on its own queue (swaps, the relocation within
+// it, its removal R) or on one target queue (reassignments and relocations into
+// it), and on its eviction flag, not on its slot or on other queues: a search step
+// leaves all of them standing but those of the two queues it changed and the
+// reassignments of a group whose flag it set.
+//   SWAP of group i with the group d slots on   k = i*W + d - 1
+//   MOVE of group i into queue h                k = G*W + i*I + h
+//   RELOCATE of group i into queue h            k = G*W + G*I + i*I + h
+__device__ inline double entry(double change, bool force)
 {
-    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
-    __shared__ double lmin[kWaves];
-    __shared__ int lint_lo[kWaves], lint_hi[kWaves];
-    // one buffer: first the slot records the lanes visit, then their tails
-    // (records and variances ahead)
-    __shared__ __align__(16) unsigned char stbuf[kSwapStageBytes];
-    __shared__ float st_c[kSwapCostStage];
+    const long long u = __double_as_longlong(change);
+    return __longlong_as_double((u & ~1ll) | (force ? 1ll : 0ll));
+}
+__device__ inline bool forced(double e) { return (__double_as_longlong(e) & 1ll) != 0; }
+
+// The queue that a workgroup of an incremental screen works on: the which-th (0
+// or 1) of the two the last step changed, -1 when that is the first again.
+__device__ inline int changed_queue(const SearchArgs &a, int64_t b, int which)
+{
+    const int g = clampi(a.dq[b * 4], 0, a.I - 1), h = clampi(a.dq[b * 4 + 1], 0, a.I - 1);
+    return which == 0 ? g : (h == g ? -1 : h);
+}
+
+// Screened removals and SWAPs of the groups at slots [base, base + len), one lane
+// per task: tasks [0, len) are the queues of each slot s without s (which the
+// MOVEs of s take up), tasks len + (s - base)*W + d - 1 the moves SWAP(s, d).
+// With a.inc_f = 0 a chain's nwg_f workgroups take all slots; else inc_f take
+// each of the two changed queues', looping over its tasks.  stbuf: first the slot
+// records the lanes visit, then their tails (records and variances ahead).
+__device__ inline void fswap_body(const SearchArgs &a, int bid, float2 *tab, float *st_c,
+                                  int *lint_lo, int *lint_hi, unsigned char *stbuf)
+{
     SRec *st_r = reinterpret_cast<SRec *>(stbuf);
     TRec *st_t = reinterpret_cast<TRec *>(stbuf);
     double *st_v = reinterpret_cast<double *>(stbuf + kSwapStage * sizeof(TRec));
-    const int64_t b = blockIdx.x / a.nwg_f;
-    const int wg = blockIdx.x % a.nwg_f;
+    const int per_chain = a.inc_f ? 2 * a.inc_f : a.nwg_f;
+    const int64_t b = bid / per_chain;
+    const int in_chain = bid % per_chain;
     if (a.done[b]) return;                    // the same in the whole workgroup
     const int G = a.G, I = a.I, W = a.W;
     const SRec *__restrict__ sr = a.srec + b * G;
-    // the slots this workgroup's tasks visit, [vlo, vhi): removals t < G visit
-    // t and t + 1, swaps s = (t - G) / W up to W + 1 past s; a workgroup can
-    // hold both kinds
-    const int t0 = wg * kThreads, t1 = min(t0 + kThreads, G + G * W) - 1;
-    int vlo = G, vhi = 0;
-    if (t0 < G) {
-        vlo = t0;
-        vhi = min(t1, G - 1) + 2;
-    }
-    if (t1 >= G) {
-        vlo = min(vlo, (max(t0, G) - G) / W);
-        vhi = max(vhi, (t1 - G) / W + W + 2);
-    }
-    vhi = min(vhi, G);
-    const bool rec_lds = vhi - vlo <= kSwapRecs;
-    const int ncost = a.swap_cost ? a.C * a.M * a.M : 0;
-    const bool cost_lds = ncost <= kSwapCostStage;
-    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
-    if (rec_lds)
-        for (int u = vlo + (int)threadIdx.x; u < vhi; u += kThreads) st_r[u - vlo] = sr[u];
-    if (cost_lds)
-        for (int k = threadIdx.x; k < ncost; k += kThreads) st_c[k] = a.swap_cost[k];
-    __syncthreads();
-    auto rec = [&](int u) { return rec_lds ? st_r[u - vlo] : sr[u]; };
-    const float *swc = cost_lds ? st_c : nullptr;
     const SSt *__restrict__ ss = a.sst + b * G;
     const TRec *__restrict__ tr = a.trec + b * G;
     const int32_t *__restrict__ qof = a.qof + b * (I + 1);
+    const int32_t *__restrict__ perm = a.perm + b * G;
+    int base = 0, len = G, wg0 = in_chain, stride = a.nwg_f;
+    if (a.inc_f) {
+        const int h = changed_queue(a, b, in_chain / a.inc_f);
+        if (h < 0) return;
+        base = qof[h];
+        len = qof[h + 1] - base;
+        wg0 = in_chain % a.inc_f;
+        stride = a.inc_f;
+    }
+    const int ntask = len + len * W;
+    const int ncost = a.swap_cost ? a.C * a.M * a.M : 0;
+    const bool cost_lds = ncost <= kSwapCostStage;
+    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
+    if (cost_lds)
+        for (int k = threadIdx.x; k < ncost; k += kThreads) st_c[k] = a.swap_cost[k];
+    const float *swc = cost_lds ? st_c : nullptr;
+    for (int wg = wg0; wg * kThreads < ntask; wg += stride) {
+    // the slots this workgroup's tasks visit, [vlo, vhi): removals t < len visit
+    // t and t + 1, swaps s = (t - len) / W up to W + 1 past s; a workgroup can
+    // hold both kinds
+    const int t0 = wg * kThreads, t1 = min(t0 + kThreads, ntask) - 1;
+    int vlo = G, vhi = 0;
+    if (t0 < len) {
+        vlo = base + t0;
+        vhi = base + min(t1, len - 1) + 2;
+    }
+    if (t1 >= len) {
+        vlo = min(vlo, base + (max(t0, len) - len) / W);
+        vhi = max(vhi, base + (t1 - len) / W + W + 2);
+    }
+    vhi = min(vhi, G);
+    const bool rec_lds = vhi - vlo <= kSwapRecs;
+    __syncthreads();                          // (the round before is done with the buffer)
+    if (rec_lds)
+        for (int u = vlo + (int)threadIdx.x; u < vhi; u += kThreads) st_r[u - vlo] = sr[u];
+    __syncthreads();
+    auto rec = [&](int u) { return rec_lds ? st_r[u - vlo] : sr[u]; };
     const int t = wg * kThreads + threadIdx.x;
-    const bool removal = t < G;
-    const bool swap = !removal && t < G + G * W;
-    const int s = removal ? t : (swap ? (t - G) / W : 0);
-    const int d = swap ? (t - G) - s * W + 1 : 0;
+    const bool removal = t < len;
+    const bool swap = !removal && t < ntask;
+    const int s = base + (removal ? t : (swap ? (t - len) / W : 0));
+    const int d = swap ? (t - len) - (s - base) * W + 1 : 0;
     int g = 0, eq = 0, lo = 0;
     bool on = false, force = false, valid = false;
     double q = 0.0, dE = 0.0, db = 0.0, vscale = 0.0;
@@ -1140,25 +1189,25 @@ __global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
     else
         q += tail_walk([&](int u) { return tr[u]; }, [&](int u) { return ss[u].V; }, tab, on, lo,
                        eq, dE, 0.0f, db, vscale, exactv);
-    double F = INFINITY, D = 0.0;
-    if (valid) {
+    if (removal) {
+        const int i = perm[s];
         const double nq = a.Nq[b * I + g];
-        if (removal) {
-            a.R[b * G + s] = q;
-            a.RD[b * G + s] = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(a.Q[b * I + g]) + nq);
-        } else {
-            const double cur = a.cur[b];
-            F = cur - a.Q[b * I + g] + q;
-            D = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(cur) + nq);
-        }
+        a.R[b * G + i] = q - a.Q[b * I + g];
+        a.RD[b * G + i] = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(a.Q[b * I + g]) + nq);
     }
-    if (swap) {
-        const int64_t k = (int64_t)s * W + (d - 1);
-        a.F[b * a.n_moves + k] = F;
-        a.D[b * a.n_moves + k] = D;
+    if (swap)
+        a.X[b * a.n_moves + (int64_t)perm[s] * W + (d - 1)] =
+            valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
     }
-    const double m = block_min(F + D, lmin);
-    if (threadIdx.x == 0) a.smin[b * a.nws + wg] = m;
+}
+
+__global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
+{
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
+    __shared__ int lint_lo[kWaves], lint_hi[kWaves];
+    __shared__ __align__(16) unsigned char stbuf[kSwapStageBytes];
+    __shared__ float st_c[kSwapCostStage];
+    fswap_body(a, (int)blockIdx.x, tab, st_c, lint_lo, lint_hi, stbuf);
 }
 
 // Screened MOVE and RELOCATE into another queue h: one workgroup per (target
@@ -1170,16 +1219,22 @@ __global__ __launch_bounds__(kThreads) void k_fswap(SearchArgs a)
 // tokens, variance and the change of costs.  The whole wavefront walks those
 // positions in step from the earliest of its lanes' tails, forming both
 // moves' terms at each position (a lane's MOVE term only past its insertion
-// point).
+// point).  Running groups, which may not move now, are screened too: their
+// entries are there when a later step makes them movable.
+// kBoth: both moves; else (an incremental screen, whose few workgroups leave room)
+// a workgroup forms one of them.
+template <bool kBoth>
 __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, float *st_c,
-                                  double *lmin, int *lint, TRec *stage)
+                                  int *lint, TRec *stage)
 {
     const int G = a.G, I = a.I;
-    const int per_chain = I * a.nwg_b;
+    const int per_chain = (kBoth ? I : 4) * a.nwg_b;
     const int64_t b = bid / per_chain;
-    const int h = (bid % per_chain) / a.nwg_b;
     const int wg = bid % a.nwg_b;
     if (a.done[b]) return;                    // the same in the whole workgroup
+    int h = (bid % per_chain) / a.nwg_b;
+    const bool do_m = kBoth || (h & 1) == 0, do_r = kBoth || !do_m;
+    if (!kBoth && (h = changed_queue(a, b, h >> 1)) < 0) return;
     const SRec *__restrict__ sr = a.srec + b * G;
     const SSt *__restrict__ ss = a.sst + b * G;
     const TRec *__restrict__ tr = a.trec + b * G;
@@ -1208,17 +1263,17 @@ __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, flo
     const int r = wg * kThreads + threadIdx.x;
     bool valid_m = false, valid_r = false, tail_m = false, tail_r = false;
     bool force_m = false, force_r = false;
-    int s = 0, g = 0, p = eq;
+    int s = 0, g = 0, p = eq, i = 0;
     double N_m = 0.0, N_r = 0.0, dE_m = 0.0, dE_r = 0.0;
     float dvz = 0.0f;
     if (r < G) {
-        const int i = a.by_slo[r];
+        i = a.by_slo[r];
         s = clampi(a.inv[b * G + i], 0, G - 1);
         const SRec x = sr[s];
         g = (int)x.q;
-        // a running group never moves; RELOCATE needs a group to evict
-        valid_m = g != h && s != qof[g];
-        valid_r = valid_m && bq < eq;
+        // RELOCATE needs a group to evict
+        valid_m = g != h && do_m;
+        valid_r = g != h && do_r && bq < eq;
         dvz = (float)(x.b * vscale);
         if (valid_m) {
             Run w;
@@ -1286,6 +1341,23 @@ __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, flo
             if (threadIdx.x < 7) stage[c1 - c0 + threadIdx.x] = TRec{0.0, 1.0f, 0.0f};
             __syncthreads();
             int u = max(c0, ulo);
+            if (!kBoth) {
+                // one kind: its change of margin, the lanes' tails masked at their start
+                const double dE = do_m ? dE_m : dE_r;
+                const bool tail = tail_m || tail_r;
+                for (; u < c1; u += 8) {
+                    const TRec *xs = stage + (u - c0);
+                    float s1 = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const TRec x = xs[j];
+                        const float q = qlm_tail::q_of(tab, (float)(x.m - dE), x.vz + dvz);
+                        s1 = fmaf(u + j >= lo ? x.n : 0.0f, q, s1);
+                    }
+                    acc_m += tail ? (double)s1 : 0.0;
+                }
+                continue;
+            }
             // masked part: some lanes' MOVE tails start later
             for (; u < c1 && u <= umask; ++u) {
                 const TRec x = stage[u - c0];
@@ -1312,32 +1384,14 @@ __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, flo
             }
         }
         N_m += tail_m ? acc_m : 0.0;
-        N_r += tail_r ? acc_r : 0.0;
-    }
-    double F_m = INFINITY, D_m = 0.0, F_r = INFINITY, D_r = 0.0;
-    if (valid_m) {
-        const double cur = a.cur[b];
-        const double nq = a.Nq[b * I + h];
-        const double base = a.R[b * G + s] - a.Q[b * I + g];
-        const double rd = a.RD[b * G + s] + kEpsP * nq + 1e-12 * (fabs(cur) + nq);
-        F_m = cur + base + (N_m - Qh);
-        D_m = force_m ? INFINITY : rd;
-        if (valid_r) {
-            F_r = cur + base + (N_r - Qh);
-            D_r = force_r ? INFINITY : rd;
-        }
+        N_r += tail_r ? (kBoth ? acc_r : acc_m) : 0.0;
     }
     if (r < G) {
-        const int64_t k = (int64_t)G * a.W + (int64_t)s * I + h;
-        a.F[b * a.n_moves + k] = F_m;
-        a.D[b * a.n_moves + k] = D_m;
-        if (g != h) {                         // frel_body screens RELOCATE into the own queue
-            a.F[b * a.n_moves + k + (int64_t)G * I] = F_r;
-            a.D[b * a.n_moves + k + (int64_t)G * I] = D_r;
-        }
+        double *x = a.X + b * a.n_moves + (int64_t)G * a.W + (int64_t)i * I + h;
+        if (do_m) *x = valid_m ? entry(N_m - Qh, force_m) : INFINITY;
+        if (do_r && g != h)                   // frel_body screens RELOCATE into the own queue
+            x[(int64_t)G * I] = valid_r ? entry(N_r - Qh, force_r) : INFINITY;
     }
-    const double m = block_min(fmin(F_m + D_m, F_r + D_r), lmin);
-    if (threadIdx.x == 0) a.smin[b * a.nws + a.nwg_f + (int64_t)h * a.nwg_b + wg] = m;
 }
 
 // Screened RELOCATE within the group's own queue, one lane per slot s: the
@@ -1348,12 +1402,22 @@ __device__ inline void fmove_body(const SearchArgs &a, int bid, float2 *tab, flo
 // way); past it only the costs change.  Each wavefront stages the tail
 // records of its queues in LDS when they fit (st: kRelStage per wavefront).
 __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, float *st_c,
-                                 double *lmin, TRec *stall)
+                                 TRec *stall)
 {
-    const int64_t b = bid / a.nwg_r;
-    const int wg = bid % a.nwg_r;
+    const int per_chain = a.inc_f ? 2 * a.inc_r : a.nwg_r;
+    const int64_t b = bid / per_chain;
     if (a.done[b]) return;                    // the same in the whole workgroup
     const int G = a.G, I = a.I;
+    // all slots, or those of one changed queue, whose inc_r workgroups loop
+    int base = 0, end = G, wg0 = bid % per_chain, stride = a.nwg_r;
+    if (a.inc_f) {
+        const int h = changed_queue(a, b, wg0 / a.inc_r);
+        if (h < 0) return;
+        base = a.qof[b * (I + 1) + h];
+        end = a.qof[b * (I + 1) + h + 1];
+        wg0 = wg0 % a.inc_r;
+        stride = a.inc_r;
+    }
     const SRec *__restrict__ sr = a.srec + b * G;
     const SSt *__restrict__ ss = a.sst + b * G;
     const TRec *__restrict__ tr = a.trec + b * G;
@@ -1366,12 +1430,13 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
         for (int k = threadIdx.x; k < ncost; k += kThreads) st_c[k] = a.swap_cost[k];
     __syncthreads();
     const float *swc = cost_lds ? st_c : nullptr;
-    const int s = wg * kThreads + threadIdx.x;
+    for (int wg = wg0; base + wg * kThreads < end; wg += stride) {
+    const int s = base + wg * kThreads + threadIdx.x;
     bool valid = false, force = false, on1 = false, on2 = false;
     int g = 0, lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
     double q = 0.0, dE1 = 0.0, dE2 = 0.0, vscale = 0.0;
     float dvz1 = 0.0f;
-    if (s < G) {
+    if (s < end) {
         SRec x = sr[s];
         g = (int)min(x.q, (uint32_t)(I - 1));
         const int bq = qof[g], eq = qof[g + 1];
@@ -1442,20 +1507,97 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
         q += tail_walk(tr_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
         q += tail_walk(tr_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
     }
-    double F = INFINITY, D = 0.0;
-    if (valid) {
-        const double cur = a.cur[b];
-        const double nq = a.Nq[b * I + g];
-        F = cur - a.Q[b * I + g] + q;
-        D = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(cur) + nq);
+    if (s < end)
+        a.X[b * a.n_moves + (int64_t)G * a.W + (int64_t)G * I + (int64_t)a.perm[b * G + s] * I + g] =
+            valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
     }
-    if (s < G) {
-        const int64_t k = (int64_t)G * a.W + (int64_t)G * I + (int64_t)s * I + g;
-        a.F[b * a.n_moves + k] = F;
-        a.D[b * a.n_moves + k] = D;
+}
+
+// Screened MOVE of the group whose flag the last step set into the queues the
+// step did not change, a wavefront per queue: what fmove_body forms, the
+// positions past the insertion point summed across the lanes.
+__device__ inline void row_body(const SearchArgs &a, int bid, float2 *tab)
+{
+    const int G = a.G, I = a.I;
+    const int nblk = (I + kWaves - 1) / kWaves;
+    const int64_t b = bid / nblk;
+    const int h = (bid % nblk) * kWaves + wave_id();
+    if (a.done[b]) return;
+    const int i = min(a.dq[b * 4 + 2], G - 1);
+    if (i < 0) return;                        // (the same in the whole workgroup)
+    qlm_tail::stage(tab, (int)threadIdx.x, kThreads);
+    __syncthreads();
+    if (h >= I || h == changed_queue(a, b, 0) || h == changed_queue(a, b, 1)) return;
+    const SRec *__restrict__ sr = a.srec + b * G;
+    const SSt *__restrict__ ss = a.sst + b * G;
+    const TRec *__restrict__ tr = a.trec + b * G;
+    const int32_t *__restrict__ qof = a.qof + b * (I + 1);
+    const int bq = qof[h], eq = qof[h + 1];
+    const double theta = (double)a.inst_tput[h];
+    const double inv_theta = 1.0 / theta;
+    const double vscale = qlm_tail::kVarScale / (theta * theta);
+    const int cls = clampi(a.inst_class[h], 0, a.C - 1);
+    const double eps = margin_eps(eq - bq + 1);
+    const double Qh = a.Q[b * I + h];
+    const SRec x = sr[clampi(a.inv[b * G + i], 0, G - 1)];
+    const int lane = threadIdx.x & (kWave - 1);
+    bool force = false;
+    double N;
+    if (bq == eq) {
+        Run w{0.0, 0.0, 0.0, 0.0, model0_of(a, h)};
+        screen_visit(w, x, theta, inv_theta, cls, vscale, eps, tab, a, force);
+        N = w.sc;
+    } else {
+        const int p = insertion_point_wave(sr, bq + 1, eq, x.slo);
+        if (p == eq) {
+            const SSt t = ss[eq - 1];
+            const SRec y = sr[eq - 1];
+            Run w{t.A + y.a, t.V + y.b, t.K, Qh, (int)(y.nmf & 0xFFu)};
+            screen_visit(w, x, theta, inv_theta, cls, vscale, eps, tab, a, force);
+            N = w.sc;
+        } else {
+            Run w = start_at(a, sr, ss, p, bq, h);
+            screen_visit(w, x, theta, inv_theta, cls, vscale, eps, tab, a, force);
+            screen_visit(w, sr[p], theta, inv_theta, cls, vscale, eps, tab, a, force);
+            N = w.sc;
+            const double dE = x.a * inv_theta + (w.K - ss[p].K);
+            const float dvz = (float)(x.b * vscale);
+            if (p + 1 < eq)
+                force = force || !((double)(tr[p + 1].vz + dvz) >=
+                                   vz_floor(eps, a.Es[b * I + h] + fabs(dE)));
+            double acc = 0.0;
+            for (int u = p + 1 + lane; u < eq; u += kWave) {
+                const TRec y = tr[u];
+                acc += (double)(y.n * qlm_tail::q_of(tab, (float)(y.m - dE), y.vz + dvz));
+            }
+            N += wave_sum(acc);
+        }
     }
-    const double m = block_min(F + D, lmin);
-    if (threadIdx.x == 0) a.smin[b * a.nws + a.nwg_f + (int64_t)I * a.nwg_b + wg] = m;
+    if (lane == 0)
+        a.X[b * a.n_moves + (int64_t)G * a.W + (int64_t)i * I + h] = entry(N - Qh, force);
+}
+
+// The plan's queue scores' running sum, in queue order (the sum of k_stotal).
+__device__ inline void total_body(const SearchArgs &a, int64_t b, double *q)
+{
+    if (a.done[b]) return;
+    const int I = a.I;
+    const double *Q = a.Q + b * I;
+    double *T = a.T + b * (I + 1);
+    double t = 0.0;
+    if (threadIdx.x == 0) T[0] = 0.0;
+    for (int g0 = 0; g0 < I; g0 += kThreads) {
+        if (g0 + (int)threadIdx.x < I) q[threadIdx.x] = Q[g0 + threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int n = min(kThreads, I - g0);
+            for (int k = 0; k < n; ++k) {
+                t += q[k];
+                T[g0 + k + 1] = t;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // The screens of moves into another queue and of relocations, in one launch
@@ -1469,7 +1611,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     SearchArgs a)
 {
     __shared__ __align__(16) float2 tab[qlm_tail::kCells];
-    __shared__ double lmin[kWaves];
     __shared__ int lint[kWaves];
     // (the move screens stage kStage records and seven blank ones)
     static_assert(kWaves * kRelStage >= kStage + 7, "the screens' staging buffer");
@@ -1478,50 +1619,187 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     const int nrel = (int)((int64_t)a.nwg_r * a.B);
     const int bid = (int)blockIdx.x;
     if (bid < nrel)
-        frel_body(a, bid, tab, st_c, lmin, stage);
+        frel_body(a, bid, tab, st_c, stage);
     else
-        fmove_body(a, bid - nrel, tab, st_c, lmin, lint, stage);
+        fmove_body<true>(a, bid - nrel, tab, st_c, lint, stage);
 }
 
-// The bound of the chain's lowest exact score, min(F + D); the candidate list
-// starts empty.
-__global__ __launch_bounds__(kThreads) void k_sbound(SearchArgs a)
+// The screens after a search's first step, all in one launch: of the two queues
+// the step changed the removals and swaps (2 inc_f workgroups a chain), the
+// relocations within (2 inc_r) and the moves into them (4 nwg_b), the
+// reassignments of a group whose flag was set (a workgroup per four queues), and
+// the running sums of the queue scores, which the exact re-scores need (one).
+// Two plans of 8192 groups on 64 queues, window 16: 24 us a step; the full screens,
+// every step before, 139.
+__global__ __launch_bounds__(kThreads) void k_finc(SearchArgs a)
+{
+    __shared__ __align__(16) float2 tab[qlm_tail::kCells];
+    __shared__ int lint_lo[kWaves], lint_hi[kWaves];
+    static_assert(kSwapStageBytes >= (int)sizeof(TRec) * kWaves * kRelStage &&
+                  kSwapStageBytes >= (int)sizeof(double) * kThreads, "one staging buffer for all");
+    __shared__ __align__(16) unsigned char stbuf[kSwapStageBytes];
+    __shared__ float st_c[kSwapCostStage];
+    TRec *stage = reinterpret_cast<TRec *>(stbuf);
+    const int B = (int)a.B;
+    const int nmov = 4 * a.nwg_b * B, nswap = 2 * a.inc_f * B, nrel = 2 * a.inc_r * B;
+    const int nrow = (a.I + kWaves - 1) / kWaves * B;
+    int bid = (int)blockIdx.x;
+    if (bid < nmov) {
+        fmove_body<false>(a, bid, tab, st_c, lint_lo, stage);
+    } else if ((bid -= nmov) < nswap) {
+        fswap_body(a, bid, tab, st_c, lint_lo, lint_hi, stbuf);
+    } else if ((bid -= nswap) < nrel) {
+        frel_body(a, bid, tab, st_c, stage);
+    } else if ((bid -= nrel) < nrow) {
+        row_body(a, bid, tab);
+    } else {
+        total_body(a, bid - nrow, reinterpret_cast<double *>(stbuf));
+    }
+}
+
+constexpr int kMoveGroups = 16;               // groups of a workgroup of k_smin and k_sselect
+constexpr int kMoveEach = kMoveGroups / kWaves;   // and of a wavefront
+
+// What a group's moves share: its slot and queue, whether it is running (it never
+// moves), and its removal.
+struct GroupHead {
+    double base, rd;
+    int32_t s, g, head, pad;
+};
+
+// The screened score F and its bound D of every move of workgroup `wg`'s groups,
+// to put(k, F, D) in every lane (k the move's number, by slot; F = +inf and D = 0
+// where k names no move; put is called in step, with on = false past the end of a
+// row).  The groups' heads, a chain of dependent reads, are read by a lane each; a
+// wavefront takes four groups' rows, whose reads are independent.  (A wavefront
+// that read each group's own head took 9 us for two plans of 8192 groups, this
+// 8.5.)
+template <class Put>
+__device__ inline void block_moves(const SearchArgs &a, int64_t b, int wg, const Put &put)
+{
+    __shared__ GroupHead heads[kMoveGroups];
+    const int G = a.G, I = a.I, W = a.W;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int i0 = wg * kMoveGroups;
+    if ((int)threadIdx.x < kMoveGroups && i0 + (int)threadIdx.x < G) {
+        const int i = i0 + (int)threadIdx.x;
+        GroupHead h;
+        h.base = a.R[b * G + i];
+        h.rd = a.RD[b * G + i];
+        h.s = clampi(a.inv[b * G + i], 0, G - 1);
+        h.g = (int)min(a.srec[b * G + h.s].q, (uint32_t)(I - 1));
+        h.head = h.s == a.qof[b * (I + 1) + h.g];
+        h.pad = 0;
+        heads[threadIdx.x] = h;
+    }
+    __syncthreads();
+    const double cur = a.cur[b];
+    const double *X = a.X + b * a.n_moves;
+    const double *Nq = a.Nq + b * I;
+    const int u0 = wave_id() * kMoveEach;
+    for (int d0 = 0; d0 < W; d0 += kWave) {
+        const bool row = d0 + lane < W;
+        double e[kMoveEach];
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const int i = i0 + u0 + u;
+            e[u] = row && i < G ? X[(int64_t)i * W + d0 + lane] : INFINITY;
+        }
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const GroupHead &h = heads[u0 + u];
+            const bool on = row && i0 + u0 + u < G;
+            const bool move = on && !h.head && e[u] < INFINITY;
+            const double nq = move ? Nq[h.g] : 0.0;
+            put(on, (int64_t)h.s * W + d0 + lane, move ? cur + e[u] : INFINITY,
+                !move ? 0.0 : (forced(e[u]) ? INFINITY : kEpsP * nq + 1e-12 * (fabs(cur) + nq)));
+        }
+    }
+    const double *M = X + (int64_t)G * W;
+    for (int h0 = 0; h0 < I; h0 += kWave) {
+        const int q = h0 + lane;
+        const double nh = q < I ? Nq[q] : 0.0;
+        const double dh = kEpsP * nh + 1e-12 * (fabs(cur) + nh);
+        double em[kMoveEach], er[kMoveEach];
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const int i = i0 + u0 + u;
+            const bool on = q < I && i < G;
+            em[u] = on ? M[(int64_t)i * I + q] : INFINITY;
+            er[u] = on ? M[(int64_t)G * I + (int64_t)i * I + q] : INFINITY;
+        }
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const GroupHead &h = heads[u0 + u];
+            const bool on = q < I && i0 + u0 + u < G;
+            const int64_t k = (int64_t)G * W + (int64_t)h.s * I + q;
+            const bool mm = on && !h.head && em[u] < INFINITY, mr = on && !h.head && er[u] < INFINITY;
+            put(on, k, mm ? cur + h.base + em[u] : INFINITY,
+                !mm ? 0.0 : (forced(em[u]) ? INFINITY : h.rd + dh));
+            // (a relocation within the queue removes nothing)
+            const bool own = q == h.g;
+            put(on, k + (int64_t)G * I, mr ? cur + (own ? 0.0 : h.base) + er[u] : INFINITY,
+                !mr ? 0.0 : (forced(er[u]) ? INFINITY : (own ? 0.0 : h.rd) + dh));
+        }
+    }
+}
+
+// The least F + D of each workgroup's groups (the chain's least bounds its lowest
+// exact score); the candidate list starts empty.
+__global__ __launch_bounds__(kThreads) void k_smin(SearchArgs a)
 {
     __shared__ double lmin[kWaves];
-    const int64_t b = blockIdx.x;
+    const int64_t b = blockIdx.x / a.nws;
+    const int wg = (int)(blockIdx.x % a.nws);
     if (a.done[b]) return;
     double m = INFINITY;
-    for (int w = threadIdx.x; w < a.nws; w += kThreads) m = fmin(m, a.smin[b * a.nws + w]);
+    block_moves(a, b, wg, [&](bool on, int64_t, double F, double D) { m = on ? fmin(m, F + D) : m; });
     m = block_min(m, lmin);
     if (threadIdx.x == 0) {
-        a.U[b] = m;
-        a.ncand[b] = 0;
+        a.smin[b * a.nws + wg] = m;
+        if (wg == 0) a.ncand[b] = 0;
     }
+}
+
+// The screened scores and bounds in the moves' own order (qlm_search_screen).
+__global__ __launch_bounds__(kThreads) void k_semit(SearchArgs a)
+{
+    const int64_t b = blockIdx.x / a.nws;
+    block_moves(a, b, (int)(blockIdx.x % a.nws), [&](bool on, int64_t k, double F, double D) {
+        if (on) {
+            a.F[b * a.n_moves + k] = F;
+            a.D[b * a.n_moves + k] = D;
+        }
+    });
 }
 
 // Candidates: moves whose exact score may be the lowest and below the plan's.
 __global__ __launch_bounds__(kThreads) void k_sselect(SearchArgs a)
 {
-    const int nblk = (int)((a.n_moves + kThreads - 1) / kThreads);
-    const int64_t b = blockIdx.x / nblk;
+    __shared__ double lmin[kWaves];
+    __shared__ double least;
+    const int64_t b = blockIdx.x / a.nws;
     if (a.done[b]) return;
-    const int64_t k = (int64_t)(blockIdx.x % nblk) * kThreads + threadIdx.x;
-    bool c = false;
-    if (k < a.n_moves) {
-        const double lo = a.F[b * a.n_moves + k] - a.D[b * a.n_moves + k];
-        c = lo <= a.U[b] && lo < a.cur[b];
-    }
-    const uint64_t mask = __ballot(c);
-    if (!mask) return;
+    double m = INFINITY;
+    for (int w = threadIdx.x; w < a.nws; w += kThreads) m = fmin(m, a.smin[b * a.nws + w]);
+    m = block_min(m, lmin);
+    if (threadIdx.x == 0) least = m;
+    __syncthreads();
+    const double U = least, cur = a.cur[b];
     const int lane = threadIdx.x & (kWave - 1);
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&a.ncand[b], __popcll(mask));
-    base = __shfl(base, 0, kWave);
-    if (c) {
-        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        a.cand[b * a.n_moves + base + below] = (int32_t)k;
-    }
+    block_moves(a, b, (int)(blockIdx.x % a.nws), [&](bool on, int64_t k, double F, double D) {
+        const bool c = on && F - D <= U && F - D < cur;
+        const uint64_t mask = __ballot(c);
+        if (!mask) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&a.ncand[b], __popcll(mask));
+        at = __shfl(at, 0, kWave);
+        if (c) {
+            const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            a.cand[b * a.n_moves + at + below] = (int32_t)k;
+        }
+    });
 }
 
 // Exact scores of the candidates, two wavefronts per candidate: a move into
@@ -1785,6 +2063,8 @@ __global__ __launch_bounds__(kThreads) void k_spick(SearchArgs a, int step)
     if (k < (int64_t)G * W) {
         if (threadIdx.x == 0) {
             const int s = (int)(k / W), t = s + (int)(k % W) + 1;
+            a.dq[b * 4] = a.dq[b * 4 + 1] = (int32_t)a.srec[b * G + s].q;
+            a.dq[b * 4 + 2] = -1;
             const int32_t pi = perm[s];
             const uint8_t fi = flag[s];
             perm[s] = perm[t];
@@ -1795,6 +2075,15 @@ __global__ __launch_bounds__(kThreads) void k_spick(SearchArgs a, int step)
         return;
     }
     const int64_t r = k - (int64_t)G * W;
+    if (threadIdx.x == 0) {
+        const bool relocate = r >= (int64_t)G * I;
+        const int64_t sh = relocate ? r - (int64_t)G * I : r;
+        const int s = (int)(sh / I);
+        a.dq[b * 4] = (int32_t)a.srec[b * G + s].q;
+        a.dq[b * 4 + 1] = (int32_t)(sh % I);
+        a.dq[b * 4 + 2] = relocate && !(a.srec[b * G + s].nmf & kFlagBit) ? perm[s] : -1;
+    }
+    __syncthreads();
     if (r < (int64_t)G * I) {
         place_apply(a, b, (int)(r / I), (int)(r % I));
     } else {
@@ -2418,7 +2707,7 @@ struct Layout {
     int nwg_a, nwg_b, nwg, nwg_f, nwg_r, nws;
     int64_t n_moves;
     size_t grec, by_slo, rank_part, perm, flag, qof, inv, srec, sst, trec, R, RD, Q, Nq, Es, T, cur, done, steps,
-        wmin_s, wmin_i, smin, F, D, cand, cex, ncand, U, scratch, dq, total;
+        wmin_s, wmin_i, smin, X, cand, cex, ncand, U, scratch, dq, total;
 };
 
 Layout layout(int G, int I, int W, int64_t B)
@@ -2429,7 +2718,7 @@ Layout layout(int G, int I, int W, int64_t B)
     L.nwg = L.nwg_a + 2 * I * L.nwg_b;
     L.nwg_f = (int)(((int64_t)G * (W + 1) + kThreads - 1) / kThreads);
     L.nwg_r = (G + kThreads - 1) / kThreads;
-    L.nws = L.nwg_f + I * L.nwg_b + L.nwg_r;
+    L.nws = (G + kMoveGroups - 1) / kMoveGroups;
     L.n_moves = (int64_t)G * W + 2 * (int64_t)G * I;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -2461,8 +2750,7 @@ Layout layout(int G, int I, int W, int64_t B)
     L.wmin_s = take(8 * (size_t)L.nwg * b);
     L.wmin_i = take(8 * (size_t)L.nwg * b);
     L.smin = take(8 * (size_t)L.nws * b);
-    L.F = take(8 * nm * b);
-    L.D = take(8 * nm * b);
+    L.X = take(8 * nm * b);
     L.cand = take(4 * nm * b);
     L.cex = take(8 * nm * b);
     L.ncand = take(4 * b);
@@ -2484,6 +2772,7 @@ int check_search(const qlm_problem *pr, int64_t B, int32_t W)
     if (B < 0) return fail(QLM_ERR_ARG, "search: n_plans must be >= 0");
     const Layout L = layout(pr->n_groups, pr->n_instances, W, 1);
     const int64_t Bc = B > 0 ? B : 1;
+    // (nwg bounds the screens' grids: removals and swaps, both kinds into every queue)
     const int64_t sel = (L.n_moves + kThreads - 1) / kThreads;
     if ((int64_t)L.nwg * Bc > INT_MAX || sel * Bc > INT_MAX || (int64_t)L.nws * Bc > INT_MAX ||
         (int64_t)kExactBlocks * Bc > INT_MAX ||
@@ -2536,8 +2825,7 @@ SearchArgs search_args(const qlm_problem *pr, int64_t B, int32_t W, unsigned cha
     a.wmin_s = (double *)(ws + L.wmin_s);
     a.wmin_i = (int64_t *)(ws + L.wmin_i);
     a.smin = (double *)(ws + L.smin);
-    a.F = (double *)(ws + L.F);
-    a.D = (double *)(ws + L.D);
+    a.X = (double *)(ws + L.X);
     a.cand = (int32_t *)(ws + L.cand);
     a.cex = (double *)(ws + L.cex);
     a.ncand = (int32_t *)(ws + L.ncand);
@@ -2592,11 +2880,16 @@ int search_begin(const qlm_problem *pr, const qlm_plans *pl, int32_t W, void *ws
     }
 }
 
-int launch_state(SearchArgs &a, int force, hipStream_t stream)
+int launch_sstate(SearchArgs &a, int force, hipStream_t stream)
 {
     const int nblk = (a.I + kWaves - 1) / kWaves;
     hipLaunchKernelGGL(k_sstate, dim3((unsigned)(nblk * a.B)), dim3(kThreads), 0, stream, a, force);
-    int rc = launched("k_sstate launch");
+    return launched("k_sstate launch");
+}
+
+int launch_state(SearchArgs &a, int force, hipStream_t stream)
+{
+    int rc = launch_sstate(a, force, stream);
     if (rc) return rc;
     hipLaunchKernelGGL(k_stotal, dim3((unsigned)a.B), dim3(kThreads), 0, stream, a, force);
     return launched("k_stotal launch");
@@ -2629,16 +2922,32 @@ int exact_moves(SearchArgs &a, hipStream_t stream)
 }
 
 // The screens of every move (removals and swaps, then reassignments, then
-// relocations into other queues and within a queue).
-int screen_moves(SearchArgs &a, hipStream_t stream)
+// relocations into other queues and within a queue), or, `changed`, of the moves
+// of the two queues that the last step changed: the workgroups for each of them
+// are those of a queue of twice the mean length, and loop over a longer one.
+int screen_moves(SearchArgs &a, bool changed, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_fswap, dim3((unsigned)(a.nwg_f * a.B)), dim3(kThreads), 0, stream, a);
-    int rc = launched("k_fswap launch");
-    if (rc) return rc;
-    const dim3 mgrid((unsigned)(((int64_t)a.I * a.nwg_b + a.nwg_r) * a.B));
+    const int64_t mean2 = 2 * ((int64_t)a.G + a.I - 1) / a.I;
+    const int64_t wf = (mean2 * (a.W + 1) + kThreads - 1) / kThreads;
+    const int64_t wr = (mean2 + kThreads - 1) / kThreads;
+    a.inc_f = changed ? (int)(wf < a.nwg_f ? wf : a.nwg_f) : 0;
+    a.inc_r = changed ? (int)(wr < a.nwg_r ? wr : a.nwg_r) : 0;
+    int rc;
     qlm_internal::TimedLaunch tl;
+    if (changed) {
+        const int64_t grid = 4 * (int64_t)a.nwg_b + 2 * (int64_t)(a.inc_f + a.inc_r) +
+                             (a.I + kWaves - 1) / kWaves + 1;
+        if ((rc = qlm_internal::timing_begin(stream, &tl))) return rc;
+        hipLaunchKernelGGL(k_finc, dim3((unsigned)(grid * a.B)), dim3(kThreads), 0, stream, a);
+        if ((rc = launched("k_finc launch"))) return rc;
+        qlm_internal::timing_end(stream, &tl);
+        return QLM_OK;
+    }
+    hipLaunchKernelGGL(k_fswap, dim3((unsigned)(a.nwg_f * a.B)), dim3(kThreads), 0, stream, a);
+    if ((rc = launched("k_fswap launch"))) return rc;
+    const int64_t mgrid = (int64_t)a.I * a.nwg_b + a.nwg_r;
     if ((rc = qlm_internal::timing_begin(stream, &tl))) return rc;
-    hipLaunchKernelGGL(k_fmove, mgrid, dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_fmove, dim3((unsigned)(mgrid * a.B)), dim3(kThreads), 0, stream, a);
     if ((rc = launched("k_fmove launch"))) return rc;
     qlm_internal::timing_end(stream, &tl);
     return QLM_OK;
@@ -2690,11 +2999,11 @@ int session_args(const qlm_problem *pr, int64_t B, void *ws, size_t ws_bytes, Se
 // One search step after the screens: candidates, their exact scores, the pick.
 int pick_step(SearchArgs &a, int step, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_sbound, dim3((unsigned)a.B), dim3(kThreads), 0, stream, a);
-    int rc = launched("k_sbound launch");
+    const dim3 grid((unsigned)(a.nws * a.B));
+    hipLaunchKernelGGL(k_smin, grid, dim3(kThreads), 0, stream, a);
+    int rc = launched("k_smin launch");
     if (rc) return rc;
-    const int64_t sel = (a.n_moves + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(k_sselect, dim3((unsigned)(sel * a.B)), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_sselect, grid, dim3(kThreads), 0, stream, a);
     if ((rc = launched("k_sselect launch"))) return rc;
     hipLaunchKernelGGL(k_sexact, dim3((unsigned)(kExactBlocks * a.B)), dim3(kThreads), 0, stream, a);
     if ((rc = launched("k_sexact launch"))) return rc;
@@ -2905,7 +3214,9 @@ int qlm_search_screen(const qlm_problem *problem, const qlm_plans *plans, int32_
     if (rc) return rc;
     a.F = score;
     a.D = bound;
-    return screen_moves(a, stream);
+    if ((rc = screen_moves(a, false, stream))) return rc;
+    hipLaunchKernelGGL(k_semit, dim3((unsigned)(a.nws * a.B)), dim3(kThreads), 0, stream, a);
+    return launched("k_semit launch");
 }
 
 int qlm_local_search(const qlm_problem *problem, const qlm_plans *start, const qlm_plans_out *out,
@@ -2931,11 +3242,12 @@ int qlm_local_search(const qlm_problem *problem, const qlm_plans *start, const q
     rc = load_and_state(a, start, stream);
     if (rc) return rc;
     for (int t = 0; t < max_steps; ++t) {
-        if (t > 0 && (rc = launch_state(a, 0, stream))) return rc;
-        if ((rc = screen_moves(a, stream))) return rc;
+        // after the first step only the entries of the two queues it changed are
+        // screened again (the plan's score is the exact one that the step chose)
+        if (t > 0 && (rc = launch_sstate(a, 0, stream))) return rc;
+        if ((rc = screen_moves(a, t > 0, stream))) return rc;
         if ((rc = pick_step(a, t, stream))) return rc;
     }
-    if (max_steps > 0 && (rc = launch_state(a, 1, stream))) return rc;
     const qlm_plans_out o = *out;
     const int64_t rows = (int64_t)a.G + a.I + 1 + (o.evict_bits ? (a.G + 31) / 32 : 0) + 1;
     int64_t grid = (rows * a.B + kThreads - 1) / kThreads;

@@ -181,3 +181,42 @@ def test_validate_tiles(qlm, G, I, P, ld):
     torch.cuda.synchronize()
     assert np.array_equal(status.cpu().numpy(), want)
     assert int(n.item()) == int((want != 0).sum())
+
+
+# Search: after the first step only the two changed queues are screened.  Every
+# step equals a search of one step (which screens everything) from the plan it
+# left: relocations that set flags, emptied and skewed queues (workgroups that loop),
+# more queues and wider windows than a wavefront, one queue, no window
+@pytest.mark.parametrize("G,I,W,steps,kind", [
+    (1, 1, 2, 2, "plain"), (30, 3, 4, 14, "evict"), (64, 9, 0, 10, "empty"), (90, 1, 70, 6, "plain"),
+    (200, 70, 3, 8, "evict"), (300, 4, 8, 12, "skewed"), (500, 12, 16, 8, "evict")])
+def test_search_incremental(qlm, G, I, W, steps, kind):
+    import torch
+    P = 3
+    pr, pl = make(G, I, P, 500 + G, evict=kind != "plain")
+    rng = np.random.default_rng(G)
+    pr["evict_cost"] = 0.5
+    pr["grp_slo"] = rng.choice([5.0, 20.0, 60.0, 400.0], G).astype(np.float32)
+    if kind in ("empty", "skewed"):
+        for p in range(P):
+            cuts = np.sort(rng.integers(0, G + 1, I - 1)) if kind == "empty" else \
+                np.minimum(G, np.arange(1, I) * 2)
+            pl["qoff"][1:I, p] = cuts
+    dpr, dpl = device_inputs(pr, pl)
+    print("case search", G, I, W, kind, flush=True)
+    whole = qlm.local_search(dpr, dpl, W, steps, trace=True)
+    torch.cuda.synchronize()
+    cur, trace = dpl, []
+    for _ in range(steps):
+        one = qlm.local_search(dpr, cur, W, 1, trace=True)
+        torch.cuda.synchronize()
+        cur = one["plans"]
+        trace.append(one["trace"][:, 0].cpu().numpy())
+    assert np.array_equal(whole["trace"].cpu().numpy(), np.stack(trace, 1))
+    for name in ("perm", "qoff", "evict_bits"):
+        assert torch.equal(getattr(whole["plans"], name), getattr(cur, name)), name
+    assert torch.equal(whole["score"], one["score"])
+    exact = qlm.rwt_score_exact(dpr, cur, np.arange(P))
+    assert torch.equal(exact, whole["score"])
+    if kind == "evict":
+        assert int((whole["trace"] >= G * (W + I)).sum()) > 0       # a relocation among them
