@@ -383,9 +383,16 @@ __global__ __launch_bounds__(1024) void k_score_form(ScoreArgs a, int32_t *form)
 // the indicator is the one the definition gives; where the scaled variance is
 // too small for single precision, P is the double-precision erfc; elsewhere
 // it comes from the tail table as in the fast path.
+// Slots [s_begin, s_end) of the plan (a part's, as in k_score): a part that does
+// not start with the plan first adds up its first queue's slots before it, in the
+// same order.  Group ids are read 8 slots ahead, and a queue's end with the next
+// three queues' in one go, so that most heads (some lane has one in 4 of 10 slots
+// with 16 queues of 64 groups) wait for no read.  1024 groups, 32768 plans: a call of
+// 123 us; with one wavefront a plan, each head waiting, 472.
 template <bool EVICT, bool PEN, bool DETAIL>
 __device__ void walk_general(const ScoreArgs &a, const Lds &L, uint32_t tail0, int64_t tb, int lp,
-                             bool det, int64_t dq, double &S_out, double &PE_out)
+                             bool det, int64_t dq, int s_begin, int s_end, double &S_out,
+                             double &PE_out)
 {
     const int G = a.G;
     const int I1 = a.I - 1;
@@ -401,33 +408,96 @@ __device__ void walk_general(const ScoreArgs &a, const Lds &L, uint32_t tail0, i
     double A = 0.0, K = 0.0, V = 0.0, S = 0.0, PE = 0.0;
     double theta = 1.0, inv_theta = 1.0;
     uint32_t cbase = 0u, rowb = 0u;   // class row base; cost row of the slot before
-    int g = -1, nb = 0;               // current queue, the slot where the next starts
-    for (int s0 = 0; s0 < G; s0 += 8) {
-        uint32_t id[8];
+    int g = -1, nb = s_begin;         // current queue, the slot where the next starts
+    constexpr int kHeld = 3;
+    int held[kHeld] = {-1, -1, -1};   // ends of the queues after it (-1: not read)
+    // the queue that holds slot s, from queue h on: its end and those of the next
+    auto open = [&](int h, int s) __attribute__((always_inline)) {
+        int e;
+        do {
+            e = h >= I1 ? INT_MAX : (int)at(a.qoff, h + 1);
+            if (e > s || h >= I1) break;
+            ++h;
+        } while (true);
+        g = h;
+        nb = e;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) id[k] = at(a.perm, min(s0 + k, G - 1));
-        const uint32_t evw = EVICT ? at(a.evict, s0 >> 5) : 0u;
+        for (int j = 0; j < kHeld; ++j) held[j] = h + 1 + j < I1 ? (int)at(a.qoff, h + 2 + j) : -1;
+    };
+    auto set_queue = [&]() __attribute__((always_inline)) {
+        const uint4 ir = *lds_ptr<const uint4>(L.inst + 16u * (uint32_t)g);
+        theta = __longlong_as_double((long long)(((uint64_t)ir.y << 32) | ir.x));
+        inv_theta = 1.0 / theta;
+        cbase = ir.z;
+        rowb = ir.w;
+        A = 0.0;
+        K = 0.0;
+        V = 0.0;
+    };
+    if (s_begin > 0) {
+        // the last queue that starts at or before s_begin, and its slots so far
+        int lo = 0, hi = I1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if ((int)at(a.qoff, mid) <= s_begin)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        open(lo, s_begin);
+        set_queue();
+        const int qs = clampi((int)at(a.qoff, g), 0, s_begin);
+        int first = qs;
+        for (int o = 32; o > 0; o >>= 1) first = min(first, __shfl_xor(first, o, kWave));
+        for (int s0 = first & ~7; s0 < s_begin; s0 += 8) {
+            uint32_t id[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) id[k] = at(a.perm, min(s0 + k, G - 1));
+            const uint32_t evw = EVICT ? at(a.evict, s0 >> 5) : 0u;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int s = s0 + k;
+                if (s >= qs && s < s_begin) {
+                    const uint4 r = *lds_ptr<const uint4>((min(id[k], (uint32_t)G) << 4) + L.grp);
+                    const double n = (double)(r.w >> kGenCountShift);
+                    const uint32_t m = r.w & 255u;
+                    K = K + *lds_ptr<const double>(rowb + (m << 3));
+                    if (EVICT && ((evw >> (s & 31)) & 1u)) K = K + ecost;
+                    A = A + n * (double)__uint_as_float(r.x);
+                    V = V + n * (double)__uint_as_float(r.y);
+                    rowb = cbase + m * row_bytes;
+                }
+            }
+        }
+    }
+    uint32_t nid[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) nid[k] = at(a.perm, min(s_begin + k, G - 1));
+    uint32_t nevw = EVICT ? at(a.evict, s_begin >> 5) : 0u;
+    for (int s0 = s_begin; s0 < s_end; s0 += 8) {       // (s_begin is a multiple of 32)
+        uint32_t id[8];
+        const uint32_t evw = nevw;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) id[k] = nid[k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) nid[k] = at(a.perm, min(s0 + 8 + k, G - 1));
+        if (EVICT) nevw = at(a.evict, min(s0 + 8, G - 1) >> 5);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int s = s0 + k;
-            if (s >= G) break;
+            if (s >= s_end) break;
             if (s == nb) {
-                // the queue holding slot s: the next one not empty
-                int h = g, e_nb;
-                do {
-                    ++h;
-                    e_nb = h >= I1 ? INT_MAX : (int)at(a.qoff, h + 1);
-                } while (e_nb <= s && h < I1);
-                g = h;
-                nb = e_nb;
-                const uint4 ir = *lds_ptr<const uint4>(L.inst + 16u * (uint32_t)g);
-                theta = __longlong_as_double((long long)(((uint64_t)ir.y << 32) | ir.x));
-                inv_theta = 1.0 / theta;
-                cbase = ir.z;
-                rowb = ir.w;
-                A = 0.0;
-                K = 0.0;
-                V = 0.0;
+                if (g + 1 >= I1 || held[0] > s) {
+                    // the next queue, its end held (the last queue's is no slot)
+                    g += 1;
+                    nb = g >= I1 ? INT_MAX : held[0];
+#pragma unroll
+                    for (int j = 0; j + 1 < kHeld; ++j) held[j] = held[j + 1];
+                    held[kHeld - 1] = -1;
+                } else {
+                    open(g + 1, s);
+                }
+                set_queue();
             }
             const uint4 r = *lds_ptr<const uint4>((min(id[k], (uint32_t)G) << 4) + L.grp);
             const double mu = (double)__uint_as_float(r.x);
@@ -482,6 +552,28 @@ __device__ inline double add_parts(const double *psum, int np)
     double t = psum[(np - 1) * kWave];
     for (int k = np - 2; k >= 0; --k) t = psum[k * kWave] + t;
     return t;
+}
+
+// The parts' sums S (and PE) meet in LDS, in the place of the tail table (every
+// walk of the workgroup done); the first part's wavefronts get the plans' sums.
+template <bool PEN>
+__device__ inline void join_parts(float2 *tail, int wave, int np, bool back, double &S, double &PE)
+{
+    static_assert(sizeof(float2) * kTailCells == sizeof(double) * kScoreThreads,
+                  "a partial sum per thread");
+    // (the lane found anew: nothing of the thread index lives through the walk)
+    const int me = wave * kWave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    double *psum = reinterpret_cast<double *>(tail) + me;
+    __syncthreads();
+    *psum = S;
+    __syncthreads();
+    if (!back) S = add_parts(psum, np);
+    if (PEN) {
+        __syncthreads();
+        *psum = PE;
+        __syncthreads();
+        if (!back) PE = add_parts(psum, np);
+    }
 }
 
 // Screening score of every plan.  One lane = one plan; the slots of a plan are
@@ -573,21 +665,26 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
     const int s_begin = back ? part_begin(a.part_first, a.part_step, part) : 0;
     const int s_end = part < np - 1 ? part_begin(a.part_first, a.part_step, part + 1) : G;
     if (!compact) {
-      // General records: the front wavefront of each tile walks the whole plan
-      // exactly (walk_general); the back one, if any, idles.
+      // General records: every part of a tile walks its slots exactly
+      // (walk_general).
       for (int r0 = (int)blockIdx.x * per_round; r0 < ntiles; r0 += (int)gridDim.x * per_round) {
         const int t = r0 + in_round;
-        if (back || t >= ntiles) continue;
-        const int tb = t * kWave;
-        const bool live = tb + lane < P;
-        const int lp = live ? lane : P - 1 - tb;
-        const int p = tb + lp;
-        const bool det = DETAIL && live && p >= a.d_begin && p < a.d_begin + a.d_count;
         double S = 0.0, PE = 0.0;
-        walk_general<EVICT, PEN, DETAIL>(a, L, tail0, tb, lp, det, p - a.d_begin, S, PE);
-        if (live) {
-          a.score[p] = S;
-          if (PEN) a.penalty[p] = PE;
+        int p_out = -1;
+        if (t < ntiles) {
+          const int tb = t * kWave;
+          const bool live = tb + lane < P;
+          const int lp = live ? lane : P - 1 - tb;
+          const int p = tb + lp;
+          const bool det = DETAIL && live && p >= a.d_begin && p < a.d_begin + a.d_count;
+          walk_general<EVICT, PEN, DETAIL>(a, L, tail0, tb, lp, det, p - a.d_begin, s_begin, s_end,
+                                           S, PE);
+          if (live) p_out = p;
+        }
+        if (np > 1) join_parts<PEN>(s_tail, wave, np, back, S, PE);
+        if (!back && p_out >= 0) {
+          a.score[p_out] = S;
+          if (PEN) a.penalty[p_out] = PE;
           lane_min = fmin(lane_min, S);
         }
       }
@@ -1089,20 +1186,7 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
       // (read anew, not held in a register through the walk)
       const int parts = __builtin_amdgcn_readfirstlane(s_parts);
       if (parts > 1) {
-          static_assert(sizeof(s_tail) == sizeof(double) * kScoreThreads, "a partial sum per thread");
-          // (the lane found anew: nothing of the thread index lives through the walk)
-          const int me = wave * kWave + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-          double *psum = reinterpret_cast<double *>(s_tail) + me;
-          __syncthreads();                          // every walk is done with the table
-          *psum = S_out;
-          __syncthreads();
-          if (!back) S_out = add_parts(psum, parts);
-          if (PEN) {
-              __syncthreads();
-              *psum = PE_out;
-              __syncthreads();
-              if (!back) PE_out = add_parts(psum, parts);
-          }
+          join_parts<PEN>(s_tail, wave, parts, back, S_out, PE_out);
       }
       if (!back && p_out >= 0) {
           a.score[p_out] = S_out;

@@ -220,3 +220,50 @@ def test_search_incremental(qlm, G, I, W, steps, kind):
     assert torch.equal(exact, whole["score"])
     if kind == "evict":
         assert int((whole["trace"] >= G * (W + I)).sum()) > 0       # a relocation among them
+
+
+# The general walk in parts: groups without requests or variance, counts and
+# models beyond the compact records; penalties and detail across the parts
+@pytest.mark.parametrize("G,I,P,kind", [
+    (31, 3, 65, "zero"), (128, 4, 5000, "zero"), (1000, 16, 300, "zero"), (1024, 1, 70, "zero"),
+    (2051, 5, 333, "counts"), (600, 1, 130, "models"), (512, 16, 20000, "zero"),
+    (700, 64, 200, "same")])
+def test_general_parts(qlm, orc, G, I, P, kind):
+    import torch
+    many = kind == "models"                  # (their costs leave LDS for one class)
+    pr, pl = make(G, I, P, 700 + G, M=66 if many else 4, evict=not many)
+    rng = np.random.default_rng(G)
+    if kind == "zero":
+        pr["grp_count"][rng.random(G) < 0.1] = 0
+        pr["grp_var"][rng.random(G) < 0.3] = 0.0
+    if kind == "counts":
+        pr["grp_count"][0] = 5000
+    if kind == "same":                       # whole-second waits that meet SLOs exactly
+        pr["grp_var"][:] = 0.0
+        pr["grp_count"][:] = 8
+        pr["grp_mu"][:] = 750.0
+        pr["inst_tput"][:] = 6000.0
+        pr["swap_cost"][:] = 4.0
+        pr["grp_slo"] = rng.integers(0, 60, G).astype(np.float32)
+    dpr, dpl = device_inputs(pr, pl)
+    print("case general", G, I, P, kind, flush=True)
+    assert qlm.score_form(dpr, not many) == 0
+    d = min(P, 66)
+    res = qlm.rwt_score(dpr, dpl, penalty=True, detail=(P - d, d))
+    bi, bs = qlm.best_plan(dpr, dpl)
+    torch.cuda.synchronize()
+    osc, ope = orc.score_plans(pr, pl)
+    err = np.abs(res["score"].cpu().numpy() - osc)
+    assert np.all(err <= SCORE_REL * dpr.total_requests), err.max()
+    mag = (ope + pr["grp_slo"].astype(np.float64).sum()) + np.abs(pr["grp_slo"]).sum()
+    perr = np.abs(res["penalty"].cpu().numpy() - ope)
+    assert np.all(perr <= 2.0 * (2 * G + 4) * 2.0 ** -53 * mag + 1e-300), perr.max()
+    from gpu_util import assert_close_detail
+    out = [res[k].cpu().numpy() for k in ("wait_mean", "wait_sd", "prob")]
+    for q in (0, d // 2, d - 1):
+        ref = orc.plan_detail(pr, pl, P - d + q)
+        assert_close_detail([x[:, q] for x in out], ref, G, (G, I, q))
+        zero = ref["wait_sd"] == 0
+        assert np.array_equal(out[2][zero, q], ref["prob"][zero])
+    _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
+    assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
