@@ -2149,20 +2149,18 @@ __global__ __launch_bounds__(kThreads) void k_place_eval(SearchArgs a, int group
     const uint8_t *__restrict__ flag = a.flag + b * G;
     const int32_t *__restrict__ qof = a.qof + b * (I + 1);
     const int lane = threadIdx.x & (kWave - 1);
+    int q64 = lane < I ? qof[lane] : INT_MAX;          // (read beside the group's slot)
     const int s = __builtin_amdgcn_readfirstlane(clampi(a.inv[b * G + group], 0, G - 1));
-    // the group's queue: the last g with qof[g] <= s
-    int g = 0;
-    {
-        int lo = 0, hi = I - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (qof[mid] <= s)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        g = __builtin_amdgcn_readfirstlane(lo);
+    // the group's queue: the last g with qof[g] <= s, counted 64 queues at a time
+    // (a binary search is six reads, one after another)
+    int before = 0;
+    for (int q0 = 0;;) {
+        before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q64 <= s));
+        q0 += kWave;
+        if (q0 >= I) break;
+        q64 = q0 + lane < I ? qof[q0 + lane] : INT_MAX;
     }
+    const int g = clampi(before - 1, 0, I - 1);
     const int bg = clampi(qof[g], 0, G);
     const bool lead = lane == 0;
     if (w == I && lead) {
@@ -2247,8 +2245,7 @@ __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *
     __shared__ int64_t lk[kWaves];
     __shared__ int64_t kk;
     __shared__ int kp, kg, stay;
-    // the queue scores and their running sums, staged for the totals
-    __shared__ double sT[kMaxSearchInstances + 1], sQ[kMaxSearchInstances];
+    __shared__ double sQ[kMaxSearchInstances];         // the queue scores
     __shared__ int scand[kThreads];
     __shared__ double scex[kThreads];
     const int64_t b = blockIdx.x;
@@ -2272,38 +2269,26 @@ __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *
         stay = a.dq[b * 4 + 2];
     }
     __syncthreads();
-    // the running sums of the queue scores, in queue order (the additions of a
-    // serial sum, rippled across the first wavefront's lanes)
-    if (threadIdx.x < kWave) {
-        const int lane = threadIdx.x;
-        double carry = 0.0;
-        if (lane == 0) sT[0] = 0.0;
-        for (int q0 = 0; q0 < I; q0 += kWave) {
-            const int cnt = min(kWave, I - q0);
-            const double x = lane < cnt ? sQ[q0 + lane] : 0.0;
-            const double lx = from_left0(x);
-            double t = carry;
-            const int steps = __builtin_amdgcn_readfirstlane(cnt - 1);
-            for (int j = 0; j < steps; j += 8) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) t = from_left(t) + lx;
-            }
-            const double t1 = t + x;
-            if (lane < cnt) sT[q0 + lane + 1] = t1;
-            carry = lane_value(t1, cnt - 1);
+    // the queue scores added in queue order, with those of queues g and h replaced
+    // (every lane reads the same score at a time, several ahead)
+    auto total2 = [&](int g, double qg, int h, double qh) __attribute__((always_inline)) {
+        double t = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < I; ++q) {
+            const double v = sQ[q];
+            t += q == g ? qg : (q == h ? qh : v);
         }
-    }
-    __syncthreads();
+        return t;
+    };
     if (stay) {
         if (threadIdx.x == 0) {
-            a.cur[b] = sT[I];
+            const double cur = total2(-1, 0.0, -1, 0.0);
+            a.cur[b] = cur;
             if (queue) queue[b] = g0;
-            if (score) score[b] = sT[I];
+            if (score) score[b] = cur;
         }
         return;
     }
-    const double *T = sT;
-    const double *Q = sQ;
     const double rg = a.U[b];
     double best = INFINITY;
     int64_t bk = INT64_MAX;
@@ -2311,7 +2296,7 @@ __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *
     // group's own queue without it, the other queues as they stand
     auto total = [&](int c, double v) __attribute__((always_inline)) {
         const int h = c < I ? c : c - I;
-        return h != g0 ? total_with2(T, Q, I, g0, rg, h, v) : total_with(T, Q, I, g0, v);
+        return total2(g0, h != g0 ? rg : v, h != g0 ? h : -1, v);
     };
     for (int c = threadIdx.x; c < n; c += kThreads) {
         const double v = total(c, one ? v1 : a.cex[b * a.n_moves + c]);
