@@ -22,8 +22,8 @@
 //   k_gexact  exact double-precision re-score of the candidates (same
 //             definition as the oracle, summed per queue then over queues): one
 //             wavefront per (candidate, queue), the running sums rippling from
-//             lane to lane in position order
-//   k_gpick   lowest exact score, lowest index on ties.
+//             lane to lane in position order; then the lowest exact score, the
+//             lowest index on ties
 //   k_exact   exact re-score of a list of plans (qlm_rwt_score_exact), one
 //             workgroup per plan, its wavefronts over the plan's queues.
 //   k_validate_plans / k_validate_problem   structural checks.
@@ -122,7 +122,8 @@ struct ScoreArgs {
     float *d_mean, *d_sd, *d_prob;
     double *wg_min;           // best_plan: per-workgroup minimum score, or null
     double *wg_nsum;          // best_plan: total requests (written by block 0)
-    int32_t *ncand;           // best_plan: candidate count, zeroed by block 0
+    int32_t *ncand;           // best_plan: candidate count and k_gexact's count of
+                              // finished tasks, zeroed by block 0
 };
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
     if (!compact) stage_general(a, L);
     double *red = lds_ptr<double>(L.red);
     if (a.wg_nsum && blockIdx.x == 0) {
-        if (threadIdx.x == 0 && a.ncand) *a.ncand = 0;
+        if (threadIdx.x == 0 && a.ncand) a.ncand[0] = a.ncand[1] = 0;
         double t = 0.0;
         for (int i = threadIdx.x; i < a.G; i += blockDim.x)
             t += (double)(uint32_t)clampi(a.grp_count[i], 0, (int)kCountMask);
@@ -1418,22 +1419,28 @@ __device__ double block_min(double v, double *ls)
     return b;
 }
 
-// Candidate selection: every workgroup reduces the per-workgroup minima of the
-// screened scores, then appends the plans of its share whose screened score is
-// within twice the screening error bound of the minimum (the exact minimum is
-// always among them) to the candidate list, one atomic per wavefront.  The
-// scoring kernel zeroed the count.
-__global__ __launch_bounds__(kSelThreads) void k_gselect(const double *fast, const double *wg_min,
-                                                         int n_wg, const double *nsum, int64_t P,
-                                                         int64_t *cand, int32_t *ncand)
+// The screened score up to which a plan can be the best: twice the screening
+// bound above the lowest (of the per-workgroup minima).  In every thread.
+__device__ double select_limit(const double *wg_min, int n_wg, const double *nsum, double *ls)
 {
-    __shared__ double ls[kSelThreads / kWave];
     double m = INFINITY;
     for (int k = threadIdx.x; k < n_wg; k += blockDim.x) m = fmin(m, wg_min[k]);
     m = block_min(m, ls);
     // |screened - exact| <= eps * (total requests), plus the rounding of both sums
     const double delta = kEpsP * (*nsum) * (1.0 + 1e-9) + 1e-300;
-    const double thr = m + 2.0 * delta;
+    return m + 2.0 * delta;
+}
+
+// Candidate selection: every workgroup appends the plans of its share whose
+// screened score is within twice the screening error bound of the minimum (the
+// exact minimum is always among them) to the candidate list, one atomic per
+// wavefront.  The scoring kernel zeroed the count.
+__global__ __launch_bounds__(kSelThreads) void k_gselect(const double *fast, const double *wg_min,
+                                                         int n_wg, const double *nsum, int64_t P,
+                                                         int64_t *cand, int32_t *ncand)
+{
+    __shared__ double ls[kSelThreads / kWave];
+    const double thr = select_limit(wg_min, n_wg, nsum, ls);
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t stride = (int64_t)gridDim.x * kSelThreads;
     for (int64_t base = (int64_t)blockIdx.x * kSelThreads + (threadIdx.x - lane); base < P;
@@ -1450,75 +1457,159 @@ __global__ __launch_bounds__(kSelThreads) void k_gselect(const double *fast, con
     }
 }
 
-// Exact scores of the candidates.  When the per-(candidate, queue) sums fit
-// (count <= cap), one wavefront per (candidate, queue) writes its queue's
-// score to Q; else every workgroup scores whole candidates and writes the
-// plan's score over its screened score in X.
-__global__ __launch_bounds__(kGexThreads) void k_gexact(ExactArgs a, const int64_t *cand,
-                                                        const int32_t *ncand, int64_t cap,
-                                                        double *Q, double *X)
+// A double written for other workgroups, and read from them, at device scope.
+__device__ inline void put_shared(double *p, double v)
 {
-    __shared__ double qpart[kExactPass];
-    const int64_t n = __builtin_amdgcn_readfirstlane(ncand[0]);
-    if (n <= cap) {
-        constexpr int nwv = kGexThreads / kWave;
-        const int64_t tasks = n * a.I;
-        for (int64_t t = (int64_t)blockIdx.x * nwv + wave_id(); t < tasks;
-             t += (int64_t)gridDim.x * nwv) {
-            const int64_t k = t / a.I;
-            const int g = (int)(t - k * a.I);
-            int64_t p = cand[k];
-            p = p < 0 ? 0 : (p >= a.P ? a.P - 1 : p);
-            const double sc = wave_queue_exact(a, p, g);
-            if ((threadIdx.x & (kWave - 1)) == 0) Q[k * a.I + g] = sc;
-        }
-    } else {
-        for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
-            int64_t p = cand[k];
-            p = p < 0 ? 0 : (p >= a.P ? a.P - 1 : p);
-            const double s = block_plan_exact(a, p, qpart);
-            if (threadIdx.x == 0) X[p] = s;
-        }
-    }
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double get_shared(const double *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The candidate with the lowest exact score, the lowest index on ties; a NaN
-// score never wins.  Plan scores are the queue sums added in queue order (or
-// the whole-plan scores of k_gexact's second form).  No candidates: index -1,
-// score +inf.
-__global__ __launch_bounds__(256) void k_gpick(const int64_t *cand, const int32_t *ncand,
-                                               int64_t cap, int I, const double *Q,
-                                               const double *X, int64_t *out_i, double *out_s)
+// score never wins.  Plan scores are the queue sums added in queue order (or the
+// whole-plan scores of k_gexact's second form).  No candidates: index -1, score
+// +inf.  One workgroup of kGexThreads: a wavefront per candidate (its lanes load the
+// queue sums: about 1.5 us, four at a time) while they are few against the queues,
+// else a lane per candidate (about 0.7 us a queue, 256 at a time).
+__device__ void pick_best(const int64_t *cand, int64_t n, bool sums, int I, const double *Q,
+                          const double *X, int64_t *out_i, double *out_s)
 {
-    __shared__ double ls[256 / kWave];
-    __shared__ int64_t li[256 / kWave];
-    const int64_t n = ncand ? (int64_t)ncand[0] : 0;
+    __shared__ double ls[kGexThreads / kWave];
+    __shared__ int64_t li[kGexThreads / kWave];
     double s = INFINITY;
     int64_t i = -1;
-    // one wavefront per candidate: the lanes load its queue sums, which are
-    // added in queue order
     const int lane = threadIdx.x & (kWave - 1);
-    const int nw = blockDim.x / kWave;
-    for (int64_t k = wave_id(); k < n; k += nw) {
-        const int64_t p = cand[k];
-        double t = 0.0;
-        if (n <= cap) {
+    auto take = [&](double t, int64_t p) {
+        const bool better = t == t && (i < 0 || t < s || (t == s && p < i));
+        s = better ? t : s;
+        i = better ? p : i;
+    };
+    if (!sums) {
+        for (int64_t k = threadIdx.x; k < n; k += kGexThreads) take(get_shared(X + cand[k]), cand[k]);
+    } else if (n <= 2 * (int64_t)I) {
+        for (int64_t k = wave_id(); k < n; k += kGexThreads / kWave) {
+            double t = 0.0;
             for (int g0 = 0; g0 < I; g0 += kWave) {
-                const double q = g0 + lane < I ? Q[k * I + g0 + lane] : 0.0;
+                const double q = g0 + lane < I ? get_shared(Q + k * I + g0 + lane) : 0.0;
                 const int c = min(kWave, I - g0);
                 for (int j = 0; j < c; ++j) t += lane_value(q, j);
             }
-        } else {
-            t = X[p];
+            if (lane == 0) take(t, cand[k]);
         }
-        const bool take = lane == 0 && t == t && (i < 0 || t < s || (t == s && p < i));
-        s = take ? t : s;
-        i = take ? p : i;
+    } else {
+        for (int64_t k = threadIdx.x; k < n; k += kGexThreads) {
+            double t = 0.0;
+            for (int g = 0; g < I; ++g) t += get_shared(Q + k * I + g);
+            take(t, cand[k]);
+        }
     }
     block_argmin(s, i, ls, li);
     if (threadIdx.x == 0) {
         *out_i = i;
         *out_s = i >= 0 ? s : INFINITY;
+    }
+}
+
+// Exact scores of the candidates, and the best of them.  When the
+// per-(candidate, queue) sums fit (count <= cap), one wavefront per (candidate,
+// queue) writes its queue's score to Q; else every workgroup scores whole
+// candidates and writes the plan's score over its screened score in X.  The
+// workgroup that finishes the last task picks (a launch of its own for that took
+// 4 to 6 us).  With few plans (kSmall) the candidates are not listed by a kernel
+// before: every workgroup selects them itself, four plans a thread; best_plan calls
+// end to end, listed before | selected here: 8 groups, 1 queue, 256 plans 16.8 |
+// 15.8 us and 1024 plans 17.7 | 16.2; 512 groups, 64 queues, 1024 plans 54.4 | 53.1.
+constexpr int kSmallPlans = 1024;
+
+template <bool kSmall>
+__global__ __launch_bounds__(kGexThreads) void k_gexact(ExactArgs a, const int64_t *cand,
+                                                        int32_t *ncand, int64_t cap, double *Q,
+                                                        double *X, const double *wg_min, int n_wg,
+                                                        const double *nsum, int64_t *out_i,
+                                                        double *out_s)
+{
+    __shared__ double qpart[kExactPass];
+    __shared__ int64_t s_cand[kSmall ? kSmallPlans : 1];
+    __shared__ int s_done;
+    constexpr int nwv = kGexThreads / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t n;
+    if (kSmall) {
+        __shared__ double ls[nwv];
+        constexpr int per = kSmallPlans / kGexThreads;
+        __shared__ int s_n[per * nwv];
+        double x[per];                         // (loaded with the minima)
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const int64_t p = threadIdx.x + j * kGexThreads;
+            x[j] = p < a.P ? X[p] : INFINITY;
+        }
+        const double thr = select_limit(wg_min, n_wg, nsum, ls);
+        // in plan order, alike in every workgroup
+        uint64_t in[per];
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            in[j] = __ballot(x[j] <= thr && threadIdx.x + j * kGexThreads < a.P);
+            if (lane == 0) s_n[j * nwv + wave_id()] = __popcll(in[j]);
+        }
+        __syncthreads();
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            for (int w = 0; w < nwv; ++w) {
+                if (w == wave_id() && (in[j] >> lane & 1))
+                    s_cand[c + __popcll(in[j] & ((1ull << lane) - 1ull))] =
+                        threadIdx.x + j * kGexThreads;
+                c += s_n[j * nwv + w];
+            }
+        }
+        __syncthreads();
+        n = __builtin_amdgcn_readfirstlane(c);
+        cand = s_cand;
+    } else {
+        n = __builtin_amdgcn_readfirstlane(ncand[0]);
+    }
+    const bool sums = n <= cap;
+    const int64_t tasks = sums ? n * a.I : n;
+    const int64_t groups = sums ? (tasks + nwv - 1) / nwv : tasks;    // of a workgroup's tasks
+    int mine = 0;                              // groups this workgroup took
+    for (int64_t t0 = blockIdx.x; t0 < groups; t0 += gridDim.x) {
+        ++mine;
+        if (sums) {
+            const int64_t t = t0 * nwv + wave_id();
+            if (t >= tasks) continue;
+            const int64_t k = t / a.I;
+            const int g = (int)(t - k * a.I);
+            int64_t p = cand[k];
+            p = p < 0 ? 0 : (p >= a.P ? a.P - 1 : p);
+            const double sc = wave_queue_exact(a, p, g);
+            if (lane == 0) put_shared(Q + t, sc);
+        } else {
+            int64_t p = cand[t0];
+            p = p < 0 ? 0 : (p >= a.P ? a.P - 1 : p);
+            const double sc = block_plan_exact(a, p, qpart);
+            if (threadIdx.x == 0) put_shared(X + p, sc);
+        }
+    }
+    if (mine == 0 && !(groups == 0 && blockIdx.x == 0)) return;
+    // every wavefront's scores written and released, then counted
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_done = mine + __hip_atomic_fetch_add(&ncand[1], mine, __ATOMIC_ACQ_REL,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_done == (int)groups) pick_best(cand, n, sums, a.I, Q, X, out_i, out_s);
+}
+
+// No plans: no best.
+__global__ void k_gnone(int64_t *out_i, double *out_s)
+{
+    if (threadIdx.x == 0) {
+        *out_i = -1;
+        *out_s = INFINITY;
     }
 }
 
@@ -2177,10 +2268,9 @@ int best_plan_impl(const qlm_problem *problem, const qlm_plans *plans, void *ws,
         return fail(QLM_ERR_WORKSPACE, "workspace too small");
     hipError_t e;
     if (P == 0) {
-        hipLaunchKernelGGL(k_gpick, dim3(1), dim3(256), 0, stream, nullptr, nullptr, (int64_t)0, I,
-                           nullptr, nullptr, best_index, best_score);
+        hipLaunchKernelGGL(k_gnone, dim3(1), dim3(kWave), 0, stream, best_index, best_score);
         e = hipGetLastError();
-        return e == hipSuccess ? QLM_OK : hip_fail(e, "k_gpick launch");
+        return e == hipSuccess ? QLM_OK : hip_fail(e, "k_gnone launch");
     }
     unsigned char *w = (unsigned char *)ws;
     double *fast = (double *)w;
@@ -2196,26 +2286,35 @@ int best_plan_impl(const qlm_problem *problem, const qlm_plans *plans, void *ws,
     // candidates whose per-queue sums fit in the rest of the workspace
     int64_t cap = (int64_t)((ws_bytes - fixed) / (8 * (size_t)I));
     if (cap > P) cap = P;
+    const int64_t most = ((int64_t)1 << 30) / I;    // (tasks are counted in 32 bits)
+    if (cap > most) cap = most;
     int grid = 0;
     rc = launch_score(problem, plans, fast, nullptr, nullptr, wg_min, nsum, ncand, &grid, stream,
                       timed);
     if (rc) return rc;
-    int sgrid = (int)((P + kSelThreads - 1) / kSelThreads);
-    if (sgrid > kSelBlocks) sgrid = kSelBlocks;
-    hipLaunchKernelGGL(k_gselect, dim3(sgrid), dim3(kSelThreads), 0, stream, fast, wg_min, grid,
-                       nsum, P, cand, ncand);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "k_gselect launch");
     ExactArgs a = exact_args(problem, plans);
-    hipLaunchKernelGGL(k_gexact, dim3(kGexBlocks), dim3(kGexThreads), 0, stream, a,
-                       (const int64_t *)cand, (const int32_t *)ncand, cap, Q, fast);
+    if (P <= kSmallPlans && cap >= P) {
+        // (no exact score goes to a screened one's place, which other workgroups
+        // may still select by.)  A wavefront per plan and queue as far as the grid
+        // goes: small plans tie often, and those without a task end at once.
+        int64_t blocks = (P * (int64_t)I + kGexThreads / kWave - 1) / (kGexThreads / kWave);
+        if (blocks > kGexBlocks) blocks = kGexBlocks;
+        hipLaunchKernelGGL(k_gexact<true>, dim3((unsigned)blocks), dim3(kGexThreads), 0, stream, a,
+                           (const int64_t *)nullptr, ncand, cap, Q, fast, (const double *)wg_min, grid,
+                           (const double *)nsum, best_index, best_score);
+    } else {
+        int sgrid = (int)((P + kSelThreads - 1) / kSelThreads);
+        if (sgrid > kSelBlocks) sgrid = kSelBlocks;
+        hipLaunchKernelGGL(k_gselect, dim3(sgrid), dim3(kSelThreads), 0, stream, fast, wg_min, grid,
+                           nsum, P, cand, ncand);
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(e, "k_gselect launch");
+        hipLaunchKernelGGL(k_gexact<false>, dim3(kGexBlocks), dim3(kGexThreads), 0, stream, a,
+                           (const int64_t *)cand, ncand, cap, Q, fast, (const double *)wg_min, grid,
+                           (const double *)nsum, best_index, best_score);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_gexact launch");
-    hipLaunchKernelGGL(k_gpick, dim3(1), dim3(256), 0, stream, (const int64_t *)cand,
-                       (const int32_t *)ncand, cap, I, (const double *)Q, (const double *)fast,
-                       best_index, best_score);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "k_gpick launch");
     return QLM_OK;
 }
 

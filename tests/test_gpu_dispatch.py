@@ -267,3 +267,31 @@ def test_general_parts(qlm, orc, G, I, P, kind):
         assert np.array_equal(out[2][zero, q], ref["prob"][zero])
     _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
     assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
+
+
+# The best plan's candidates: few and many, selected by the re-score itself (up to
+# 1024 plans) or listed before; every plan tied, one best, none (NaN scores); a
+# workspace whose queue sums hold fewer candidates than there are
+@pytest.mark.parametrize("G,I,P,kind", [
+    (8, 1, 1, "tie"), (8, 1, 256, "tie"), (40, 3, 1024, "tie"), (40, 3, 1025, "tie"),
+    (40, 3, 1024, "one"), (64, 64, 700, "one"), (64, 64, 1500, "tie"), (20, 2, 300, "nan"),
+    (20, 2, 2000, "nan")])
+def test_best_plan_candidates(qlm, orc, G, I, P, kind):
+    import torch
+    pr, pl = make(G, I, P, 40 + P + G)
+    if kind == "tie":
+        pr["grp_slo"][:] = 1e9               # no plan violates anything
+    if kind == "nan":
+        pr["grp_mu"][:] = np.nan
+    dpr, dpl = device_inputs(pr, pl)
+    print("case candidates", G, I, P, kind, flush=True)
+    for _ in range(3):                       # (the counts start anew in every call)
+        bi, bs = qlm.best_plan(dpr, dpl)
+        si, ss = qlm.best_plan_static(dpr, dpl)
+    torch.cuda.synchronize()
+    assert int(bi.item()) == int(si.item()) and (float(bs) == float(ss) or kind == "nan")
+    if kind == "nan":
+        return                               # (unspecified, and it returns)
+    osc, _ = orc.score_plans(pr, pl)
+    _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
+    assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
