@@ -216,18 +216,17 @@ def rwt_score(problem: DeviceProblem, plans: DevicePlans, penalty: bool = False,
     import torch
     dev = plans.perm.device
     P = plans.n_plans
-    # outputs start as NaN, so that an entry the library failed to write shows
-    score = out if out is not None else torch.full((P,), float("nan"), dtype=torch.float64,
-                                                   device=dev)
-    pen = torch.full((P,), float("nan"), dtype=torch.float64, device=dev) if penalty else None
+    # (the library writes every entry: a fill before would be a launch each)
+    score = out if out is not None else torch.empty((P,), dtype=torch.float64, device=dev)
+    pen = torch.empty((P,), dtype=torch.float64, device=dev) if penalty else None
     det = None
     res = {"score": score, "penalty": pen}
     if detail is not None:
         b, c = detail
         G = problem.n_groups
-        wm = torch.full((G, c), float("nan"), dtype=torch.float32, device=dev)
-        ws = torch.full((G, c), float("nan"), dtype=torch.float32, device=dev)
-        pr = torch.full((G, c), float("nan"), dtype=torch.float32, device=dev)
+        wm = torch.empty((G, c), dtype=torch.float32, device=dev)
+        ws = torch.empty((G, c), dtype=torch.float32, device=dev)
+        pr = torch.empty((G, c), dtype=torch.float32, device=dev)
         det = Detail(b, c, _ptr(wm), _ptr(ws), _ptr(pr))
         res.update(wait_mean=wm, wait_sd=ws, prob=pr)
     _check(library().qlm_rwt_score(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
@@ -240,7 +239,7 @@ def rwt_score(problem: DeviceProblem, plans: DevicePlans, penalty: bool = False,
 def rwt_score_exact(problem: DeviceProblem, plans: DevicePlans, plan_index, stream=None):
     import torch
     idx = torch.as_tensor(plan_index, dtype=torch.int64).to(plans.perm.device)
-    out = torch.full((idx.numel(),), float("nan"), dtype=torch.float64, device=plans.perm.device)
+    out = torch.empty((idx.numel(),), dtype=torch.float64, device=plans.perm.device)
     _check(library().qlm_rwt_score_exact(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                          _ptr(idx), idx.numel(), _ptr(out), _stream(stream)))
     return out
@@ -263,8 +262,8 @@ def best_plan(problem: DeviceProblem, plans: DevicePlans, ws=None, stream=None, 
     if ws is None:
         ws = workspace(problem, plans.n_plans, dev)
     if out is None:
-        bi = torch.full((1,), -2, dtype=torch.int64, device=dev)
-        bs = torch.full((1,), float("nan"), dtype=torch.float64, device=dev)
+        bi = torch.empty((1,), dtype=torch.int64, device=dev)
+        bs = torch.empty((1,), dtype=torch.float64, device=dev)
     else:
         bi, bs = out
     _check(library().qlm_best_plan(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
@@ -278,8 +277,8 @@ def best_plan_static(problem: DeviceProblem, plans: DevicePlans, stream=None, ou
     import torch
     dev = plans.perm.device
     if out is None:
-        bi = torch.full((1,), -2, dtype=torch.int64, device=dev)
-        bs = torch.full((1,), float("nan"), dtype=torch.float64, device=dev)
+        bi = torch.empty((1,), dtype=torch.int64, device=dev)
+        bs = torch.empty((1,), dtype=torch.float64, device=dev)
     else:
         bi, bs = out
     _check(library().qlm_best_plan_static(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
@@ -291,7 +290,7 @@ def score_form(problem: DeviceProblem, with_eviction: bool, stream=None) -> int:
     """1 when qlm_rwt_score / qlm_best_plan take their fast path for this
     problem, 0 when they take the general exact walk (synchronizes)."""
     import torch
-    f = torch.full((1,), -1, dtype=torch.int32, device=problem.grp_count.device)
+    f = torch.empty((1,), dtype=torch.int32, device=problem.grp_count.device)
     _check(library().qlm_score_form(ctypes.byref(problem.struct), int(bool(with_eviction)),
                                     _ptr(f), _stream(stream)))
     return int(f.item())
@@ -369,8 +368,7 @@ def search_moves(problem: DeviceProblem, plans: DevicePlans, window: int, ws=Non
     if ws is None:
         ws = search_workspace(problem, plans.n_plans, window, dev)
     if out is None:
-        # NaN until written: an entry the library leaves unwritten shows
-        out = torch.full((plans.n_plans, nm), float("nan"), dtype=torch.float64, device=dev)
+        out = torch.empty((plans.n_plans, nm), dtype=torch.float64, device=dev)
     _check(library().qlm_search_moves(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                       window, _ptr(ws), ws.numel(), _ptr(out), _stream(stream)))
     return out
@@ -385,8 +383,8 @@ def search_screen(problem: DeviceProblem, plans: DevicePlans, window: int, ws=No
     nm = search_n_moves(problem.n_groups, problem.n_instances, window)
     if ws is None:
         ws = search_workspace(problem, plans.n_plans, window, dev)
-    score = torch.full((plans.n_plans, nm), float("nan"), dtype=torch.float64, device=dev)
-    bound = torch.full((plans.n_plans, nm), float("nan"), dtype=torch.float64, device=dev)
+    score = torch.empty((plans.n_plans, nm), dtype=torch.float64, device=dev)
+    bound = torch.empty((plans.n_plans, nm), dtype=torch.float64, device=dev)
     _check(library().qlm_search_screen(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                        window, _ptr(ws), ws.numel(), _ptr(score), _ptr(bound),
                                        _stream(stream)))
@@ -406,10 +404,9 @@ def local_search(problem: DeviceProblem, plans: DevicePlans, window: int, max_st
     if out is None:
         out = plans_like(plans, problem.n_groups)
     o = PlansOut(int(out.perm.shape[1]), _ptr(out.perm), _ptr(out.qoff), _ptr(out.evict_bits))
-    # sentinels until written: NaN scores, -2 steps and moves
-    score = torch.full((P,), float("nan"), dtype=torch.float64, device=dev)
-    steps = torch.full((P,), -2, dtype=torch.int32, device=dev)
-    tr = torch.full((P, max(max_steps, 1)), -2, dtype=torch.int64, device=dev) if trace else None
+    score = torch.empty((P,), dtype=torch.float64, device=dev)
+    steps = torch.empty((P,), dtype=torch.int32, device=dev)
+    tr = torch.empty((P, max(max_steps, 1)), dtype=torch.int64, device=dev) if trace else None
     _check(library().qlm_local_search(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                       ctypes.byref(o), window, max_steps, _ptr(ws), ws.numel(),
                                       _ptr(score), _ptr(steps), _ptr(tr), _stream(stream)))
@@ -460,8 +457,8 @@ def place_group(problem: DeviceProblem, plans: DevicePlans, group: int, ws=None,
     if out is None:
         out = plans_like(plans, problem.n_groups)
     o = PlansOut(int(out.perm.shape[1]), _ptr(out.perm), _ptr(out.qoff), _ptr(out.evict_bits))
-    score = torch.full((P,), float("nan"), dtype=torch.float64, device=dev)
-    queue = torch.full((P,), -2, dtype=torch.int32, device=dev)
+    score = torch.empty((P,), dtype=torch.float64, device=dev)
+    queue = torch.empty((P,), dtype=torch.int32, device=dev)
     _check(library().qlm_place_group(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                      ctypes.byref(o), int(group), _ptr(ws), ws.numel(),
                                      _ptr(score), _ptr(queue), _stream(stream)))
@@ -499,7 +496,7 @@ def fcfs_score(problem: DeviceProblem, plans: DevicePlans, req_slo, ws=None, str
     if ws is None:
         ws = fcfs_workspace(problem, plans.n_plans, req_slo.numel(), dev)
     if out is None:
-        out = torch.full((max(plans.n_plans, 1),), float("nan"), dtype=torch.float64, device=dev)
+        out = torch.empty((max(plans.n_plans, 1),), dtype=torch.float64, device=dev)
     _check(library().qlm_fcfs_score(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
                                     _ptr(req_slo), req_slo.numel(), _ptr(ws), ws.numel(),
                                     _ptr(out), _stream(stream)))
@@ -530,8 +527,8 @@ def fcfs_best_plan(problem: DeviceProblem, plans: DevicePlans, req_slo, ws=None,
     if ws is None:
         ws = fcfs_workspace(problem, plans.n_plans, req_slo.numel(), dev)
     if out is None:
-        bi = torch.full((1,), -2, dtype=torch.int64, device=dev)
-        bs = torch.full((1,), float("nan"), dtype=torch.float64, device=dev)
+        bi = torch.empty((1,), dtype=torch.int64, device=dev)
+        bs = torch.empty((1,), dtype=torch.float64, device=dev)
     else:
         bi, bs = out
     _check(library().qlm_fcfs_best_plan(ctypes.byref(problem.struct), ctypes.byref(plans.struct),
