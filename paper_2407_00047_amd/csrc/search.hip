@@ -958,17 +958,21 @@ __device__ inline void screen_visit(Run &r, const SRec &x, double theta, double 
     r.prev = m;
 }
 
-// The in-step walks read one tail record per position for a whole wavefront,
-// at an address every lane shares, through the scalar cache (the records are
-// not written while the screens run).
-typedef const __attribute__((address_space(4))) TRec CTRec;
-typedef const __attribute__((address_space(4))) SSt CSSt;
-
+// A tail record at an address that the whole wavefront shares, read through the
+// scalar cache (no kernel that walks writes these records).  Said by the address
+// space: the compiler takes vector loads in a loop that stores, and the relocation
+// screen of 1341 groups in 6 queues took 64 us with them, 40 so.  (The removal
+// screen, which reads a variance besides, is faster with vector loads: 30 us for 33.)
 template <class T>
 __device__ inline const __attribute__((address_space(4))) T *as_const(const T *p)
 {
     return reinterpret_cast<const __attribute__((address_space(4))) T *>(
         reinterpret_cast<uintptr_t>(p));
+}
+__device__ inline TRec uniform_record(const TRec *tr, int u)
+{
+    const __attribute__((address_space(4))) TRec *p = as_const(tr) + u;
+    return TRec{p->m, p->vz, p->n};
 }
 
 // Sum over the positions u in [lo, hi) of each lane of n_u Q(z), the margin
@@ -1503,7 +1507,7 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
         q += tail_walk(st_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
         q += tail_walk(st_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
     } else {
-        auto tr_at = [&](int u) { return tr[u]; };
+        auto tr_at = [&](int u) { return uniform_record(tr, u); };
         q += tail_walk(tr_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
         q += tail_walk(tr_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
     }
