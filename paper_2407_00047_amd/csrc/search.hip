@@ -1086,122 +1086,122 @@ __device__ inline void fswap_body(const SearchArgs &a, int bid, float2 *tab, flo
         for (int k = threadIdx.x; k < ncost; k += kThreads) st_c[k] = a.swap_cost[k];
     const float *swc = cost_lds ? st_c : nullptr;
     for (int wg = wg0; wg * kThreads < ntask; wg += stride) {
-    // the slots this workgroup's tasks visit, [vlo, vhi): removals t < len visit
-    // t and t + 1, swaps s = (t - len) / W up to W + 1 past s; a workgroup can
-    // hold both kinds
-    const int t0 = wg * kThreads, t1 = min(t0 + kThreads, ntask) - 1;
-    int vlo = G, vhi = 0;
-    if (t0 < len) {
-        vlo = base + t0;
-        vhi = base + min(t1, len - 1) + 2;
-    }
-    if (t1 >= len) {
-        vlo = min(vlo, base + (max(t0, len) - len) / W);
-        vhi = max(vhi, base + (t1 - len) / W + W + 2);
-    }
-    vhi = min(vhi, G);
-    const bool rec_lds = vhi - vlo <= kSwapRecs;
-    __syncthreads();                          // (the round before is done with the buffer)
-    if (rec_lds)
-        for (int u = vlo + (int)threadIdx.x; u < vhi; u += kThreads) st_r[u - vlo] = sr[u];
-    __syncthreads();
-    auto rec = [&](int u) { return rec_lds ? st_r[u - vlo] : sr[u]; };
-    const int t = wg * kThreads + threadIdx.x;
-    const bool removal = t < len;
-    const bool swap = !removal && t < ntask;
-    const int s = base + (removal ? t : (swap ? (t - len) / W : 0));
-    const int d = swap ? (t - len) - (s - base) * W + 1 : 0;
-    int g = 0, eq = 0, lo = 0;
-    bool on = false, force = false, valid = false;
-    double q = 0.0, dE = 0.0, db = 0.0, vscale = 0.0;
-    if (removal || swap) {
-        g = (int)min(rec(s).q, (uint32_t)(I - 1));
-        const int bq = qof[g];
-        eq = qof[g + 1];
-        const double theta = (double)a.inst_tput[g];
-        const double inv_theta = 1.0 / theta;
-        vscale = qlm_tail::kVarScale / (theta * theta);
-        const int cls = clampi(a.inst_class[g], 0, a.C - 1);
-        const double eps = margin_eps(eq - bq);
-        Run r = start_at(a, sr, ss, s, bq, g);
-        if (removal) {
-            // without s: the group after it moves up one position; past that the
-            // queue is the old one less s's tokens and variance, with its costs
-            // shifted
-            valid = true;
-            q = r.sc;
-            if (s + 1 < eq) {
-                screen_visit(r, rec(s + 1), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+        // the slots this workgroup's tasks visit, [vlo, vhi): removals t < len visit
+        // t and t + 1, swaps s = (t - len) / W up to W + 1 past s; a workgroup can
+        // hold both kinds
+        const int t0 = wg * kThreads, t1 = min(t0 + kThreads, ntask) - 1;
+        int vlo = G, vhi = 0;
+        if (t0 < len) {
+            vlo = base + t0;
+            vhi = base + min(t1, len - 1) + 2;
+        }
+        if (t1 >= len) {
+            vlo = min(vlo, base + (max(t0, len) - len) / W);
+            vhi = max(vhi, base + (t1 - len) / W + W + 2);
+        }
+        vhi = min(vhi, G);
+        const bool rec_lds = vhi - vlo <= kSwapRecs;
+        __syncthreads();                          // (the round before is done with the buffer)
+        if (rec_lds)
+            for (int u = vlo + (int)threadIdx.x; u < vhi; u += kThreads) st_r[u - vlo] = sr[u];
+        __syncthreads();
+        auto rec = [&](int u) { return rec_lds ? st_r[u - vlo] : sr[u]; };
+        const int t = wg * kThreads + threadIdx.x;
+        const bool removal = t < len;
+        const bool swap = !removal && t < ntask;
+        const int s = base + (removal ? t : (swap ? (t - len) / W : 0));
+        const int d = swap ? (t - len) - (s - base) * W + 1 : 0;
+        int g = 0, eq = 0, lo = 0;
+        bool on = false, force = false, valid = false;
+        double q = 0.0, dE = 0.0, db = 0.0, vscale = 0.0;
+        if (removal || swap) {
+            g = (int)min(rec(s).q, (uint32_t)(I - 1));
+            const int bq = qof[g];
+            eq = qof[g + 1];
+            const double theta = (double)a.inst_tput[g];
+            const double inv_theta = 1.0 / theta;
+            vscale = qlm_tail::kVarScale / (theta * theta);
+            const int cls = clampi(a.inst_class[g], 0, a.C - 1);
+            const double eps = margin_eps(eq - bq);
+            Run r = start_at(a, sr, ss, s, bq, g);
+            if (removal) {
+                // without s: the group after it moves up one position; past that the
+                // queue is the old one less s's tokens and variance, with its costs
+                // shifted
+                valid = true;
                 q = r.sc;
-                lo = s + 2;
-                if (lo < eq) {
-                    const SRec xs = rec(s);
-                    dE = (r.K - ss[s + 1].K) - xs.a * inv_theta;
-                    db = xs.b;
-                    // the variance left ahead keeps most of its bits and a spread wide
-                    // enough for the margin's rounding (both grow along the queue)
-                    const double v0 = ss[lo].V, v1 = v0 - db;
-                    force = force || !(v1 >= 0x1p-20 * v0) ||
-                            !((double)(float)(v1 * vscale) >=
-                              vz_floor(eps, a.Es[b * I + g] + fabs(dE)));
-                    on = true;
-                }
-            }
-        } else if (s + d < eq && s != bq) {
-            valid = true;
-            screen_visit(r, rec(s + d), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-            for (int u = s + 1; u < s + d; ++u)
-                screen_visit(r, rec(u), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-            screen_visit(r, rec(s), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-            q = r.sc;
-            const int u1 = s + d + 1;
-            if (u1 < eq) {
-                screen_visit(r, rec(u1), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-                q = r.sc;
-                lo = u1 + 1;
-                if (lo < eq) {
-                    // past u1 the queue is the old one with its costs shifted by dK
-                    const double dK = r.K - ss[u1].K;
-                    force = force || !((double)tr[lo].vz >=
-                                       vz_floor(eps, a.Es[b * I + g] + fabs(dK)));
-                    if (dK == 0.0)
-                        q += a.Q[b * I + g] - ss[lo].C;
-                    else {
-                        dE = dK;
+                if (s + 1 < eq) {
+                    screen_visit(r, rec(s + 1), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                    q = r.sc;
+                    lo = s + 2;
+                    if (lo < eq) {
+                        const SRec xs = rec(s);
+                        dE = (r.K - ss[s + 1].K) - xs.a * inv_theta;
+                        db = xs.b;
+                        // the variance left ahead keeps most of its bits and a spread wide
+                        // enough for the margin's rounding (both grow along the queue)
+                        const double v0 = ss[lo].V, v1 = v0 - db;
+                        force = force || !(v1 >= 0x1p-20 * v0) ||
+                                !((double)(float)(v1 * vscale) >=
+                                  vz_floor(eps, a.Es[b * I + g] + fabs(dE)));
                         on = true;
+                    }
+                }
+            } else if (s + d < eq && s != bq) {
+                valid = true;
+                screen_visit(r, rec(s + d), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                for (int u = s + 1; u < s + d; ++u)
+                    screen_visit(r, rec(u), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                screen_visit(r, rec(s), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                q = r.sc;
+                const int u1 = s + d + 1;
+                if (u1 < eq) {
+                    screen_visit(r, rec(u1), theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                    q = r.sc;
+                    lo = u1 + 1;
+                    if (lo < eq) {
+                        // past u1 the queue is the old one with its costs shifted by dK
+                        const double dK = r.K - ss[u1].K;
+                        force = force || !((double)tr[lo].vz >=
+                                           vz_floor(eps, a.Es[b * I + g] + fabs(dK)));
+                        if (dK == 0.0)
+                            q += a.Q[b * I + g] - ss[lo].C;
+                        else {
+                            dE = dK;
+                            on = true;
+                        }
                     }
                 }
             }
         }
-    }
-    const bool exactv = __ballot(on && removal) != 0;
-    // the tails of the workgroup's lanes lie in one range of slots: staged in
-    // LDS (records and variances ahead) when it fits, so that the walks read
-    // no global memory
-    const int wlo = block_min_int(on ? lo : INT_MAX, lint_lo);
-    const int whi = -block_min_int(on ? -eq : 0, lint_hi);
-    const bool staged = wlo < whi && whi - wlo <= kSwapStage;
-    if (staged)
-        for (int u = wlo + (int)threadIdx.x; u < whi; u += kThreads) {
-            st_t[u - wlo] = tr[u];
-            st_v[u - wlo] = ss[u].V;
+        const bool exactv = __ballot(on && removal) != 0;
+        // the tails of the workgroup's lanes lie in one range of slots: staged in
+        // LDS (records and variances ahead) when it fits, so that the walks read
+        // no global memory
+        const int wlo = block_min_int(on ? lo : INT_MAX, lint_lo);
+        const int whi = -block_min_int(on ? -eq : 0, lint_hi);
+        const bool staged = wlo < whi && whi - wlo <= kSwapStage;
+        if (staged)
+            for (int u = wlo + (int)threadIdx.x; u < whi; u += kThreads) {
+                st_t[u - wlo] = tr[u];
+                st_v[u - wlo] = ss[u].V;
+            }
+        __syncthreads();
+        if (staged)
+            q += tail_walk([&](int u) { return st_t[u - wlo]; }, [&](int u) { return st_v[u - wlo]; },
+                           tab, on, lo, eq, dE, 0.0f, db, vscale, exactv);
+        else
+            q += tail_walk([&](int u) { return tr[u]; }, [&](int u) { return ss[u].V; }, tab, on, lo,
+                           eq, dE, 0.0f, db, vscale, exactv);
+        if (removal) {
+            const int i = perm[s];
+            const double nq = a.Nq[b * I + g];
+            a.R[b * G + i] = q - a.Q[b * I + g];
+            a.RD[b * G + i] = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(a.Q[b * I + g]) + nq);
         }
-    __syncthreads();
-    if (staged)
-        q += tail_walk([&](int u) { return st_t[u - wlo]; }, [&](int u) { return st_v[u - wlo]; },
-                       tab, on, lo, eq, dE, 0.0f, db, vscale, exactv);
-    else
-        q += tail_walk([&](int u) { return tr[u]; }, [&](int u) { return ss[u].V; }, tab, on, lo,
-                       eq, dE, 0.0f, db, vscale, exactv);
-    if (removal) {
-        const int i = perm[s];
-        const double nq = a.Nq[b * I + g];
-        a.R[b * G + i] = q - a.Q[b * I + g];
-        a.RD[b * G + i] = force ? INFINITY : kEpsP * nq + 1e-12 * (fabs(a.Q[b * I + g]) + nq);
-    }
-    if (swap)
-        a.X[b * a.n_moves + (int64_t)perm[s] * W + (d - 1)] =
-            valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
+        if (swap)
+            a.X[b * a.n_moves + (int64_t)perm[s] * W + (d - 1)] =
+                valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
     }
 }
 
@@ -1435,85 +1435,85 @@ __device__ inline void frel_body(const SearchArgs &a, int bid, float2 *tab, floa
     __syncthreads();
     const float *swc = cost_lds ? st_c : nullptr;
     for (int wg = wg0; base + wg * kThreads < end; wg += stride) {
-    const int s = base + wg * kThreads + threadIdx.x;
-    bool valid = false, force = false, on1 = false, on2 = false;
-    int g = 0, lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
-    double q = 0.0, dE1 = 0.0, dE2 = 0.0, vscale = 0.0;
-    float dvz1 = 0.0f;
-    if (s < end) {
-        SRec x = sr[s];
-        g = (int)min(x.q, (uint32_t)(I - 1));
-        const int bq = qof[g], eq = qof[g + 1];
-        if (s > bq) {
-            valid = true;
-            x.nmf |= kFlagBit;
-            const double theta = (double)a.inst_tput[g];
-            const double inv_theta = 1.0 / theta;
-            vscale = qlm_tail::kVarScale / (theta * theta);
-            const int cls = clampi(a.inst_class[g], 0, a.C - 1);
-            const double eps = margin_eps(eq - bq);
-            const double es = a.Es[b * I + g];
-            Run r{0.0, 0.0, 0.0, 0.0, model0_of(a, g)};
-            screen_visit(r, x, theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-            screen_visit(r, sr[bq], theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-            q = r.sc;
-            const double dK1 = r.K - ss[bq].K;
-            if (bq + 1 < s) {
-                dE1 = x.a * inv_theta + dK1;
-                dvz1 = (float)(x.b * vscale);
-                lo1 = bq + 1;
-                hi1 = s;
-                on1 = true;
-                force = force || !((double)(tr[lo1].vz + dvz1) >= vz_floor(eps, es + fabs(dE1)));
-            }
-            if (s + 1 < eq) {
-                const SSt t = ss[s + 1];
-                const SRec y = sr[s - 1];
-                Run r2{t.A, t.V, s - 1 == bq ? r.K : ss[s - 1].K + dK1, 0.0,
-                       (int)(y.nmf & 0xFFu)};
-                // its sums ahead come from the cache, not from the exact walk's
-                // order: an indicator (nothing ahead with variance) is not trusted
-                force = force || !(t.V > 0.0);
-                screen_visit(r2, sr[s + 1], theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
-                q += r2.sc;
-                const double dK2 = r2.K - t.K;
-                if (s + 2 < eq) {
-                    lo2 = s + 2;
-                    hi2 = eq;
-                    force = force || !((double)tr[lo2].vz >= vz_floor(eps, es + fabs(dK2)));
-                    if (dK2 == 0.0)
-                        q += a.Q[b * I + g] - ss[lo2].C;
-                    else {
-                        dE2 = dK2;
-                        on2 = true;
+        const int s = base + wg * kThreads + threadIdx.x;
+        bool valid = false, force = false, on1 = false, on2 = false;
+        int g = 0, lo1 = 0, hi1 = 0, lo2 = 0, hi2 = 0;
+        double q = 0.0, dE1 = 0.0, dE2 = 0.0, vscale = 0.0;
+        float dvz1 = 0.0f;
+        if (s < end) {
+            SRec x = sr[s];
+            g = (int)min(x.q, (uint32_t)(I - 1));
+            const int bq = qof[g], eq = qof[g + 1];
+            if (s > bq) {
+                valid = true;
+                x.nmf |= kFlagBit;
+                const double theta = (double)a.inst_tput[g];
+                const double inv_theta = 1.0 / theta;
+                vscale = qlm_tail::kVarScale / (theta * theta);
+                const int cls = clampi(a.inst_class[g], 0, a.C - 1);
+                const double eps = margin_eps(eq - bq);
+                const double es = a.Es[b * I + g];
+                Run r{0.0, 0.0, 0.0, 0.0, model0_of(a, g)};
+                screen_visit(r, x, theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                screen_visit(r, sr[bq], theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                q = r.sc;
+                const double dK1 = r.K - ss[bq].K;
+                if (bq + 1 < s) {
+                    dE1 = x.a * inv_theta + dK1;
+                    dvz1 = (float)(x.b * vscale);
+                    lo1 = bq + 1;
+                    hi1 = s;
+                    on1 = true;
+                    force = force || !((double)(tr[lo1].vz + dvz1) >= vz_floor(eps, es + fabs(dE1)));
+                }
+                if (s + 1 < eq) {
+                    const SSt t = ss[s + 1];
+                    const SRec y = sr[s - 1];
+                    Run r2{t.A, t.V, s - 1 == bq ? r.K : ss[s - 1].K + dK1, 0.0,
+                           (int)(y.nmf & 0xFFu)};
+                    // its sums ahead come from the cache, not from the exact walk's
+                    // order: an indicator (nothing ahead with variance) is not trusted
+                    force = force || !(t.V > 0.0);
+                    screen_visit(r2, sr[s + 1], theta, inv_theta, cls, vscale, eps, tab, a, force, swc);
+                    q += r2.sc;
+                    const double dK2 = r2.K - t.K;
+                    if (s + 2 < eq) {
+                        lo2 = s + 2;
+                        hi2 = eq;
+                        force = force || !((double)tr[lo2].vz >= vz_floor(eps, es + fabs(dK2)));
+                        if (dK2 == 0.0)
+                            q += a.Q[b * I + g] - ss[lo2].C;
+                        else {
+                            dE2 = dK2;
+                            on2 = true;
+                        }
                     }
                 }
             }
         }
-    }
-    // the positions the wavefront walks, staged in LDS when they fit
-    const int wlo = __builtin_amdgcn_readfirstlane((int)wave_min(
-        on1 ? (double)lo1 : (on2 ? (double)lo2 : 1e9)));
-    const int whi = __builtin_amdgcn_readfirstlane((int)wave_max(
-        on2 ? (double)hi2 : (on1 ? (double)hi1 : -1.0)));
-    const bool staged = wlo < whi && whi - wlo <= kRelStage;
-    if (staged)
-        for (int u = wlo + (int)(threadIdx.x & (kWave - 1)); u < whi; u += kWave)
-            st[u - wlo] = tr[u];
-    __syncthreads();
-    auto v_at = [&](int u) { return ss[u].V; };    // (not read: exactv is off)
-    if (staged) {
-        auto st_at = [&](int u) { return st[u - wlo]; };
-        q += tail_walk(st_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
-        q += tail_walk(st_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
-    } else {
-        auto tr_at = [&](int u) { return uniform_record(tr, u); };
-        q += tail_walk(tr_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
-        q += tail_walk(tr_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
-    }
-    if (s < end)
-        a.X[b * a.n_moves + (int64_t)G * a.W + (int64_t)G * I + (int64_t)a.perm[b * G + s] * I + g] =
-            valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
+        // the positions the wavefront walks, staged in LDS when they fit
+        const int wlo = __builtin_amdgcn_readfirstlane((int)wave_min(
+            on1 ? (double)lo1 : (on2 ? (double)lo2 : 1e9)));
+        const int whi = __builtin_amdgcn_readfirstlane((int)wave_max(
+            on2 ? (double)hi2 : (on1 ? (double)hi1 : -1.0)));
+        const bool staged = wlo < whi && whi - wlo <= kRelStage;
+        if (staged)
+            for (int u = wlo + (int)(threadIdx.x & (kWave - 1)); u < whi; u += kWave)
+                st[u - wlo] = tr[u];
+        __syncthreads();
+        auto v_at = [&](int u) { return ss[u].V; };    // (not read: exactv is off)
+        if (staged) {
+            auto st_at = [&](int u) { return st[u - wlo]; };
+            q += tail_walk(st_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
+            q += tail_walk(st_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
+        } else {
+            auto tr_at = [&](int u) { return uniform_record(tr, u); };
+            q += tail_walk(tr_at, v_at, tab, on1, lo1, hi1, dE1, dvz1, 0.0, vscale, false);
+            q += tail_walk(tr_at, v_at, tab, on2, lo2, hi2, dE2, 0.0f, 0.0, vscale, false);
+        }
+        if (s < end)
+            a.X[b * a.n_moves + (int64_t)G * a.W + (int64_t)G * I + (int64_t)a.perm[b * G + s] * I + g] =
+                valid ? entry(q - a.Q[b * I + g], force) : INFINITY;
     }
 }
 
@@ -2252,8 +2252,8 @@ __global__ __launch_bounds__(kThreads) void k_place_eval(SearchArgs a, int group
 #pragma clang fp contract(on)
 
 // The place with the lowest exact score (lowest c on ties), applied; a running
-// group stays, and the plan keeps its score.  The plan's queue scores are
-// summed here, in queue order (the running sums the totals need).
+// group stays, and the plan keeps its score.  Every place's total is formed here,
+// the queue scores added in queue order.
 __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *queue,
                                                          double *score)
 {
