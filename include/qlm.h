@@ -391,14 +391,15 @@ int qlm_seed_plans(const qlm_problem *problem, int32_t n, const int32_t *policy,
  * With one request per group and req_slo = grp_slo this is the group score.
  *
  * Every call takes a device workspace, 256-byte aligned, used as scratch.
- * The plans are screened in chunks: a chunk of c plans needs about 19 bytes per
+ * The plans are screened in chunks: a chunk of c plans needs about 21 bytes per
  * group and plan for the lists of groups, and every call a quarter of a byte per
  * request and 8 (I + 2) bytes per plan.  qlm_fcfs_workspace_bytes(problem, n_plans,
  * n_requests, chunk_plans) is the size for chunks of chunk_plans plans
  * (rounded up to a multiple of 64; 0 = as many as 1 GiB of lists holds, the
  * size to use), 0 for an invalid problem.  A call uses the largest chunk the
  * workspace it is given holds, so any workspace of at least the size for
- * chunk_plans = 64 works; smaller chunks only take more launches.  Calls that
+ * chunk_plans = 64 works; smaller chunks only take more launches.  The sizes
+ * never grow as the plans fall, so a workspace serves smaller batches.  Calls that
  * share a workspace must not overlap.
  */
 size_t qlm_fcfs_workspace_bytes(const qlm_problem *problem, int64_t n_plans, int64_t n_requests,

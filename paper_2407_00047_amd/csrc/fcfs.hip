@@ -1243,7 +1243,7 @@ int segment_of(int32_t G, int64_t P)
 int64_t chunk_of(int32_t G, int64_t P, int64_t want)
 {
     const size_t nseg = (size_t)((G > 0 ? G : 1) + kSeg - 1) / kSeg;
-    int64_t c = (int64_t)(kChunkBudget / ((sizeof(Piece) + sizeof(Start) + 8 +
+    int64_t c = (int64_t)(kChunkBudget / ((kSeg / kMinSeg * (sizeof(Piece) + sizeof(Start) + 8) +
                                          kSeg * (sizeof(FEntry) + sizeof(uint16_t))) * nseg));
     if (want > 0) c = want;
     c = (c + kWave - 1) / kWave * kWave;
@@ -1275,10 +1275,14 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     put(L.blk, sizeof(float2) * ((size_t)n_req / kReqBlk + (size_t)G + 1));
     put(L.nreq, 8);
     L.seg = segment_of(G, P);
-    const size_t nseg = (size_t)((G + L.seg - 1) / L.seg);
+    // (room for the longest and the most segments whatever P asks for: the size
+    // may not grow as P falls, or a workspace taken for a large batch in small
+    // chunks would be refused for a smaller one)
+    const size_t slots = (size_t)((G + kSeg - 1) / kSeg) * kSeg;
+    const size_t nseg = (size_t)((G + kMinSeg - 1) / kMinSeg);
     const size_t tiles = (size_t)(L.chunk / kWave);
-    put(L.list, sizeof(FEntry) * tiles * nseg * (size_t)(L.seg * kWave));
-    put(L.listq, sizeof(uint16_t) * tiles * nseg * (size_t)(L.seg * kWave));
+    put(L.list, sizeof(FEntry) * tiles * slots * kWave);
+    put(L.listq, sizeof(uint16_t) * tiles * slots * kWave);
     put(L.listn, 4 * tiles * nseg);
     put(L.piece, sizeof(Piece) * nseg * (size_t)L.chunk);
     put(L.start, sizeof(Start) * nseg * (size_t)L.chunk);

@@ -287,3 +287,20 @@ def test_place_session_argument_checks(lib):
     short = qlm.PlansOut(2, 0x1000, 0x1000, 0x1000)
     assert en(P(pr), 3, P(short), ws, need, None, None) == qlm.QLM_ERR_ARG
 
+
+
+@pytest.mark.parametrize("G,I,requests,chunk", [
+    (8192, 64, 8192 * 128, 64), (1000, 16, 128000, 64), (130, 1, 4000, 64), (65536, 1, 65536, 64),
+    (33, 4096, 33, 64), (8192, 1, 8192, 128), (1000, 16, 128000, 0), (1, 1, 1, 64)])
+def test_fcfs_workspace_serves_smaller_batches(lib, G, I, requests, chunk):
+    """A workspace taken for a large batch serves every smaller one: the calls
+    accept any workspace of the size for chunks of 64 plans, so that size may
+    not exceed the size for a larger batch in the same or larger chunks."""
+    from paper_2407_00047_amd import qlm
+    pr = _problem(qlm, G=G, I=I)
+    sizes = sorted({p for k in range(0, 16) for p in (2 ** k - 63, 2 ** k - 1, 2 ** k, 2 ** k + 65)
+                    if p > 0} | set(range(1920, 2200, 64)) | set(range(16256, 16500, 64)))
+    for p, q in zip(sizes, sizes[1:]):
+        least = lib.qlm_fcfs_workspace_bytes(ctypes.byref(pr), p, requests, 64)
+        assert least <= lib.qlm_fcfs_workspace_bytes(ctypes.byref(pr), q, requests, 64), (p, q)
+        assert least <= lib.qlm_fcfs_workspace_bytes(ctypes.byref(pr), q, requests, chunk), (p, q)
