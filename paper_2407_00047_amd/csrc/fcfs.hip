@@ -110,8 +110,9 @@ constexpr int kSegWaves = kSegThreads / kWave;
 constexpr int kSegBlocks = 230;             // workgroups that (nearly) every CU has one of
 constexpr size_t kSegLdsLimit = 160 * 1024; // LDS of one workgroup
 constexpr int kPrepThreads = 256;
-constexpr int kReqBlk = 32;                 // requests of a block of a group
-constexpr int kHalf = 16;                   // of which so many are evaluated at a time
+constexpr int kReqBlk = 32;                 // most requests of a block of a group
+constexpr int kHalf = 16;                   // of which so many SLOs are staged at a time
+constexpr int kEval = 8;                    // and so many evaluated between two checks for the end
 constexpr int kSub = 8;                     // slots of a k_fwalk batch
 constexpr int kTailWaves = 4;               // wavefronts of a k_ftails workgroup
 constexpr int kBlockList = 2 * kWave;       // blocks a wavefront's list holds
@@ -142,11 +143,17 @@ __device__ inline int grp_model(const FGrp &g) { return (int)(g.cm >> 21); }
 __device__ inline float grp_smin(const FGrp &g) { return __uint_as_float(g.bounds << 16); }
 __device__ inline float grp_smax(const FGrp &g) { return __uint_as_float(g.bounds & 0xFFFF0000u); }
 
-// ... and for the requests: how many are scored (clamped to n_requests), and
-// where their SLOs start.
+// ... and for the requests: how many are scored (clamped to n_requests), where
+// their SLOs start, and how many a block holds (blocks_of).
 struct FReq {
-    uint32_t first, n;
+    uint32_t first, n, per, pad;
 };
+
+// The blocks of n requests: as few as hold them in 32 each, and of one size (the
+// last may be smaller).  A wavefront evaluates 64 blocks in as many steps as the
+// largest has requests, so 33 requests are two blocks of 17, not one of 32 and one
+// of 1.
+__device__ inline int blocks_of(int n) { return (n + kReqBlk - 1) / kReqBlk; }
 
 // Per instance, for the walks: Theta, its reciprocal (for what need not be exact),
 // the table scale over Theta^2, the class
@@ -197,8 +204,8 @@ struct FArgs {
     FGrp *grp;                // [G]
     FReq *req;                // [G]
     FInst *inst;              // [I]
-    int32_t *first;           // [G + 1] request offsets in req_slo
     float2 *blk;              // lowest and highest SLO of each block (block_of)
+    float *slo;               // [kReqBlk] SLOs of each block, +inf past its last
     double *nreq;             // [1] requests scored
     FEntry *list;             // [tiles][nseg][kSeg * 64] the listed groups
     uint16_t *listq;          // and their queues
@@ -282,6 +289,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_fprep(FArgs a)
         FReq r;
         r.first = (uint32_t)lo;
         r.n = (uint32_t)(hi - lo);
+        const int nb = max(blocks_of((int)r.n), 1);
+        r.per = (r.n + (uint32_t)nb - 1u) / (uint32_t)nb;
+        r.pad = 0u;
         a.req[i] = r;
         if (i == a.G - 1) {
             a.nreq[0] = (double)hi;
@@ -299,29 +309,35 @@ __global__ __launch_bounds__(kPrepThreads) void k_fprep(FArgs a)
     }
 }
 
-// The lowest and highest SLO of every block of 32 requests of a group, and of the
-// group: one wavefront per group, two blocks at a time.
+// The lowest and highest SLO of every block of a group's requests and of the
+// group, and the blocks' SLOs, each block in a line of its own (128 bytes), with
+// +inf after its last: a request that is never late.  One wavefront per group, half
+// of it per block.
 __global__ __launch_bounds__(kThreads) void k_fblocks(FArgs a)
 {
     const int i = (int)blockIdx.x * kWaves + wave_id();
     if (i >= a.G) return;
     const int lane = threadIdx.x & (kWave - 1);
     const FReq q = a.req[i];
+    const int n = (int)q.n, nb = blocks_of(n);
+    const int j = lane & (kReqBlk - 1);
     float gmin = INFINITY, gmax = -INFINITY;
-    for (int r0 = 0; r0 < (int)q.n; r0 += kWave) {
-        const int r = r0 + lane;
-        float lo = INFINITY, hi = -INFINITY;
-        if (r < (int)q.n) {
-            const float v = a.req_slo[q.first + r];
+    for (int b0 = 0; b0 < nb; b0 += kWave / kReqBlk) {
+        const int b = b0 + lane / kReqBlk;
+        const int r = b * (int)q.per + j;
+        float lo = INFINITY, hi = -INFINITY, v = INFINITY;
+        if (j < (int)q.per && r < n) {
+            v = a.req_slo[q.first + r];
             lo = v == v ? v : -INFINITY;
             hi = v == v ? v : INFINITY;
         }
+        const int64_t at = block_of(q.first, i, b);
+        if (b < nb) a.slo[at * kReqBlk + j] = v;
         for (int o = kReqBlk / 2; o > 0; o >>= 1) {
             lo = fminf(lo, __shfl_xor(lo, o, kWave));
             hi = fmaxf(hi, __shfl_xor(hi, o, kWave));
         }
-        if ((lane & (kReqBlk - 1)) == 0 && r < (int)q.n)
-            a.blk[block_of(q.first, i, r / kReqBlk)] = make_float2(lo, hi);
+        if (j == 0 && b < nb) a.blk[at] = make_float2(lo, hi);
         gmin = fminf(gmin, fminf(lo, __shfl_xor(lo, kReqBlk, kWave)));
         gmax = fmaxf(gmax, fmaxf(hi, __shfl_xor(hi, kReqBlk, kWave)));
     }
@@ -746,76 +762,120 @@ __global__ __launch_bounds__(kSegThreads) void k_fwalk(FArgs a, int64_t p0, int6
     if (on) a.part[(int64_t)k * a.chunk + col] = (double)sure;
 }
 
-// A wavefront's list of blocks to be evaluated, eight words an entry: the start
-// E[W] of the group's first request and the step from one request to the next
-// (double each), the variance ahead of the block and its step (single), where its
-// SLOs start,
-// and requests | lane of the plan << 6 | nothing varies << 12 | the block's
-// number << 13.  Each word has an array of its own: 64 lanes storing consecutive
-// entries then meet every bank, and reading them too.
+// A wavefront's list of blocks to be evaluated, and the room for their SLOs.  An
+// entry, in two halves: the mean wait E[W] of the block's first request and the
+// step from one request to the next (double each); the variance ahead of the block
+// and its step (single), the block's number, and requests | lane of the plan << 6
+// | nothing varies << 12.  Where nothing varies the wait is the group's first
+// request's, and the block's first request r of the group stands in place of the
+// variance: E[W_r] is formed from them as the oracle forms it.
+// The SLOs come 16 of every block at a time, four reads of 16 bytes a lane, four
+// neighbouring lanes to a block, and are stored as they come: lane l's read i, of
+// block 16 i + l / 4, in place l of row i.  Which of the block's four pieces a lane
+// takes turns with l / 16, so that 16 lanes that read one piece of their own blocks
+// meet on no bank.  Two rows lie in the list's upper half, which is free once 64
+// entries have been read.
 struct BlockList {
-    uint32_t w[8][kBlockList];
+    uint4 half[2][kBlockList];
+    uint4 more[2][kWave];
 };
-
-// The sum of P over a block's requests: the group's start c0 and step c1, the
-// block's first request r0 of the group, the variance ahead v0 and its step v1,
-// the block's SLOs at src.  kAll: 32 requests in every lane, none of them flat;
-// else cnt requests (0 adds nothing), and where nothing varies (flat) comparisons
-// with E[W_r] as the oracle forms it.  kLast: reads no SLO past the block's last.
-template <bool kAll, bool kLast>
-__device__ __attribute__((always_inline)) inline float block_sum(const float2 *tab, const float *src, double c0, double c1, int r0,
-                                  float v0, float v1, int cnt, bool flat)
+__device__ inline uint4 *slo_row(BlockList &bl, int i)
 {
-    const double eb = c0 + (double)r0 * c1;
-    float S = 0.0f;
-    // (half a block at a time: the SLOs of a whole one, with what the unrolled
-    // tails keep in flight, spill registers at four wavefronts a SIMD)
-#pragma unroll 1
-    for (int h = 0; h < kReqBlk; h += kHalf) {
-        float slo[kHalf];
-#pragma unroll
-        for (int k = 0; k < kHalf; ++k) slo[k] = src[kLast ? min(h + k, max(cnt - 1, 0)) : h + k];
-        const double c0h = (double)h;
-        const float v0h = (float)h;
-#pragma unroll
-        for (int k = 0; k < kHalf; ++k) {
-            const float m = (float)fma(-(c0h + (double)k), c1, (double)slo[k] - eb);
-            const float q = qlm_tail::q_of(tab, m, fmaf(v0h + (float)k, v1, v0));
-            if (kAll) {
-                S += q;
-            } else {
-                const float late = c0 + (double)(r0 + h + k) * c1 > (double)slo[k] ? 1.0f : 0.0f;
-                S += h + k < cnt ? (flat ? late : q) : 0.0f;
-            }
-        }
-    }
-    return S;
+    return i < 2 ? &bl.half[i][kWave] : bl.more[i - 2];
+}
+__device__ inline uint4 block_half(double x, double y)
+{
+    return make_uint4((uint32_t)__double2loint(x), (uint32_t)__double2hiint(x),
+                      (uint32_t)__double2loint(y), (uint32_t)__double2hiint(y));
 }
 
-// The list's entries [from, from + n), n <= 64, one per lane, evaluated and added
-// to their plans' sums.
-__device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a, const float2 *tab, const BlockList &bl,
-                                   unsigned long long *sum, int from, int n)
+// kN requests of a block, from request h + k0 on (the staging holds those from h):
+// their tails added to S.  kFlat: blocks where nothing varies are among the lanes'.
+template <int kN, bool kFlat>
+__device__ __attribute__((always_inline)) inline void eval_step(const float2 *tab, BlockList &bl,
+                                                                double eb, double c1, float v0,
+                                                                float v1, bool flat, int r0, int h,
+                                                                int k0, float &S)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint4 *mine = slo_row(bl, lane >> 4) + 4 * (lane & 15);
+    float slo[kN];
+#pragma unroll
+    for (int c = 0; c < kN / 4; ++c) {
+        const uint4 w = mine[(k0 / 4 + c) ^ ((lane >> 2) & 3)];
+        slo[4 * c] = __uint_as_float(w.x);
+        slo[4 * c + 1] = __uint_as_float(w.y);
+        slo[4 * c + 2] = __uint_as_float(w.z);
+        slo[4 * c + 3] = __uint_as_float(w.w);
+    }
+#pragma unroll
+    for (int u = 0; u < kN; ++u) {
+        const int k = h + k0 + u;
+        const float m = (float)fma(-(double)k, c1, (double)slo[u] - eb);
+        const float q = qlm_tail::q_of(tab, m, fmaf((float)k, v1, v0));
+        if (kFlat) {
+            const float late = eb + (double)(r0 + k) * c1 > (double)slo[u] ? 1.0f : 0.0f;
+            S += flat ? late : q;
+        } else {
+            S += q;
+        }
+    }
+}
+
+// The list's entries [from, from + n), n <= 64 and from <= 64, one per lane,
+// evaluated and added to their plans' sums.  A block's requests are padded with ones
+// that are never late, so no lane is masked but those without an entry.
+__device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a, const float2 *tab,
+                                                                  BlockList &bl,
+                                                                  unsigned long long *sum, int from,
+                                                                  int n)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const bool on = lane < n;
     const int e = from + (on ? lane : 0);
-    const double c0 = __hiloint2double((int)bl.w[1][e], (int)bl.w[0][e]);
-    const double c1 = __hiloint2double((int)bl.w[3][e], (int)bl.w[2][e]);
-    const float v0 = __uint_as_float(bl.w[4][e]), v1 = __uint_as_float(bl.w[5][e]);
-    const uint32_t at = bl.w[6][e], what = bl.w[7][e];
-    const float *src = a.req_slo + at;
-    const int cnt = on ? (int)(what & 63u) : 0;
-    const int r0 = (int)(what >> 13) * kReqBlk;
+    const uint4 x = bl.half[0][e], y = bl.half[1][e];
+    const int piece = (lane ^ (lane >> 4)) & 3, b0 = lane >> 2;
+    const float4 *src[kWave / 16];
+#pragma unroll
+    for (int i = 0; i < kWave / 16; ++i)
+        src[i] = reinterpret_cast<const float4 *>(
+                     a.slo + (int64_t)bl.half[1][from + min(16 * i + b0, n - 1)].z * kReqBlk) + piece;
+    const uint32_t what = y.w;
+    // the steps of the largest block, in units of kEval
+    int trip = kEval;
+#pragma unroll
+    for (int k = kEval; k < kReqBlk; k += kEval)
+        trip += __builtin_amdgcn_ballot_w64((int)(what & 63u) > k) != 0 ? kEval : 0;
+    const double eb = __hiloint2double((int)x.y, (int)x.x), c1 = __hiloint2double((int)x.w, (int)x.z);
+    const float v0 = __uint_as_float(y.x), v1 = __uint_as_float(y.y);
     const bool flat = (what >> 12) & 1u;
-    float S;
-    // (a whole block's reads stay inside req_slo except near its end)
-    if (__builtin_amdgcn_ballot_w64((int64_t)at + kReqBlk > a.n_req) != 0)
-        S = block_sum<false, true>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
-    else if (__builtin_amdgcn_ballot_w64(cnt < kReqBlk || flat) != 0)
-        S = block_sum<false, false>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
-    else
-        S = block_sum<true, false>(tab, src, c0, c1, r0, v0, v1, cnt, flat);
+    const bool any_flat = __builtin_amdgcn_ballot_w64(flat) != 0;
+    float4 s[kWave / 16];
+#pragma unroll
+    for (int i = 0; i < kWave / 16; ++i) s[i] = src[i][0];
+    float S = 0.0f;
+#pragma unroll
+    for (int h = 0; h < kReqBlk; h += kHalf) {
+        if (h >= trip) break;
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < kWave / 16; ++i)
+            slo_row(bl, i)[lane] = make_uint4(__float_as_uint(s[i].x), __float_as_uint(s[i].y),
+                                              __float_as_uint(s[i].z), __float_as_uint(s[i].w));
+        // (the second half is on its way while the first is evaluated)
+        if (h == 0 && trip > kHalf)
+#pragma unroll
+            for (int i = 0; i < kWave / 16; ++i) s[i] = src[i][kHalf / 4];
+        wave_sync();
+        const int r0 = (int)y.x;
+        if (any_flat)
+            for (int k0 = 0; k0 < min(kHalf, trip - h); k0 += kEval)
+                eval_step<kEval, true>(tab, bl, eb, c1, v0, v1, flat, r0, h, k0, S);
+        else if (trip > h + kEval)
+            eval_step<kHalf, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S);
+        else
+            eval_step<kEval, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S);
+    }
     if (on)
         atomicAdd(&sum[(what >> 6) & 63u], (unsigned long long)(long long)((double)S * 0x1p32));
 }
@@ -828,12 +888,14 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
 // sorted by group in two passes through LDS and memory, so that a wavefront
 // could take one group of 64 plans and evaluate all of its requests with the SLOs
 // in scalar registers (0.31 + 1.45 ms for 4096 plans of 8192 groups of 128
-// requests).  Here an evaluated request costs more (its SLO comes from L2, a
-// block per lane: with every request evaluated, where spreads are as wide as the
-// waits, the whole call takes 3.4 ms and took 2.0) and few are evaluated: 0.11 +
-// 0.28 ms on random plans.  With the lists in LDS and both passes in one kernel
-// its registers left two wavefronts a SIMD: 1.40 ms.
-__global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_ftails(
+// requests, however many are sure).  Here few requests are evaluated: 0.11 + 0.21 ms
+// on random plans.  With spreads as wide as the waits most are, and the SLOs' way
+// counts: read by each lane for its own block they cost a cache line a lane and
+// kept the L1 busy for longer than the arithmetic takes (3.0 ms); 64 blocks' lines
+// read side by side and passed through LDS take 2.1.  With the lists in LDS and
+// both passes in one kernel its registers left two wavefronts a SIMD: 1.40 ms on
+// random plans.
+__global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_ftails(
     FArgs a, int64_t pc)
 {
     __shared__ __align__(16) float2 tab[qlm_tail::kCells];
@@ -852,12 +914,17 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
     const FEntry *list = a.list + (int64_t)blockIdx.x * (a.seg * kWave);
     const uint16_t *listq = a.listq + (int64_t)blockIdx.x * (a.seg * kWave);
     int nb = 0;                                // entries of the list of blocks
-    int g0 = (wave_id() - kTailWaves) * kWave; // the groups in hand
-    bool have = false;                         // they have blocks left
+    int g0 = wave_id() * kWave;                // the next groups, their entries read ahead
+    FEntry ahead = list[min(g0 + lane, total - 1)];
+    uint32_t aheadq = listq[min(g0 + lane, total - 1)];
+    bool have = false;                         // the groups in hand have blocks left
     int n = 0, bb = 0;                         // this lane's requests; the block in hand
     FEntry e{0.0, 0.0f, 0u};
-    uint32_t q = 0u, first = 0u;
+    uint32_t q = 0u;
+    int64_t block = 0;                         // the group's first block
+    int per = 1;
     const float2 *blk = a.blk;
+    float2 mm = make_float2(0.0f, 0.0f);       // the block in hand's bounds, read ahead
     double c1 = 0.0;
     float v1 = 0.0f;
     bool flat = false;
@@ -865,32 +932,36 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
     for (;;) {
         while (nb < kWave) {
             if (!have) {
-                g0 += kTailWaves * kWave;
                 if (g0 >= total) break;
                 const bool mine = g0 + lane < total;
-                e = list[mine ? g0 + lane : g0];
-                q = listq[mine ? g0 + lane : g0];
+                e = ahead;
+                q = aheadq;
+                g0 += kTailWaves * kWave;
+                ahead = list[min(g0 + lane, total - 1)];
+                aheadq = listq[min(g0 + lane, total - 1)];
                 const int i = (int)(e.id & 0xFFFFu);
                 const FReq r = a.req[i];
                 const FInst in = a.inst[q];
                 const float mu = a.grp[i].mu, var = a.grp[i].var;
-                first = r.first;
+                per = (int)r.per;
                 c1 = (double)mu / in.theta;
                 v1 = (float)((double)var * in.vscale);
                 flat = var == 0.0f && e.v0 == 0.0f;
                 n = mine ? (int)r.n : 0;
-                blk = a.blk + block_of(first, i, 0);
+                block = block_of(r.first, i, 0);
+                blk = a.blk + block;
+                mm = blk[0];
                 ones = 0ull;
                 bb = 0;
                 have = true;
             }
-            const int rb = bb * kReqBlk;
+            const int rb = bb * per;
             const float vb = fmaf((float)rb, v1, e.v0);
+            const int cb = min(per, n - rb);
+            const double ea = e.c0 + (double)rb * c1;
             bool put = false;
             if (rb < n) {
-                const int cb = min(kReqBlk, n - rb);
-                const float2 mm = blk[bb];
-                const double ea = e.c0 + (double)rb * c1, ez = e.c0 + (double)(rb + cb - 1) * c1;
+                const double ez = e.c0 + (double)(rb + cb - 1) * c1;
                 const Side d = side_of(mm.x, mm.y, fmin(ea, ez), fmax(ea, ez),
                                        fmaf((float)cb, v1, vb));
                 put = !d.sure;
@@ -899,19 +970,16 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
             const uint64_t mask = __builtin_amdgcn_ballot_w64(put);
             if (put) {
                 const int to = nb + lane_rank(mask);
-                bl.w[0][to] = (uint32_t)__double2loint(e.c0);
-                bl.w[1][to] = (uint32_t)__double2hiint(e.c0);
-                bl.w[2][to] = (uint32_t)__double2loint(c1);
-                bl.w[3][to] = (uint32_t)__double2hiint(c1);
-                bl.w[4][to] = __float_as_uint(vb);
-                bl.w[5][to] = __float_as_uint(v1);
-                bl.w[6][to] = first + (uint32_t)rb;
-                bl.w[7][to] = (uint32_t)min(kReqBlk, n - rb) | ((e.id >> 16) << 6) |
-                              (flat ? 1u << 12 : 0u) | ((uint32_t)bb << 13);
+                bl.half[0][to] = block_half(flat ? e.c0 : ea, c1);
+                bl.half[1][to] = make_uint4(flat ? (uint32_t)rb : __float_as_uint(vb),
+                                            __float_as_uint(v1), (uint32_t)(block + bb),
+                                            (uint32_t)cb | ((e.id >> 16) << 6) |
+                                                (flat ? 1u << 12 : 0u));
             }
             nb += __builtin_popcountll(mask);
             ++bb;
-            if (__builtin_amdgcn_ballot_w64(bb * kReqBlk < n) == 0) {
+            if (bb * per < n) mm = blk[bb];
+            if (__builtin_amdgcn_ballot_w64(bb * per < n) == 0) {
                 if (ones) atomicAdd(&sum[e.id >> 16], ones << 32);
                 have = false;
             }
@@ -1253,7 +1321,7 @@ int64_t chunk_of(int32_t G, int64_t P, int64_t want)
 }
 
 struct FLayout {
-    size_t grp, req, inst, blk, nreq, list, listq, listn, piece, start, part, F, bmin, ncand, cand, Q, parts, total;
+    size_t grp, req, inst, blk, slo, nreq, list, listq, listn, piece, start, part, F, bmin, ncand, cand, Q, parts, total;
     int64_t chunk;
     int seg;
 };
@@ -1273,6 +1341,7 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     put(L.req, sizeof(FReq) * (size_t)G);
     put(L.inst, sizeof(FInst) * (size_t)I);
     put(L.blk, sizeof(float2) * ((size_t)n_req / kReqBlk + (size_t)G + 1));
+    put(L.slo, sizeof(float) * kReqBlk * ((size_t)n_req / kReqBlk + (size_t)G + 1));
     put(L.nreq, 8);
     L.seg = segment_of(G, P);
     // (room for the longest and the most segments whatever P asks for: the size
@@ -1335,6 +1404,7 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.req = (FReq *)(w + L.req);
     a.inst = (FInst *)(w + L.inst);
     a.blk = (float2 *)(w + L.blk);
+    a.slo = (float *)(w + L.slo);
     a.nreq = (double *)(w + L.nreq);
     a.list = (FEntry *)(w + L.list);
     a.listq = (uint16_t *)(w + L.listq);

@@ -150,6 +150,26 @@ def test_fcfs_lists(qlm, orc, G, I, P, kind):
     assert float(one[0]) <= X.min()
 
 
+# Per-request tails with every request evaluated: groups on either side of a step of
+# 8, a half of 16 and a block of 32 requests, of one size and of all of them
+@pytest.mark.parametrize("sizes", [(1, 1), (2, 2), (8, 8), (9, 9), (10, 10), (16, 18), (24, 26),
+                                   (32, 32), (33, 33), (34, 34), (64, 66), (97, 97), (0, 130)])
+def test_fcfs_blocks(qlm, orc, sizes):
+    import torch
+    G, I, P = 150, 5, 70
+    pr, pl = make(G, I, P, 60 + sizes[0], sizes=sizes)
+    pr["grp_var"] = (pr["grp_var"] * 1e5).astype(np.float32)
+    pr["grp_var"][::7] = 0.0
+    N = int(pr["grp_count"].sum())
+    req = np.random.default_rng(N).uniform(0.0, 3000.0, N).astype(np.float32)
+    dpr, dpl = device_inputs(pr, pl)
+    print("case fcfs blocks", sizes, flush=True)
+    F = qlm.fcfs_score(dpr, dpl, qlm.device_requests(req))
+    torch.cuda.synchronize()
+    err = np.abs(F.cpu().numpy() - orc.score_plans_fcfs(pr, pl, req))
+    assert np.all(err <= SCORE_REL * N), err.max()
+
+
 # Validation: 8 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
 # a workgroup per plan past them; each kind of malformed plan at the tile's edges
 @pytest.mark.parametrize("G,I,P,ld", [
