@@ -39,15 +39,18 @@
 // pieces into each segment's starting sums, and k_fwalk walks each segment again
 // from them.
 //
-// Sums.  A block's terms are added in single precision (32 terms at most) and
-// join the plan's sum over the segment as a 64-bit fixed-point number (2^-32: the
-// segment's requests stay below 2^29), so that the order in which blocks are
-// evaluated changes no bit; the segments' sums are added in order, in double.
+// Sums.  A block's terms but the first are added in single precision (31 terms at
+// most), then the first in double; the sum joins the plan's over the segment as a
+// 64-bit fixed-point number, rounded to the nearest, so that the order in which
+// blocks are evaluated changes no bit.  The point lies as low as the number of
+// requests allows (a million: 2^-41, the last bit of a double-precision sum of
+// 4096); the segments' sums are added in order, in double.
 //
 // Screening bound, per request: table error below 2.2e-6; single-precision
 // rounding of the cell coordinate, of the line's evaluation, of the margin and
 // of the variance below 1.7e-6; the sum of at most 32 terms in single
-// precision below 1.9e-6 per term; so |screened - exact| <= 8e-6 per request.
+// precision below 1.9e-6 per term; the rounding of a sum to fixed point below 1e-10
+// (2^-34, with 2^28 requests or more); so |screened - exact| <= 8e-6 per request.
 // The margin is formed in double from the start E[W], whose rounding stays
 // below 2^-50 E[W_r]: negligible while E[W_r] <= 2^30 SD[W_r] (true of any
 // plan whose variances are not zero or vanishingly small).  A request with
@@ -128,6 +131,7 @@ constexpr size_t kChunkBudget = (size_t)1 << 30;  // bytes of lists and segment 
 // Tail cells beyond which a tail is surely in an end cell (exactly 0 or 1): the
 // table's half width, 512, and room for the rounding of margin and spread.
 constexpr float kSureCells = 516.0f;
+constexpr int kFixBits = 62;                // bits of a segment's score below its sign
 
 // Per group, built once per call: for the walks (the count clamped to 21 bits,
 // the model clamped to [0, M), the bounds of the group's SLOs) in 16 bytes, so
@@ -212,7 +216,7 @@ struct FArgs {
     int32_t *listn;           // [tiles][nseg] how many
     Piece *piece;             // [nseg][chunk]
     Start *start;             // [nseg][chunk]
-    double *part;             // [nseg][chunk] the segments' screened scores
+    int64_t *part;            // [nseg][chunk] the segments' screened scores, in fixed point
     double *F;                // [P] screened scores
     double *bmin;             // [kSumBlocks]
     int32_t *ncand;           // [1]
@@ -221,6 +225,8 @@ struct FArgs {
     double *parts;            // [2 kExactBlocks] their sums of sixteen slices, when tasks are shared
     int64_t chunk;
     int32_t seg, nseg;        // slots per segment, segments of a plan
+    int32_t fix_bits;         // bits after the point of a segment's score
+    double fix, unfix;        // 2^fix_bits and 2^-fix_bits
 };
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -759,7 +765,7 @@ __global__ __launch_bounds__(kSegThreads) void k_fwalk(FArgs a, int64_t p0, int6
         }
     }
     if (lane == 0) a.listn[tile * nseg + k] = ng;
-    if (on) a.part[(int64_t)k * a.chunk + col] = (double)sure;
+    if (on) a.part[(int64_t)k * a.chunk + col] = (int64_t)((uint64_t)sure << a.fix_bits);
 }
 
 // A wavefront's list of blocks to be evaluated, and the room for their SLOs.  An
@@ -789,13 +795,20 @@ __device__ inline uint4 block_half(double x, double y)
                       (uint32_t)__double2loint(y), (uint32_t)__double2hiint(y));
 }
 
+// A sum as a 64-bit fixed-point number, to the nearest.
+__device__ inline unsigned long long fixed_point(const FArgs &a, double x)
+{
+    return (unsigned long long)__double2ll_rn(x * a.fix);
+}
+
 // kN requests of a block, from request h + k0 on (the staging holds those from h):
-// their tails added to S.  kFlat: blocks where nothing varies are among the lanes'.
+// their tails added to S, that of the block's first request put into S0.  kFlat:
+// blocks where nothing varies are among the lanes'.
 template <int kN, bool kFlat>
 __device__ __attribute__((always_inline)) inline void eval_step(const float2 *tab, BlockList &bl,
                                                                 double eb, double c1, float v0,
                                                                 float v1, bool flat, int r0, int h,
-                                                                int k0, float &S)
+                                                                int k0, float &S0, float &S)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const uint4 *mine = slo_row(bl, lane >> 4) + 4 * (lane & 15);
@@ -812,13 +825,15 @@ __device__ __attribute__((always_inline)) inline void eval_step(const float2 *ta
     for (int u = 0; u < kN; ++u) {
         const int k = h + k0 + u;
         const float m = (float)fma(-(double)k, c1, (double)slo[u] - eb);
-        const float q = qlm_tail::q_of(tab, m, fmaf((float)k, v1, v0));
+        float q = qlm_tail::q_of(tab, m, fmaf((float)k, v1, v0));
         if (kFlat) {
             const float late = eb + (double)(r0 + k) * c1 > (double)slo[u] ? 1.0f : 0.0f;
-            S += flat ? late : q;
-        } else {
-            S += q;
+            q = flat ? late : q;
         }
+        if (k == 0)
+            S0 = q;
+        else
+            S += q;
     }
 }
 
@@ -853,7 +868,7 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
     float4 s[kWave / 16];
 #pragma unroll
     for (int i = 0; i < kWave / 16; ++i) s[i] = src[i][0];
-    float S = 0.0f;
+    float S0 = 0.0f, S = 0.0f;
 #pragma unroll
     for (int h = 0; h < kReqBlk; h += kHalf) {
         if (h >= trip) break;
@@ -870,14 +885,13 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
         const int r0 = (int)y.x;
         if (any_flat)
             for (int k0 = 0; k0 < min(kHalf, trip - h); k0 += kEval)
-                eval_step<kEval, true>(tab, bl, eb, c1, v0, v1, flat, r0, h, k0, S);
+                eval_step<kEval, true>(tab, bl, eb, c1, v0, v1, flat, r0, h, k0, S0, S);
         else if (trip > h + kEval)
-            eval_step<kHalf, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S);
+            eval_step<kHalf, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
         else
-            eval_step<kEval, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S);
+            eval_step<kEval, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
     }
-    if (on)
-        atomicAdd(&sum[(what >> 6) & 63u], (unsigned long long)(long long)((double)S * 0x1p32));
+    if (on) atomicAdd(&sum[(what >> 6) & 63u], fixed_point(a, (double)S0 + (double)S));
 }
 
 // Pass 4: the listed groups of one (tile, segment), one workgroup: its wavefronts
@@ -900,7 +914,7 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
 {
     __shared__ __align__(16) float2 tab[qlm_tail::kCells];
     __shared__ BlockList lists[kTailWaves];
-    __shared__ unsigned long long sum[kWave];  // per plan, times 2^32
+    __shared__ unsigned long long sum[kWave];  // per plan, in fixed point
     const int nseg = a.nseg;
     const int64_t tile = blockIdx.x / nseg;
     const int k = (int)(blockIdx.x % nseg);
@@ -965,7 +979,7 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
                 const Side d = side_of(mm.x, mm.y, fmin(ea, ez), fmax(ea, ez),
                                        fmaf((float)cb, v1, vb));
                 put = !d.sure;
-                ones += d.sure && d.one ? (unsigned long long)cb : 0ull;
+                ones += d.sure && d.one ? (unsigned long long)cb << a.fix_bits : 0ull;
             }
             const uint64_t mask = __builtin_amdgcn_ballot_w64(put);
             if (put) {
@@ -980,7 +994,7 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
             ++bb;
             if (bb * per < n) mm = blk[bb];
             if (__builtin_amdgcn_ballot_w64(bb * per < n) == 0) {
-                if (ones) atomicAdd(&sum[e.id >> 16], ones << 32);
+                if (ones) atomicAdd(&sum[e.id >> 16], ones);
                 have = false;
             }
         }
@@ -993,10 +1007,8 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
     }
     __syncthreads();
     const int64_t col = tile * kWave + threadIdx.x;
-    if (threadIdx.x < kWave && col < pc) {
-        double *part = a.part + (int64_t)k * a.chunk + col;
-        *part += (double)(long long)sum[threadIdx.x] * 0x1p-32;
-    }
+    if (threadIdx.x < kWave && col < pc)
+        a.part[(int64_t)k * a.chunk + col] += (int64_t)sum[threadIdx.x];
 }
 
 // Screened plan scores of the chunk (the segments' sums in order) and the
@@ -1011,12 +1023,12 @@ __global__ __launch_bounds__(kThreads) void k_fsum(FArgs a, int64_t p0, int64_t 
         double s = 0.0;
         // (eight reads in flight: one after another they took 21 us for 64 segments)
         for (int b0 = 0; b0 < nb; b0 += 8) {
-            double v[8];
+            int64_t v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                v[u] = b0 + u < nb ? a.part[(int64_t)(b0 + u) * a.chunk + c] : 0.0;
+                v[u] = a.part[(int64_t)min(b0 + u, nb - 1) * a.chunk + c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+            for (int u = 0; u < 8; ++u) s += b0 + u < nb ? (double)v[u] * a.unfix : 0.0;
         }
         a.F[p0 + c] = s;
         mn = fmin(mn, s);
@@ -1411,7 +1423,7 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.listn = (int32_t *)(w + L.listn);
     a.piece = (Piece *)(w + L.piece);
     a.start = (Start *)(w + L.start);
-    a.part = (double *)(w + L.part);
+    a.part = (int64_t *)(w + L.part);
     a.F = (double *)(w + L.F);
     a.bmin = (double *)(w + L.bmin);
     a.ncand = (int32_t *)(w + L.ncand);
@@ -1421,6 +1433,12 @@ FArgs fargs(const qlm_problem *pr, const qlm_plans *pl, const float *req_slo, in
     a.chunk = L.chunk;
     a.seg = L.seg;
     a.nseg = (a.G + L.seg - 1) / L.seg;
+    // a segment of a plan holds at most every request, and 2^28 (128 groups of 2^21)
+    const int64_t most = n_req < ((int64_t)1 << 28) ? n_req : (int64_t)1 << 28;
+    a.fix_bits = kFixBits;
+    while (most >> (kFixBits - a.fix_bits)) --a.fix_bits;
+    a.fix = ldexp(1.0, a.fix_bits);
+    a.unfix = ldexp(1.0, -a.fix_bits);
     return a;
 }
 

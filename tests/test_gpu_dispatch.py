@@ -170,6 +170,36 @@ def test_fcfs_blocks(qlm, orc, sizes):
     assert np.all(err <= SCORE_REL * N), err.max()
 
 
+# Per-request sums: tails of some 1e-9 keep their bits, alone in their block (a
+# group of one request each) and as the first of 33 requests of which the others are
+# late.  The table's lines follow so small a tail to 3e-4 of it (a cell is 0.0117
+# wide, Q'' = z Q' there); a sum that rounds each block to 2^-32 or adds it to 32 in
+# single precision loses percent of them, or all.
+@pytest.mark.parametrize("n", [1, 33])
+def test_fcfs_small_tails(qlm, orc, n):
+    import torch
+    from cases import plans, problem
+    I, rng = 300, np.random.default_rng(n)
+    theta, head, mu, var = 1000.0, 4, 500.0, 1e5
+    groups = [(head, mu, var, 0, 1e9) for _ in range(I)] + [(n, 1.0, 1.0, 0, 1e9) for _ in range(I)]
+    pr = problem(groups, [(theta, 0)] * I)
+    pl = plans([[[g, I + g] for g in range(I)]] * 3, 2 * I)
+    req = np.full(I * (head + n), 1e9, np.float32)
+    z = rng.uniform(5.6, 5.95, I)
+    mine = np.full((I, n), -1e6, np.float32)             # late, but for the first
+    mine[:, 0] = head * mu / theta + z * np.sqrt(head * var) / theta
+    req[I * head:] = mine.reshape(-1)
+    dpr, dpl = device_inputs(pr, pl)
+    print("case fcfs small tails", n, flush=True)
+    F = qlm.fcfs_score(dpr, dpl, qlm.device_requests(req))
+    torch.cuda.synchronize()
+    late = float(I * (n - 1))
+    want = orc.score_plans_fcfs(pr, pl, req) - late
+    got = F.cpu().numpy() - late
+    assert np.all(want > 3e-7)
+    assert np.all(np.abs(got - want) <= 2e-3 * want), (got, want)
+
+
 # Validation: 8 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
 # a workgroup per plan past them; each kind of malformed plan at the tile's edges
 @pytest.mark.parametrize("G,I,P,ld", [
