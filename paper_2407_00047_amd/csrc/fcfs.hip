@@ -115,9 +115,11 @@ constexpr size_t kSegLdsLimit = 160 * 1024; // LDS of one workgroup
 constexpr int kPrepThreads = 256;
 constexpr int kReqBlk = 32;                 // most requests of a block of a group
 constexpr int kHalf = 16;                   // of which so many SLOs are staged at a time
-constexpr int kEval = 8;                    // and so many evaluated between two checks for the end
+constexpr int kEval = 4;                    // and so many evaluated at least
 constexpr int kSub = 8;                     // slots of a k_fwalk batch
 constexpr int kTailWaves = 4;               // wavefronts of a k_ftails workgroup
+constexpr int kBounds = 4;                  // blocks whose bounds are read at a time
+constexpr int kShare = 2048;                // groups of one, while the list is that long
 constexpr int kBlockList = 2 * kWave;       // blocks a wavefront's list holds
 constexpr int kMaxFcfsGroups = 1 << 16;
 constexpr int kMaxFcfsInstances = 4096;
@@ -148,9 +150,12 @@ __device__ inline float grp_smin(const FGrp &g) { return __uint_as_float(g.bound
 __device__ inline float grp_smax(const FGrp &g) { return __uint_as_float(g.bounds & 0xFFFF0000u); }
 
 // ... and for the requests: how many are scored (clamped to n_requests), where
-// their SLOs start, and how many a block holds (blocks_of).
-struct FReq {
-    uint32_t first, n, per, pad;
+// their SLOs start, how many a block holds (blocks_of), and the group's statistics
+// again (k_ftails reads them for 64 groups at a time, a cache line each).
+struct alignas(32) FReq {
+    uint32_t first, n, per;
+    float mu, var;
+    uint32_t pad[3];
 };
 
 // The blocks of n requests: as few as hold them in 32 each, and of one size (the
@@ -297,7 +302,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_fprep(FArgs a)
         r.n = (uint32_t)(hi - lo);
         const int nb = max(blocks_of((int)r.n), 1);
         r.per = (r.n + (uint32_t)nb - 1u) / (uint32_t)nb;
-        r.pad = 0u;
+        r.mu = g.mu;
+        r.var = g.var;
+        r.pad[0] = r.pad[1] = r.pad[2] = 0u;
         a.req[i] = r;
         if (i == a.G - 1) {
             a.nreq[0] = (double)hi;
@@ -847,20 +854,22 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
 {
     const int lane = threadIdx.x & (kWave - 1);
     const bool on = lane < n;
-    const int e = from + (on ? lane : 0);
-    const uint4 x = bl.half[0][e], y = bl.half[1][e];
+    // (with n < 64 the list ends there, from = 0: what the other lanes read is an
+    // entry evaluated before or the empty one)
+    const uint4 x = bl.half[0][from + lane], y = bl.half[1][from + lane];
     const int piece = (lane ^ (lane >> 4)) & 3, b0 = lane >> 2;
     const float4 *src[kWave / 16];
 #pragma unroll
     for (int i = 0; i < kWave / 16; ++i)
         src[i] = reinterpret_cast<const float4 *>(
-                     a.slo + (int64_t)bl.half[1][from + min(16 * i + b0, n - 1)].z * kReqBlk) + piece;
+                     a.slo + (int64_t)bl.half[1][from + 16 * i + b0].z * kReqBlk) + piece;
     const uint32_t what = y.w;
     // the steps of the largest block, in units of kEval
+    const int cnt = on ? (int)(what & 63u) : 0;
     int trip = kEval;
 #pragma unroll
-    for (int k = kEval; k < kReqBlk; k += kEval)
-        trip += __builtin_amdgcn_ballot_w64((int)(what & 63u) > k) != 0 ? kEval : 0;
+    for (int b = kReqBlk / 2; b >= kEval; b /= 2)
+        trip += __builtin_amdgcn_ballot_w64(cnt > trip - kEval + b) != 0 ? b : 0;
     const double eb = __hiloint2double((int)x.y, (int)x.x), c1 = __hiloint2double((int)x.w, (int)x.z);
     const float v0 = __uint_as_float(y.x), v1 = __uint_as_float(y.y);
     const bool flat = (what >> 12) & 1u;
@@ -882,14 +891,17 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
 #pragma unroll
             for (int i = 0; i < kWave / 16; ++i) s[i] = src[i][kHalf / 4];
         wave_sync();
-        const int r0 = (int)y.x;
-        if (any_flat)
-            for (int k0 = 0; k0 < min(kHalf, trip - h); k0 += kEval)
+        const int r0 = (int)y.x, rest = trip - h;
+        if (any_flat) {
+            for (int k0 = 0; k0 < min(kHalf, rest); k0 += kEval)
                 eval_step<kEval, true>(tab, bl, eb, c1, v0, v1, flat, r0, h, k0, S0, S);
-        else if (trip > h + kEval)
+        } else if (rest >= kHalf) {
             eval_step<kHalf, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
-        else
-            eval_step<kEval, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
+        } else {
+            if (rest >= 8) eval_step<8, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
+            if (rest == 12) eval_step<4, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 8, S0, S);
+            if (rest == 4) eval_step<4, false>(tab, bl, eb, c1, v0, v1, flat, r0, h, 0, S0, S);
+        }
     }
     if (on) atomicAdd(&sum[(what >> 6) & 63u], fixed_point(a, (double)S0 + (double)S));
 }
@@ -902,35 +914,43 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
 // sorted by group in two passes through LDS and memory, so that a wavefront
 // could take one group of 64 plans and evaluate all of its requests with the SLOs
 // in scalar registers (0.31 + 1.45 ms for 4096 plans of 8192 groups of 128
-// requests, however many are sure).  Here few requests are evaluated: 0.11 + 0.21 ms
-// on random plans.  With spreads as wide as the waits most are, and the SLOs' way
-// counts: read by each lane for its own block they cost a cache line a lane and
-// kept the L1 busy for longer than the arithmetic takes (3.0 ms); 64 blocks' lines
-// read side by side and passed through LDS take 2.1.  With the lists in LDS and
-// both passes in one kernel its registers left two wavefronts a SIMD: 1.40 ms on
-// random plans.
+// requests, however many are sure; the call 2.0).  Here few requests are evaluated:
+// 0.10 + 0.16 ms on random plans, the call 0.41.  With spreads as wide as the waits
+// nearly all are, and the L1's misses count: a line per lane for the SLOs, one per
+// block for its bounds and two per group took the kernel to 3.0 ms; 64 blocks' SLOs
+// read as whole lines and passed through LDS, four blocks' bounds and all of a
+// group's numbers read at a time leave 1.85 (arithmetic busy 88% of it), the call
+// 2.11; where the groups are smaller it is the faster one (33 requests: 0.98 ms for
+// 1.03).  With the lists in LDS and both passes in one kernel its registers left two
+// wavefronts a SIMD: 1.40 ms on random plans.
 __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_ftails(
-    FArgs a, int64_t pc)
+    FArgs a, int64_t pc, uint32_t lists_n)
 {
     __shared__ __align__(16) float2 tab[qlm_tail::kCells];
     __shared__ BlockList lists[kTailWaves];
     __shared__ unsigned long long sum[kWave];  // per plan, in fixed point
     const int nseg = a.nseg;
-    const int64_t tile = blockIdx.x / nseg;
-    const int k = (int)(blockIdx.x % nseg);
-    const int total = min(a.listn[blockIdx.x], a.seg * kWave);
-    if (total == 0) return;                    // (the same in the whole workgroup)
+    const int64_t which = blockIdx.x % lists_n;
+    const int64_t tile = which / nseg;
+    const int k = (int)(which % nseg);
+    const int total = min(a.listn[which], a.seg * kWave);
+    // of a long list, every share-th workgroup's groups (2048 of them: half as many
+    // cost more in tables staged and in last evaluations of a few blocks)
+    const int part = (int)(blockIdx.x / lists_n);
+    const int share = (total + kShare - 1) / kShare;
+    if (part >= share) return;                 // (the same in the whole workgroup)
+    const int lane = threadIdx.x & (kWave - 1);
+    const FEntry *list = a.list + which * (a.seg * kWave);
+    const uint16_t *listq = a.listq + which * (a.seg * kWave);
+    int g0 = (part * kTailWaves + wave_id()) * kWave;   // the next groups, their entries read ahead
+    FEntry ahead = list[min(g0 + lane, total - 1)];
+    uint32_t aheadq = listq[min(g0 + lane, total - 1)];
     qlm_tail::stage(tab, (int)threadIdx.x, kTailWaves * kWave);
     if (threadIdx.x < kWave) sum[threadIdx.x] = 0ull;
     __syncthreads();
     BlockList &bl = lists[wave_id()];
-    const int lane = threadIdx.x & (kWave - 1);
-    const FEntry *list = a.list + (int64_t)blockIdx.x * (a.seg * kWave);
-    const uint16_t *listq = a.listq + (int64_t)blockIdx.x * (a.seg * kWave);
+    bl.half[0][lane] = bl.half[1][lane] = make_uint4(0u, 0u, 0u, 0u);
     int nb = 0;                                // entries of the list of blocks
-    int g0 = wave_id() * kWave;                // the next groups, their entries read ahead
-    FEntry ahead = list[min(g0 + lane, total - 1)];
-    uint32_t aheadq = listq[min(g0 + lane, total - 1)];
     bool have = false;                         // the groups in hand have blocks left
     int n = 0, bb = 0;                         // this lane's requests; the block in hand
     FEntry e{0.0, 0.0f, 0u};
@@ -938,11 +958,13 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
     int64_t block = 0;                         // the group's first block
     int per = 1;
     const float2 *blk = a.blk;
-    float2 mm = make_float2(0.0f, 0.0f);       // the block in hand's bounds, read ahead
+    float2 mm[kBounds];                        // the bounds of its next blocks, read ahead
+#pragma unroll
+    for (int u = 0; u < kBounds; ++u) mm[u] = make_float2(0.0f, 0.0f);
     double c1 = 0.0;
     float v1 = 0.0f;
     bool flat = false;
-    unsigned long long ones = 0ull;
+    unsigned long long ones = 0ull;            // its sure blocks
     for (;;) {
         while (nb < kWave) {
             if (!have) {
@@ -950,21 +972,21 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
                 const bool mine = g0 + lane < total;
                 e = ahead;
                 q = aheadq;
-                g0 += kTailWaves * kWave;
+                g0 += share * kTailWaves * kWave;
                 ahead = list[min(g0 + lane, total - 1)];
                 aheadq = listq[min(g0 + lane, total - 1)];
                 const int i = (int)(e.id & 0xFFFFu);
                 const FReq r = a.req[i];
                 const FInst in = a.inst[q];
-                const float mu = a.grp[i].mu, var = a.grp[i].var;
                 per = (int)r.per;
-                c1 = (double)mu / in.theta;
-                v1 = (float)((double)var * in.vscale);
-                flat = var == 0.0f && e.v0 == 0.0f;
+                c1 = (double)r.mu / in.theta;
+                v1 = (float)((double)r.var * in.vscale);
+                flat = r.var == 0.0f && e.v0 == 0.0f;
                 n = mine ? (int)r.n : 0;
                 block = block_of(r.first, i, 0);
                 blk = a.blk + block;
-                mm = blk[0];
+#pragma unroll
+                for (int u = 0; u < kBounds; ++u) mm[u] = blk[u];
                 ones = 0ull;
                 bb = 0;
                 have = true;
@@ -976,7 +998,7 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
             bool put = false;
             if (rb < n) {
                 const double ez = e.c0 + (double)(rb + cb - 1) * c1;
-                const Side d = side_of(mm.x, mm.y, fmin(ea, ez), fmax(ea, ez),
+                const Side d = side_of(mm[0].x, mm[0].y, fmin(ea, ez), fmax(ea, ez),
                                        fmaf((float)cb, v1, vb));
                 put = !d.sure;
                 ones += d.sure && d.one ? (unsigned long long)cb << a.fix_bits : 0ull;
@@ -992,8 +1014,13 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
             }
             nb += __builtin_popcountll(mask);
             ++bb;
-            if (bb * per < n) mm = blk[bb];
-            if (__builtin_amdgcn_ballot_w64(bb * per < n) == 0) {
+            const bool more = bb * per < n;
+#pragma unroll
+            for (int u = 0; u + 1 < kBounds; ++u) mm[u] = mm[u + 1];
+            if (bb % kBounds == 0 && more)
+#pragma unroll
+                for (int u = 0; u < kBounds; ++u) mm[u] = blk[bb + u];
+            if (__builtin_amdgcn_ballot_w64(more) == 0) {
                 if (ones) atomicAdd(&sum[e.id >> 16], ones);
                 have = false;
             }
@@ -1007,8 +1034,13 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
     }
     __syncthreads();
     const int64_t col = tile * kWave + threadIdx.x;
-    if (threadIdx.x < kWave && col < pc)
-        a.part[(int64_t)k * a.chunk + col] += (int64_t)sum[threadIdx.x];
+    if (threadIdx.x < kWave && col < pc) {
+        int64_t *score = &a.part[(int64_t)k * a.chunk + col];
+        if (share == 1)
+            *score += (int64_t)sum[threadIdx.x];
+        else
+            atomicAdd((unsigned long long *)score, sum[threadIdx.x]);
+    }
 }
 
 // Screened plan scores of the chunk (the segments' sums in order) and the
@@ -1352,7 +1384,7 @@ FLayout flayout(const qlm_problem *pr, int64_t P, int64_t n_req, int64_t chunk)
     put(L.grp, sizeof(FGrp) * (size_t)G);
     put(L.req, sizeof(FReq) * (size_t)G);
     put(L.inst, sizeof(FInst) * (size_t)I);
-    put(L.blk, sizeof(float2) * ((size_t)n_req / kReqBlk + (size_t)G + 1));
+    put(L.blk, sizeof(float2) * ((size_t)n_req / kReqBlk + (size_t)G + kBounds));
     put(L.slo, sizeof(float) * kReqBlk * ((size_t)n_req / kReqBlk + (size_t)G + 1));
     put(L.nreq, 8);
     L.seg = segment_of(G, P);
@@ -1529,8 +1561,12 @@ int screen_all(const FArgs &a, hipStream_t stream)
         if ((rc = launched("k_fwalk launch"))) return rc;
         qlm_internal::TimedLaunch tl;
         if ((rc = qlm_internal::timing_begin(stream, &tl))) return rc;
-        hipLaunchKernelGGL(k_ftails, dim3((unsigned)(tiles * a.nseg)), dim3(kTailWaves * kWave), 0,
-                           stream, a, pc);
+        // (as many workgroups as the longest list has shares; those without one end at
+        // once, after every list's first)
+        const unsigned nlists = (unsigned)(tiles * a.nseg);
+        const unsigned shares = (unsigned)((a.seg * kWave + kShare - 1) / kShare);
+        hipLaunchKernelGGL(k_ftails, dim3(nlists * shares), dim3(kTailWaves * kWave), 0, stream, a,
+                           pc, nlists);
         if ((rc = launched("k_ftails launch"))) return rc;
         qlm_internal::timing_end(stream, &tl);
         hipLaunchKernelGGL(k_fsum, dim3(kSumBlocks), dim3(kThreads), 0, stream, a, p0, pc,
