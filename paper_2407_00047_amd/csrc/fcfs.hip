@@ -1103,41 +1103,18 @@ __global__ __launch_bounds__(kThreads) void k_fselect(FArgs a, int nbmin)
 // ---------------------------------------------------------------------------
 // Exact scores
 
-// The oracle's terms for one group in double, for its requests in slice j of
-// nsl (consecutive arrivals): the slice's sum starts at 0 and adds its P_r in
-// arrival order.
-__device__ inline double slot_exact(const FArgs &a, int i, double A, double V, double K,
-                                    double theta, int j, int nsl)
-{
-    const int n = (int)a.req[i].n;
-    const double mu = (double)a.grp[i].mu;
-    const double var = (double)a.grp[i].var;
-    const float *slo = a.req_slo + a.req[i].first;
-    const double EW = A / theta + K;
-    double slot = 0.0;
-    const int r0 = (int)((int64_t)n * j / nsl), r1 = (int)((int64_t)n * (j + 1) / nsl);
-    for (int r = r0; r < r1; ++r) {
-        const double sl = (double)slo[r];
-        const double Er = EW + (double)r * (mu / theta);
-        const double SDr = sqrt(V + (double)r * var) / theta;
-        double P;
-        if (SDr > 0.0)
-            P = 0.5 * erfc((sl - Er) / (SDr * 1.4142135623730951));
-        else
-            P = (Er > sl) ? 1.0 : 0.0;
-        slot += P;
-    }
-    return slot;
-}
-
 // Workgroups over a fixed grid take (candidate k, queue g) tasks; every group's
-// requests are cut into 64 slices (consecutive arrivals), four for each of a
-// workgroup's 16 wavefronts (slices w, w + 16, ...).  A wavefront walks the queue's positions 64 at a time, one per
+// requests are cut into 64 slices (consecutive arrivals), four next to each other for
+// each of a workgroup's 16 wavefronts (so that groups of a few requests keep as many
+// wavefronts busy).  A wavefront walks the queue's positions 64 at a time, one per
 // lane; the running sums ripple from lane to lane in position order, then each
-// lane forms its slices of its group's requests' terms, and those sums ripple
-// into the slices' queue sums the same way.  The queue score is the slices'
-// sums added in slice order, sixteen at a time, then the four sums (the oracle's
-// sum reassociated: equal to within the rounding of a sum of that many terms).
+// lane forms its slices of its group's requests' terms, and a lane per slice adds
+// them in position order.  (Rippled like the running sums, slice after slice, the
+// terms took longer than their erfc where many plans are re-scored: 64 plans of 64
+// queues 1.00 ms, 0.77 so.)  The queue score is the sum over the wavefronts' first
+// slices, second, third and fourth ones, each in order, then of the four (the
+// oracle's sum reassociated: equal to within the rounding of a sum of that many
+// terms).
 // When few tasks are there (one candidate of 64 queues is the usual case) two or
 // four workgroups share a task, each with half or a quarter of every wavefront's
 // slices, and the sums of sixteen go to `parts` (task_score adds them); the
@@ -1147,6 +1124,33 @@ constexpr int kExactThreads = 1024;
 constexpr int kExactWaves = kExactThreads / kWave;
 constexpr int kExactSubs = 4;                      // slices per wavefront
 constexpr int kExactSlices = kExactWaves * kExactSubs;
+
+// The oracle's terms for one group in double: its requests, their mean wait EW and
+// the step from one to the next, the variance ahead and its step.  slice: the sum of
+// slice j of the requests (consecutive arrivals), which starts at 0 and adds its P_r
+// in arrival order.
+struct ExactGroup {
+    const float *slo;
+    int n;
+    double EW, step, V, var;
+    __device__ inline double slice(double theta, int j) const
+    {
+        double slot = 0.0;
+        const int r0 = n * j / kExactSlices, r1 = n * (j + 1) / kExactSlices;  // (n < 2^21)
+        for (int r = r0; r < r1; ++r) {
+            const double sl = (double)slo[r];
+            const double Er = EW + (double)r * step;
+            const double SDr = sqrt(V + (double)r * var) / theta;
+            double P;
+            if (SDr > 0.0)
+                P = 0.5 * erfc((sl - Er) / (SDr * 1.4142135623730951));
+            else
+                P = (Er > sl) ? 1.0 : 0.0;
+            slot += P;
+        }
+        return slot;
+    }
+};
 
 // Workgroups that share a task.
 __device__ inline int task_split(int64_t tasks)
@@ -1168,6 +1172,7 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
                                                            const int32_t *count_dev, int64_t count)
 {
     __shared__ double part[kExactSubs][kExactWaves];
+    __shared__ double terms[kExactWaves][kExactSubs][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int js = wave_id();
     const int64_t n = count_dev ? (int64_t)__builtin_amdgcn_readfirstlane(count_dev[0]) : count;
@@ -1188,7 +1193,8 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
         const double theta = (double)a.inst_tput[g];
         const int cls = clampi(a.inst_class[g], 0, a.C - 1);
         int prev = a.inst_model0 ? clampi(a.inst_model0[g], -1, a.M - 1) : -1;
-        double rA = 0.0, rV = 0.0, rK = 0.0, rC[kExactSubs] = {0.0, 0.0, 0.0, 0.0};
+        double rA = 0.0, rV = 0.0, rK = 0.0;
+        double rC = 0.0;                       // lane s < subs: the sum of its slice sub0 + s
         for (int v0 = bq; v0 < eq; v0 += kWave) {
             const int cnt = min(kWave, eq - v0);
             const bool on = lane < cnt;
@@ -1231,20 +1237,39 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
             double K = K0 + c1;
             K = K + c2;
             const int last = cnt - 1;
-#pragma unroll
-            for (int s = 0; s < kExactSubs; ++s) {
-                if (s >= subs) break;
-                const double term = i >= 0 ? slot_exact(a, i, A, V, K, theta,
-                                                        (sub0 + s) * kExactWaves + js, kExactSlices)
-                                           : 0.0;
-                const double lt = from_left0(term);
-                double C = rC[s];
-                for (int j = 0; j < steps; j += 8) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) C = from_left(C) + lt;
-                }
-                rC[s] = lane_value(C, last) + lane_value(term, last);
+            // the slices' terms, a position per lane, change places in LDS: a lane per
+            // slice then adds its positions one after another
+            double (*mine)[kWave] = terms[js];
+            ExactGroup x{nullptr, 0, 0.0, 0.0, V, 0.0};
+            if (i >= 0) {
+                const FReq q = a.req[i];
+                x.slo = a.req_slo + q.first;
+                x.n = (int)q.n;
+                x.EW = A / theta + K;
+                x.step = (double)q.mu / theta;
+                x.var = (double)q.var;
             }
+            bool some = false;
+            for (int s = 0; s < subs; ++s) {
+                const double t = x.slice(theta, js * kExactSubs + sub0 + s);
+                some = some || t != 0.0;
+                mine[s][lane] = t;
+            }
+            wave_sync();
+            // (zeros leave the sums as they are: slices without requests, tails of none)
+            if (__builtin_amdgcn_ballot_w64(some) != 0 && lane < subs) {
+                const double *t = mine[lane];
+                int j = 0;
+                for (; j + 8 <= cnt; j += 8) {
+                    double x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = t[j + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) rC += x[u];
+                }
+                for (; j < cnt; ++j) rC += t[j];
+            }
+            wave_sync();
             rA = lane_value(A, last) + lane_value(xa, last);
             rV = lane_value(V, last) + lane_value(xb, last);
             rK = lane_value(K, last);
@@ -1252,8 +1277,7 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
             int carry = __builtin_amdgcn_readlane(mm, last);
             prev = carry;
         }
-        if (lane == 0)
-            for (int s = 0; s < kExactSubs; ++s) part[s][js] = rC[s];
+        if (lane < subs) part[lane][js] = rC;
         __syncthreads();
         if (threadIdx.x == 0) {
             double q = 0.0;
@@ -1289,20 +1313,32 @@ __global__ __launch_bounds__(kPickThreads) void k_fpick(FArgs a, int64_t *best_i
     const int n = a.ncand[0];
     double bs = INFINITY;
     int64_t bi = -1;
-    // one wavefront per candidate: the lanes load its queue scores, which are
-    // added in queue order
     const int lane = threadIdx.x & (kWave - 1);
-    for (int k = wave_id(); k < n; k += kPickThreads / kWave) {
-        double s = 0.0;
-        for (int g0 = 0; g0 < a.I; g0 += kWave) {
-            const double q = g0 + lane < a.I ? task_score(a, n, k, g0 + lane) : 0.0;
-            const int c = min(kWave, a.I - g0);
-            for (int j = 0; j < c; ++j) s += lane_value(q, j);
-        }
-        const int64_t p = a.cand[k];
-        if (lane == 0 && s == s && (bi < 0 || better(s, p, bs, bi))) {   // a NaN score never wins
+    auto take = [&](double s, int64_t p) {
+        if (s == s && (bi < 0 || better(s, p, bs, bi))) {   // a NaN score never wins
             bs = s;
             bi = p;
+        }
+    };
+    if (n <= 2 * a.I) {
+        // one wavefront per candidate: the lanes load its queue scores, which are
+        // added in queue order
+        for (int k = wave_id(); k < n; k += kPickThreads / kWave) {
+            double s = 0.0;
+            for (int g0 = 0; g0 < a.I; g0 += kWave) {
+                const double q = g0 + lane < a.I ? task_score(a, n, k, g0 + lane) : 0.0;
+                const int c = min(kWave, a.I - g0);
+                for (int j = 0; j < c; ++j) s += lane_value(q, j);
+            }
+            if (lane == 0) take(s, a.cand[k]);
+        }
+    } else {
+        // many (every plan, where none misses an SLO): a lane per candidate; 4096 of
+        // 16 queues took 1.3 ms a wavefront each
+        for (int k = threadIdx.x; k < n; k += kPickThreads) {
+            double s = 0.0;
+            for (int g = 0; g < a.I; ++g) s += task_score(a, n, k, g);
+            take(s, a.cand[k]);
         }
     }
     for (int o = kWave / 2; o > 0; o >>= 1) {

@@ -200,6 +200,27 @@ def test_fcfs_small_tails(qlm, orc, n):
     assert np.all(np.abs(got - want) <= 2e-3 * want), (got, want)
 
 
+# Exact per-request scores of many plans: groups of fewer requests than slices,
+# queues of more positions than lanes; and the pick among more candidates than a
+# wavefront each is right for (every plan tied)
+@pytest.mark.parametrize("G,I,P,sizes", [(70, 1, 130, (1, 1)), (200, 3, 300, (0, 9)),
+                                         (150, 2, 64, (63, 65)), (64, 64, 129, (16, 130))])
+def test_fcfs_exact_many(qlm, orc, G, I, P, sizes):
+    import torch
+    pr, pl = make(G, I, P, 90 + G, sizes=sizes)
+    N = int(pr["grp_count"].sum())
+    req = np.random.default_rng(G).uniform(0.0, 3000.0, N).astype(np.float32)
+    dpr, dpl = device_inputs(pr, pl)
+    print("case fcfs exact many", G, I, P, flush=True)
+    X = qlm.fcfs_score_exact(dpr, dpl, qlm.device_requests(req), np.arange(P))
+    never = qlm.device_requests(np.full(N, 1e9, np.float32))
+    bi, bs = qlm.fcfs_best_plan(dpr, dpl, never)
+    torch.cuda.synchronize()
+    S = orc.score_plans_fcfs(pr, pl, req)
+    assert np.all(np.abs(X.cpu().numpy() - S) <= 1e-12 * (np.abs(S) + 1.0))
+    assert int(bi.item()) == 0 and float(bs.item()) == 0.0
+
+
 # Validation: 8 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
 # a workgroup per plan past them; each kind of malformed plan at the tile's edges
 @pytest.mark.parametrize("G,I,P,ld", [
