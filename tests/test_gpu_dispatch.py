@@ -257,10 +257,12 @@ def test_validate_tiles(qlm, G, I, P, ld):
 # Search: after the first step only the two changed queues are screened.  Every
 # step equals a search of one step (which screens everything) from the plan it
 # left: relocations that set flags, emptied and skewed queues (workgroups that loop),
-# more queues and wider windows than a wavefront, one queue, no window
+# one queue of nearly all groups (more workgroups than a mean queue's), more queues
+# and wider windows than a wavefront, one queue, no window
 @pytest.mark.parametrize("G,I,W,steps,kind", [
     (1, 1, 2, 2, "plain"), (30, 3, 4, 14, "evict"), (64, 9, 0, 10, "empty"), (90, 1, 70, 6, "plain"),
-    (200, 70, 3, 8, "evict"), (300, 4, 8, 12, "skewed"), (500, 12, 16, 8, "evict")])
+    (200, 70, 3, 8, "evict"), (300, 4, 8, 12, "skewed"), (500, 12, 16, 8, "evict"),
+    (1500, 16, 2, 5, "heavy")])
 def test_search_incremental(qlm, G, I, W, steps, kind):
     import torch
     P = 3
@@ -268,6 +270,10 @@ def test_search_incremental(qlm, G, I, W, steps, kind):
     rng = np.random.default_rng(G)
     pr["evict_cost"] = 0.5
     pr["grp_slo"] = rng.choice([5.0, 20.0, 60.0, 400.0], G).astype(np.float32)
+    if kind == "heavy":                          # nearly all groups in one queue
+        for p in range(P):
+            pl["qoff"][1:I, p] = np.where(np.arange(1, I) <= 5 * p, np.arange(1, I), G - I +
+                                          np.arange(1, I))
     if kind in ("empty", "skewed"):
         for p in range(P):
             cuts = np.sort(rng.integers(0, G + 1, I - 1)) if kind == "empty" else \
