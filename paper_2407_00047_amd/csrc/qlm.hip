@@ -1625,11 +1625,14 @@ __global__ void k_zero_i64(int64_t *p)
 // and qoff are read coalesced, kValRows of them in flight per thread, and every
 // plan has a bitmap of seen group ids in LDS (word w of plan j at w 2^ls + j: with
 // 64 plans a wavefront's 64 bits lie in 64 banks).  A permutation sets G bits.
-// Bytes bound it: 16,384 plans of 1024 groups (70 MB) take 14.8 us; a workgroup
-// per plan, whose reads were 4 bytes out of every row, took 84.
+// Bytes bound it: 16,384 plans of 1024 groups (70 MB) take 14.8 us of a call of 16.3
+// when the batch is checked again, 18.3 in turn with seven others (0.56 GB, more than
+// the memory-side cache holds); a workgroup per plan, whose reads were 4 bytes out of
+// every row, took 84 and 96.  The first pass over a batch in memory that the card has
+// not read before takes 0.18 ms either way.
 constexpr int kValThreads = 1024;
 constexpr int kValRows = 8;
-constexpr int kMaxValShift = 6, kMinValShift = 3;
+constexpr int kMaxValShift = 6, kRowValShift = 3;
 
 __global__ __launch_bounds__(kValThreads) void k_validate_tile(ExactArgs a, int ls,
                                                                int64_t *n_invalid, int32_t *status)
@@ -1683,7 +1686,7 @@ __global__ __launch_bounds__(kValThreads) void k_validate_tile(ExactArgs a, int 
     }
 }
 
-// More groups than eight plans' bitmaps of k_validate_tile leave room for: one
+// More groups than k_validate_tile's bitmaps leave room for (qlm_validate_plans): one
 // workgroup per plan.
 __global__ __launch_bounds__(256) void k_validate_plans(ExactArgs a, int64_t *n_invalid,
                                                        int32_t *status)
@@ -1836,6 +1839,7 @@ using qlm_internal::hip_fail;
 
 constexpr size_t kLdsLimit = 160 * 1024;   // gfx950 LDS per workgroup
 constexpr int64_t kValBlocks = 512;        // workgroups of k_validate_tile that fill the chip
+constexpr int64_t kFewValBlocks = 16;      // and that are too few for plans side by side
 
 // Dynamic LDS of the scoring kernel: everything but its static tail table.
 constexpr size_t kScoreLdsLimit = kLdsLimit - sizeof(float) * 2 * kTailCells;
@@ -2340,11 +2344,17 @@ int qlm_validate_plans(const qlm_problem *problem, const qlm_plans *plans, int64
     if (lds > kLdsLimit) return fail(QLM_ERR_CAPACITY, "too many groups to validate");
     const int64_t P = plans->n_plans;
     // plans a workgroup: 64, fewer (down to 8, whose rows are 32 bytes) where that
-    // leaves less than two workgroups a CU or where the bitmaps do not fit
+    // leaves less than two workgroups a CU; down to one while they are not even 16
+    // (one plan of 25000 groups: 32 us in a workgroup for eight, 14 in its own, 24 in
+    // one of k_validate_plans's 256 threads; 40 plans 33, 18, 29; 128 plans 41 in
+    // workgroups for eight and 49).  k_validate_plans where more plans than that leave
+    // no room for eight bitmaps.
     int ls = kMaxValShift;
-    while (ls > kMinValShift && (P >> ls) < kValBlocks) --ls;
-    while (ls >= kMinValShift && (lds << ls) + 1024 > kLdsLimit) --ls;
-    const bool tile = ls >= kMinValShift;
+    while (ls > kRowValShift && (P >> ls) < kValBlocks) --ls;
+    while (ls > 0 && (P >> ls) < kFewValBlocks) --ls;
+    const bool few = ls < kRowValShift;
+    while (ls > (few ? 0 : kRowValShift) && (lds << ls) + 1024 > kLdsLimit) --ls;
+    const bool tile = (lds << ls) + 1024 <= kLdsLimit;
     const size_t bytes = tile ? lds << ls : lds;
     const void *kernel = tile ? (const void *)k_validate_tile : (const void *)k_validate_plans;
     e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);

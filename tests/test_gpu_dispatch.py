@@ -221,11 +221,13 @@ def test_fcfs_exact_many(qlm, orc, G, I, P, sizes):
     assert int(bi.item()) == 0 and float(bs.item()) == 0.0
 
 
-# Validation: 8 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
-# a workgroup per plan past them; each kind of malformed plan at the tile's edges
+# Validation: 1 to 64 plans a workgroup (by plan count and by the bitmaps' size) and
+# a smaller workgroup per plan past them; each kind of malformed plan at the tile's edges
 @pytest.mark.parametrize("G,I,P,ld", [
     (1, 1, 5, 5), (33, 4, 4097, 4100), (64, 1, 9000, 9000), (500, 9, 16500, 16501),
-    (300, 9, 33000, 33000), (5000, 16, 70, 70), (25000, 3, 33, 40), (170000, 2, 3, 3)])
+    (300, 9, 33000, 33000), (5000, 16, 70, 70), (25000, 3, 33, 40), (170000, 2, 3, 3),
+    (25000, 5, 1, 1), (16001, 5, 17, 17), (9000, 3, 127, 127), (9000, 3, 128, 130),
+    (170000, 2, 129, 129)])
 def test_validate_tiles(qlm, G, I, P, ld):
     import torch
     pr, pl = make(G, I, P, 900 + G, ld=ld)
