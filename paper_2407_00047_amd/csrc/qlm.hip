@@ -2032,7 +2032,10 @@ int score_resident(ScoreKernel k, int waves, size_t lds, int *cus, int64_t *bloc
 //
 // Workgroups hold 16 wavefronts, and fewer (down to one tile's) where that
 // leaves CUs without a workgroup: 16384 plans of 128 groups on 16 workgroups
-// took 50 us, on 256 32 us (unsplit), 23 us split in four.
+// took 50 us, on 256 32 us (unsplit), 23 us split in four.  But no less than one
+// a SIMD unless it copies at most 16 groups' records a lane: 64 plans of 8192 groups
+// on one queue take 1.17 ms with one wavefront, 1.13 with four or sixteen; 300 plans
+// 1.17, 1.14 and 1.26.
 int score_grid(ScoreKernel k, size_t lds, int64_t P, int G, int I, int *grid, int *threads,
                int32_t *nparts, int32_t *first, int32_t *step)
 {
@@ -2052,14 +2055,15 @@ int score_grid(ScoreKernel k, size_t lds, int64_t P, int G, int I, int *grid, in
     }
     if (n == 1) *first = *step = G;
     int64_t need = (tiles + wpb / n - 1) / (wpb / n);
-    while (wpb > n && 10 * need < 9 * (int64_t)cus) {
+    auto copies = [&](int w) { return w >= 4 || (int64_t)w * kWave * 16 >= G; };
+    for (int w2 = wpb / 2; w2 >= n && 10 * need < 9 * (int64_t)cus && copies(w2); w2 /= 2) {
         // (all of them resident still: a launch with parts has one round)
         int64_t fit2 = 0;
-        rc = score_resident(k, wpb / 2, lds, &cus, &fit2);
+        rc = score_resident(k, w2, lds, &cus, &fit2);
         if (rc) return rc;
-        const int64_t need2 = (tiles + wpb / 2 / n - 1) / (wpb / 2 / n);
+        const int64_t need2 = (tiles + w2 / n - 1) / (w2 / n);
         if (need2 > fit2) break;
-        wpb /= 2;
+        wpb = w2;
         need = need2;
         fit = fit2;
     }
