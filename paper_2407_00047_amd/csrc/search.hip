@@ -2172,6 +2172,10 @@ __global__ __launch_bounds__(kThreads) void k_sout(SearchArgs a, qlm_plans_out o
 // placement session keeps only the plan, the slot of every group and the
 // queue scores up to date between its steps.  A group at its queue's head is
 // running and is not placed (k_place_pick keeps the plan).
+// kMany: more than kManyQueues queues.
+constexpr int kManyQueues = 16 * kWave;
+
+template <bool kMany>
 __global__ __launch_bounds__(kThreads) void k_place_eval(SearchArgs a, int group)
 {
     const int G = a.G, I = a.I;
@@ -2186,13 +2190,26 @@ __global__ __launch_bounds__(kThreads) void k_place_eval(SearchArgs a, int group
     int q64 = lane < I ? qof[lane] : INT_MAX;          // (read beside the group's slot)
     const int s = __builtin_amdgcn_readfirstlane(clampi(a.inv[b * G + group], 0, G - 1));
     // the group's queue: the last g with qof[g] <= s, counted 64 queues at a time
-    // (a binary search is six reads, one after another)
+    // (a binary search is six reads and more, one after another; with more than 16
+    // times 64 queues it is the shorter chain: 4096 queues 13 us, counted 32)
     int before = 0;
-    for (int q0 = 0;;) {
-        before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q64 <= s));
-        q0 += kWave;
-        if (q0 >= I) break;
-        q64 = q0 + lane < I ? qof[q0 + lane] : INT_MAX;
+    if (!kMany) {
+        for (int q0 = 0;;) {
+            before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q64 <= s));
+            q0 += kWave;
+            if (q0 >= I) break;
+            q64 = q0 + lane < I ? qof[q0 + lane] : INT_MAX;
+        }
+    } else {
+        int hi = I;
+        while (before < hi) {
+            const int mid = (before + hi) >> 1;
+            if (qof[mid] <= s)
+                before = mid + 1;
+            else
+                hi = mid;
+        }
+        before = __builtin_amdgcn_readfirstlane(before);
     }
     const int g = clampi(before - 1, 0, I - 1);
     const int bg = clampi(qof[g], 0, G);
@@ -2272,6 +2289,7 @@ __global__ __launch_bounds__(kThreads) void k_place_eval(SearchArgs a, int group
 // The place with the lowest exact score (lowest c on ties), applied; a running
 // group stays, and the plan keeps its score.  Every place's total is formed here,
 // the queue scores added in queue order.
+template <bool kMany>
 __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *queue,
                                                          double *score)
 {
@@ -2280,6 +2298,7 @@ __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *
     __shared__ int64_t kk;
     __shared__ int kp, kg, stay;
     __shared__ double sQ[kMaxSearchInstances];         // the queue scores
+    __shared__ double sT[kMany ? kMaxSearchInstances + 1 : 1];   // and, if many, their running sums
     __shared__ int scand[kThreads];
     __shared__ double scex[kThreads];
     const int64_t b = blockIdx.x;
@@ -2303,9 +2322,41 @@ __global__ __launch_bounds__(kThreads) void k_place_pick(SearchArgs a, int32_t *
         stay = a.dq[b * 4 + 2];
     }
     __syncthreads();
+    // the running sums of many queue scores, in queue order (the additions of a serial
+    // sum, rippled across the first wavefront's lanes)
+    if (kMany) {
+        if (threadIdx.x < kWave) {
+            const int lane = threadIdx.x;
+            double carry = 0.0;
+            if (lane == 0) sT[0] = 0.0;
+            for (int q0 = 0; q0 < I; q0 += kWave) {
+                const int cnt = min(kWave, I - q0);
+                const double x = lane < cnt ? sQ[q0 + lane] : 0.0;
+                const double lx = from_left0(x);
+                double t = carry;
+                const int steps = __builtin_amdgcn_readfirstlane(cnt - 1);
+                for (int j = 0; j < steps; j += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) t = from_left(t) + lx;
+                }
+                const double t1 = t + x;
+                if (lane < cnt) sT[q0 + lane + 1] = t1;
+                carry = lane_value(t1, cnt - 1);
+            }
+        }
+        __syncthreads();
+    }
     // the queue scores added in queue order, with those of queues g and h replaced
-    // (every lane reads the same score at a time, several ahead)
+    // (every lane reads the same score at a time, several ahead; many of them from the
+    // first replaced one on, a lane each: four steps over 4096 queues 18.5 ms, 10.1 so)
     auto total2 = [&](int g, double qg, int h, double qh) __attribute__((always_inline)) {
+        if (kMany) {
+            int q = min(g < 0 ? I : g, h < 0 ? I : h);
+            double t = sT[q];
+#pragma unroll 8
+            for (; q < I; ++q) t += q == g ? qg : (q == h ? qh : sQ[q]);
+            return t;
+        }
         double t = 0.0;
 #pragma unroll 8
         for (int q = 0; q < I; ++q) {
@@ -2993,12 +3044,13 @@ int place_step(SearchArgs &a, int32_t group, int32_t *queue, double *score, hipS
     qlm_internal::TimedLaunch tl;
     if ((rc = qlm_internal::timing_begin(stream, &tl))) return rc;
     const int eblk = (2 * a.I + 1 + kWaves - 1) / kWaves;
-    hipLaunchKernelGGL(k_place_eval, dim3((unsigned)(eblk * a.B)), dim3(kThreads), 0, stream, a,
-                       group);
+    const bool many = a.I > kManyQueues;
+    hipLaunchKernelGGL(many ? k_place_eval<true> : k_place_eval<false>,
+                       dim3((unsigned)(eblk * a.B)), dim3(kThreads), 0, stream, a, group);
     if ((rc = launched("k_place_eval launch"))) return rc;
     qlm_internal::timing_end(stream, &tl);
-    hipLaunchKernelGGL(k_place_pick, dim3((unsigned)a.B), dim3(kThreads), 0, stream, a, queue,
-                       score);
+    hipLaunchKernelGGL(many ? k_place_pick<true> : k_place_pick<false>, dim3((unsigned)a.B),
+                       dim3(kThreads), 0, stream, a, queue, score);
     return launched("k_place_pick launch");
 }
 

@@ -301,6 +301,27 @@ def test_search_incremental(qlm, G, I, W, steps, kind):
         assert int((whole["trace"] >= G * (W + I)).sum()) > 0       # a relocation among them
 
 
+# Placements at the line where queues become many (the group's queue by a search, the
+# queue scores' running sums kept) and past it
+@pytest.mark.parametrize("I", [1024, 1025, 2100])
+def test_place_many_queues(qlm, orc, I):
+    import torch
+    G, P = 3000, 2
+    pr, pl = make(G, I, P, 800 + I)
+    dpr, dpl = device_inputs(pr, pl)
+    for group in (0, 1, G // 2, G - 1):
+        print("case place many", I, group, flush=True)
+        r = qlm.place_group(dpr, dpl, group)
+        torch.cuda.synchronize()
+        out = r["plans"]
+        for p in range(P):
+            o = orc.place_group(pr, pl, p, group)
+            assert int(r["queue"][p]) == o["queue"]
+            assert np.array_equal(out.perm[:, p].cpu().numpy(), o["perm"])
+            assert np.array_equal(out.qoff[:, p].cpu().numpy(), o["qoff"])
+        assert torch.equal(qlm.rwt_score_exact(dpr, out, np.arange(P)), r["score"])
+
+
 # The general walk in parts: groups without requests or variance, counts and
 # models beyond the compact records; penalties and detail across the parts
 @pytest.mark.parametrize("G,I,P,kind", [
