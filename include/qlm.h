@@ -261,8 +261,9 @@ int qlm_search_moves(const qlm_problem *problem, const qlm_plans *plans, int32_t
                      void *ws, size_t ws_bytes, double *move_score, qlm_stream stream);
 
 /*
- * Screened scores of every move, the first stage of every qlm_local_search
- * step: score [P][n_moves] and bound [P][n_moves] device out, plan-major like
+ * Screened scores of every move, the first stage of a qlm_local_search (whose
+ * later steps renew them for the two queues that the step before changed):
+ * score [P][n_moves] and bound [P][n_moves] device out, plan-major like
  * qlm_search_moves.  For every move |score - exact score| <= bound, where the
  * exact score is the one qlm_search_moves returns.  The screen walks a move's
  * target queue from cached waits and variances with the normal tail read from
@@ -279,10 +280,11 @@ int qlm_search_screen(const qlm_problem *problem, const qlm_plans *plans, int32_
  * Steepest-descent local search from every start plan, independently: each
  * step scores every move, takes the lowest score (the lowest k on ties) and
  * applies it when it is strictly below the current plan's score; otherwise
- * that plan has converged and stops.  At most max_steps steps.  Each step
- * screens every move (qlm_search_screen), scores exactly only the moves that
- * can still be the lowest and improve, and decides on the exact scores, so
- * the steps are those of a search that scores every move exactly.
+ * that plan has converged and stops.  At most max_steps steps.  Every move is
+ * screened (qlm_search_screen), again where a step changed the queues that it
+ * concerns; each step scores exactly only the moves that can still be the lowest
+ * and improve, and decides on the exact scores, so the steps are those of a
+ * search that scores every move exactly.
  *   start   the start plans (read before any output is written, so `out` may
  *           name the same arrays)
  *   out     the final plans, with their eviction words (required; QLM_ERR_ARG
@@ -414,7 +416,8 @@ size_t qlm_fcfs_workspace_bytes(const qlm_problem *problem, int64_t n_plans, int
  * the start E[W] in double (one walk of each queue); per request, the margin
  * in double, the variance in single precision and the normal tail from the
  * 1024-cell table, except where that is surely exactly 0 or 1;
- * single-precision sums of at most 32 terms.
+ * single-precision sums of at most 31 terms, added up in 64-bit fixed point
+ * (rounded to the nearest 2^-34 with 2^28 requests or more, finer with fewer).
  */
 int qlm_fcfs_score(const qlm_problem *problem, const qlm_plans *plans, const float *req_slo,
                    int64_t n_requests, void *ws, size_t ws_bytes, double *score,
@@ -515,11 +518,12 @@ const char *qlm_last_error(void);
  * each call is bracketed by HIP events on the call's stream: the plan-scoring
  * kernel of every qlm_rwt_score / qlm_best_plan call, the kernel that scores
  * the reassignment moves in every qlm_search_moves / qlm_search_screen call
- * and every step of qlm_local_search, the candidate kernel of every
- * qlm_place_group call, and the per-request kernel of every plan
- * chunk of qlm_fcfs_score / qlm_fcfs_best_plan.  qlm_timing_read waits for the recorded events and
- * returns the number of timed launches and their summed duration in
- * milliseconds since the last reset, then resets.
+ * and the first step of a qlm_local_search, the one that renews the screens in
+ * each later step, the candidate kernel of every qlm_place_group call, and the
+ * kernel that evaluates tails of every plan chunk of qlm_fcfs_score /
+ * qlm_fcfs_best_plan.  qlm_timing_read waits for the recorded events and returns
+ * the number of timed launches and their summed duration in milliseconds since the
+ * last reset, then resets.
  */
 int qlm_timing_enable(int on);
 int qlm_timing_read(int64_t *launches, double *total_ms);

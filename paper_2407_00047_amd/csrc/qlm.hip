@@ -388,8 +388,9 @@ __global__ __launch_bounds__(1024) void k_score_form(ScoreArgs a, int32_t *form)
 // not start with the plan first adds up its first queue's slots before it, in the
 // same order.  Group ids are read 8 slots ahead, and a queue's end with the next
 // three queues' in one go, so that most heads (some lane has one in 4 of 10 slots
-// with 16 queues of 64 groups) wait for no read.  1024 groups, 32768 plans: a call of
-// 123 us; with one wavefront a plan, each head waiting, 472.
+// with 16 queues of 64 groups) wait for no read.  1024 groups, 32768 plans: a
+// best_plan call of 119 us; with one wavefront for a plan's whole length, each head
+// waiting, 620.
 template <bool EVICT, bool PEN, bool DETAIL>
 __device__ void walk_general(const ScoreArgs &a, const Lds &L, uint32_t tail0, int64_t tb, int lp,
                              bool det, int64_t dq, int s_begin, int s_end, double &S_out,
@@ -880,8 +881,11 @@ __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(4
 
         // Software pipeline over the slots of the plan:
         //   ring[8]   group ids of the next 8 slots (buffer loads, 8 slots ahead: with
-        //             four wavefronts per SIMD that covers the memory latency, and
-        //             leaves the kernel within 128 registers without spills)
+        //             four wavefronts per SIMD that covers the memory latency.  The
+        //             kernel takes all 128 registers and spills 12 to 15 (31 to 51 with
+        //             penalties or detail); what is spilled is used in the set-up, the
+        //             general walk and the slow queue entry, and no scratch traffic
+        //             shows at 8192 groups)
         //   rec[4]    LDS records of slots s..s+2 (gathered D = 2 slots ahead)
         //   cost      swap/eviction seconds of slot s, read during slot s-1
         //   rsn       rsqrt of slot s's variance ahead, formed at the end of slot s-1
@@ -1516,9 +1520,11 @@ __device__ void pick_best(const int64_t *cand, int64_t n, bool sums, int I, cons
 // per-(candidate, queue) sums fit (count <= cap), one wavefront per (candidate,
 // queue) writes its queue's score to Q; else every workgroup scores whole
 // candidates and writes the plan's score over its screened score in X.  The
-// workgroup that finishes the last task picks (a launch of its own for that took
-// 4 to 6 us).  With few plans (kSmall) the candidates are not listed by a kernel
-// before: every workgroup selects them itself, four plans a thread; best_plan calls
+// workgroup that finishes the last task picks.  That saves small calls a launch and
+// the gap before it; at 131,072 plans of 8192 groups it saves nothing (re-score and
+// pick 13.5 + 5.2 us as two kernels, 19.0 as one: the counting waits for the scores
+// to be written back).  With few plans (kSmall) the candidates are not listed by a
+// kernel before: every workgroup selects them itself, four plans a thread; best_plan calls
 // end to end, listed before | selected here: 8 groups, 1 queue, 256 plans 16.8 |
 // 15.8 us and 1024 plans 17.7 | 16.2; 512 groups, 64 queues, 1024 plans 54.4 | 53.1.
 constexpr int kSmallPlans = 1024;

@@ -215,7 +215,7 @@ struct SearchArgs {
     int32_t *cand;                // [n_moves] candidate moves
     double *cex;                  // [n_moves] their exact scores
     int32_t *ncand;               // [1]
-    double *U;                    // [1] min(F + D)
+    double *U;                    // [1] placement: the group's queue without it
     int32_t *scratch;             // [2 G] shifts of k_spick
     int32_t *dq;                  // [4] placement: the group's slot and queue, and
                                   // whether it is running (stays); search: the two
@@ -2842,7 +2842,8 @@ int check_search(const qlm_problem *pr, int64_t B, int32_t W)
     if (B < 0) return fail(QLM_ERR_ARG, "search: n_plans must be >= 0");
     const Layout L = layout(pr->n_groups, pr->n_instances, W, 1);
     const int64_t Bc = B > 0 ? B : 1;
-    // (nwg bounds the screens' grids: removals and swaps, both kinds into every queue)
+    // (nwg bounds the screens' grids: removals and swaps, both kinds into every queue;
+    // sel is no grid: moves past it have always been refused)
     const int64_t sel = (L.n_moves + kThreads - 1) / kThreads;
     if ((int64_t)L.nwg * Bc > INT_MAX || sel * Bc > INT_MAX || (int64_t)L.nws * Bc > INT_MAX ||
         (int64_t)kExactBlocks * Bc > INT_MAX ||
