@@ -395,7 +395,7 @@ int qlm_seed_plans(const qlm_problem *problem, int32_t n, const int32_t *policy,
  * Every call takes a device workspace, 256-byte aligned, used as scratch.
  * The plans are screened in chunks: a chunk of c plans needs about 21 bytes per
  * group and plan for the lists of groups, and every call 4.25 bytes per request,
- * 184 per group and 8 (I + 2) bytes per plan.  qlm_fcfs_workspace_bytes(problem, n_plans,
+ * 168 per group and 8 (I + 2) bytes per plan.  qlm_fcfs_workspace_bytes(problem, n_plans,
  * n_requests, chunk_plans) is the size for chunks of chunk_plans plans
  * (rounded up to a multiple of 64; 0 = as many as 1 GiB of lists holds, the
  * size to use), 0 for an invalid problem.  A call uses the largest chunk the

@@ -118,7 +118,7 @@ constexpr int kHalf = 16;                   // of which so many SLOs are staged 
 constexpr int kEval = 4;                    // and so many evaluated at least
 constexpr int kSub = 8;                     // slots of a k_fwalk batch
 constexpr int kTailWaves = 4;               // wavefronts of a k_ftails workgroup
-constexpr int kBounds = 4;                  // blocks whose bounds are read at a time
+constexpr int kBounds = 2;                  // blocks whose bounds are read at a time
 constexpr int kShare = 2048;                // groups of one, while the list is that long
 constexpr int kBlockList = 2 * kWave;       // blocks a wavefront's list holds
 constexpr int kMaxFcfsGroups = 1 << 16;
@@ -149,14 +149,15 @@ __device__ inline int grp_model(const FGrp &g) { return (int)(g.cm >> 21); }
 __device__ inline float grp_smin(const FGrp &g) { return __uint_as_float(g.bounds << 16); }
 __device__ inline float grp_smax(const FGrp &g) { return __uint_as_float(g.bounds & 0xFFFF0000u); }
 
-// ... and for the requests: how many are scored (clamped to n_requests), where
-// their SLOs start, how many a block holds (blocks_of), and the group's statistics
-// again (k_ftails reads them for 64 groups at a time, a cache line each).
-struct alignas(32) FReq {
-    uint32_t first, n, per;
+// ... and for the requests: where their SLOs start, how many are scored (clamped to
+// n_requests) with how many a block holds (blocks_of) above, and the group's
+// statistics again: k_ftails reads 64 groups' at a time, in one read of 16 bytes.
+struct alignas(16) FReq {
+    uint32_t first, np;
     float mu, var;
-    uint32_t pad[3];
 };
+__device__ inline int req_count(const FReq &r) { return (int)(r.np & kCountMask); }
+__device__ inline int req_block(const FReq &r) { return (int)(r.np >> 21); }
 
 // The blocks of n requests: as few as hold them in 32 each, and of one size (the
 // last may be smaller).  A wavefront evaluates 64 blocks in as many steps as the
@@ -299,12 +300,11 @@ __global__ __launch_bounds__(kPrepThreads) void k_fprep(FArgs a)
         a.grp[i] = g;
         FReq r;
         r.first = (uint32_t)lo;
-        r.n = (uint32_t)(hi - lo);
-        const int nb = max(blocks_of((int)r.n), 1);
-        r.per = (r.n + (uint32_t)nb - 1u) / (uint32_t)nb;
+        const uint32_t n = (uint32_t)(hi - lo);
+        const uint32_t nb = (uint32_t)max(blocks_of((int)n), 1);
+        r.np = n | ((n + nb - 1u) / nb << 21);
         r.mu = g.mu;
         r.var = g.var;
-        r.pad[0] = r.pad[1] = r.pad[2] = 0u;
         a.req[i] = r;
         if (i == a.G - 1) {
             a.nreq[0] = (double)hi;
@@ -332,14 +332,14 @@ __global__ __launch_bounds__(kThreads) void k_fblocks(FArgs a)
     if (i >= a.G) return;
     const int lane = threadIdx.x & (kWave - 1);
     const FReq q = a.req[i];
-    const int n = (int)q.n, nb = blocks_of(n);
+    const int n = req_count(q), per = req_block(q), nb = blocks_of(n);
     const int j = lane & (kReqBlk - 1);
     float gmin = INFINITY, gmax = -INFINITY;
     for (int b0 = 0; b0 < nb; b0 += kWave / kReqBlk) {
         const int b = b0 + lane / kReqBlk;
-        const int r = b * (int)q.per + j;
+        const int r = b * per + j;
         float lo = INFINITY, hi = -INFINITY, v = INFINITY;
-        if (j < (int)q.per && r < n) {
+        if (j < per && r < n) {
             v = a.req_slo[q.first + r];
             lo = v == v ? v : -INFINITY;
             hi = v == v ? v : INFINITY;
@@ -915,14 +915,19 @@ __device__ __attribute__((always_inline)) inline void eval_blocks(const FArgs &a
 // could take one group of 64 plans and evaluate all of its requests with the SLOs
 // in scalar registers (0.31 + 1.45 ms for 4096 plans of 8192 groups of 128
 // requests, however many are sure; the call 2.0).  Here few requests are evaluated:
-// 0.10 + 0.16 ms on random plans, the call 0.41.  With spreads as wide as the waits
+// 0.10 + 0.16 ms on random plans, the call 0.40.  With spreads as wide as the waits
 // nearly all are, and the L1's misses count: a line per lane for the SLOs, one per
 // block for its bounds and two per group took the kernel to 3.0 ms; 64 blocks' SLOs
-// read as whole lines and passed through LDS, four blocks' bounds and all of a
+// read as whole lines and passed through LDS, two blocks' bounds and all of a
 // group's numbers read at a time leave 1.85 (arithmetic busy 88% of it), the call
-// 2.11; where the groups are smaller it is the faster one (33 requests: 0.98 ms for
-// 1.03).  With the lists in LDS and both passes in one kernel its registers left two
-// wavefronts a SIMD: 1.40 ms on random plans.
+// 2.11 to 2.16.  So the sorted form would still be the faster one for groups of 128
+// requests that all need their tails, by 4 to 14% (2048 groups), and this is for
+// smaller groups (33 requests 0.93 ms for 1.02, 32 3.68 for 4.30 on 16384 plans) and
+// wherever a third of the requests are sure.  With the lists in LDS and both passes
+// in one kernel its registers left two wavefronts a SIMD: 1.40 ms on random plans.
+// Four wavefronts a workgroup: with two or three fewer lists wait for room (6000
+// plans of 1000 groups 87 and 91 us, 93 with four, 110 with eight) and the tables
+// are copied more often (8192 groups 439 and 431, 417 with four).
 __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_ftails(
     FArgs a, int64_t pc, uint32_t lists_n)
 {
@@ -978,11 +983,11 @@ __global__ __launch_bounds__(kTailWaves * kWave) __attribute__((amdgpu_waves_per
                 const int i = (int)(e.id & 0xFFFFu);
                 const FReq r = a.req[i];
                 const FInst in = a.inst[q];
-                per = (int)r.per;
+                per = req_block(r);
                 c1 = (double)r.mu / in.theta;
                 v1 = (float)((double)r.var * in.vscale);
                 flat = r.var == 0.0f && e.v0 == 0.0f;
-                n = mine ? (int)r.n : 0;
+                n = mine ? req_count(r) : 0;
                 block = block_of(r.first, i, 0);
                 blk = a.blk + block;
 #pragma unroll
@@ -1244,7 +1249,7 @@ __global__ __launch_bounds__(kExactThreads) void k_fexact(FArgs a, const int64_t
             if (i >= 0) {
                 const FReq q = a.req[i];
                 x.slo = a.req_slo + q.first;
-                x.n = (int)q.n;
+                x.n = req_count(q);
                 x.EW = A / theta + K;
                 x.step = (double)q.mu / theta;
                 x.var = (double)q.var;
