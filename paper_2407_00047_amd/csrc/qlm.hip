@@ -34,8 +34,10 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <type_traits>
 #include <vector>
 
@@ -1960,13 +1962,13 @@ int device_cus(int *cus)
     return QLM_OK;
 }
 
-struct OccKey {
-    int dev, threads;
-    ScoreKernel k;
-    size_t lds;
-};
+// A scheduler's group count, and with it the LDS bytes, differs from call to call, and
+// a call asks for up to five workgroup sizes: found by order, and not kept without end
+// (in a list searched from its start, 400 group counts added 1 to 2 us to every call).
+using OccKey = std::tuple<int, int, ScoreKernel, size_t>;   // device, threads, kernel, LDS
+constexpr size_t kMaxOcc = 4096;
 std::mutex g_occ_mu;
-std::vector<std::pair<OccKey, std::pair<int, int>>> g_occ;   // -> (CUs, blocks per CU)
+std::map<OccKey, std::pair<int, int>> g_occ;                // -> (CUs, blocks per CU)
 
 // CU count and resident workgroups per CU for kernel k with that many threads
 // and lds bytes, cached.
@@ -1975,15 +1977,15 @@ int occupancy(ScoreKernel k, int threads, size_t lds, int *cus, int *per_cu)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    const OccKey key(dev, threads, k, lds);
     {
         std::lock_guard<std::mutex> lk(g_occ_mu);
-        for (auto &it : g_occ)
-            if (it.first.dev == dev && it.first.threads == threads && it.first.k == k &&
-                it.first.lds == lds) {
-                *cus = it.second.first;
-                *per_cu = it.second.second;
-                return QLM_OK;
-            }
+        const auto it = g_occ.find(key);
+        if (it != g_occ.end()) {
+            *cus = it->second.first;
+            *per_cu = it->second.second;
+            return QLM_OK;
+        }
     }
     int rc = device_cus(cus);
     if (rc) return rc;
@@ -1993,7 +1995,8 @@ int occupancy(ScoreKernel k, int threads, size_t lds, int *cus, int *per_cu)
     if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (*per_cu < 1) *per_cu = 1;
     std::lock_guard<std::mutex> lk(g_occ_mu);
-    g_occ.push_back({OccKey{dev, threads, k, lds}, {*cus, *per_cu}});
+    if (g_occ.size() >= kMaxOcc) g_occ.clear();
+    g_occ[key] = {*cus, *per_cu};
     return QLM_OK;
 }
 

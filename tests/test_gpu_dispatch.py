@@ -395,3 +395,31 @@ def test_best_plan_candidates(qlm, orc, G, I, P, kind):
     osc, _ = orc.score_plans(pr, pl)
     _, obs = assert_argmin(int(bi.item()), osc, (G, I, P))
     assert abs(float(bs.item()) - obs) <= 1e-12 * abs(obs)
+
+
+# The grid's occupancies are kept by sizes, and no more than 4096 of them: group counts
+# past that many, then an early one again
+def test_many_group_counts(qlm, orc):
+    import ctypes
+    import torch
+    G = 6000
+    pr, pl = make(G, 1, 64, 5, evict=False)
+    dpr, dpl = device_inputs(pr, pl)
+    # the identity order, of which a problem of n groups takes the first n
+    dpl.perm.copy_(torch.arange(G, dtype=torch.int32, device="cuda")[:, None].expand(G, 64))
+    lib, ws = qlm.library(), qlm.workspace(dpr, 64)
+    out = (torch.empty(1, dtype=torch.int64, device="cuda"),
+           torch.empty(1, dtype=torch.float64, device="cuda"))
+    first = None
+    for n in [40] + list(range(41, 4600)) + [40]:
+        sub = qlm.Problem.from_buffer_copy(dpr.struct)
+        sub.n_groups = n
+        dpl.qoff[1:] = n
+        assert lib.qlm_best_plan(ctypes.byref(sub), ctypes.byref(dpl.struct), ws.data_ptr(),
+                                 ws.numel(), out[0].data_ptr(), out[1].data_ptr(), None) == 0
+        if n == 40:
+            torch.cuda.synchronize()
+            score = float(out[1].item())
+            assert first is None or score == first
+            first = score
+    torch.cuda.synchronize()
